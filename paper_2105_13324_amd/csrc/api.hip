@@ -86,7 +86,7 @@ int cfd_hmax(const mc_problem& p) {
 bool cfd_ok(const mc_problem& p) { return cfd_layers(p) >= 1 && cfd_hmax(p) <= CFD_MAX_H; }
 
 struct Layout {
-    size_t desc, prefix, state;
+    size_t desc, prefix;
     std::vector<size_t> q, q8, pal, runs, bsum, bcnt, guide, views, kn, lay, kern, hw;
     size_t total;
 };
@@ -95,7 +95,7 @@ bool plan(const mc_problem* probs, int n, Layout& L, bool cfd = false) {
     size_t off = 0;
     L.desc = off;   off += align256(sizeof(ProbDesc) * (size_t)n);
     L.prefix = off; off += align256(sizeof(uint64_t) * 2 * ((size_t)n + 1));
-    L.state = off;  off += align256(sizeof(CallState));
+    off += 256;                                  // spare (a workspace's size stays what it was)
     L.q.resize(n); L.q8.resize(n); L.pal.resize(n); L.runs.resize(n); L.bsum.resize(n); L.bcnt.resize(n);
     L.guide.resize(n); L.views.resize(n); L.kn.resize(n);
     L.lay.assign(n, 0); L.kern.assign(n, 0); L.hw.assign(n, 0);
@@ -292,20 +292,29 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
     const int vr = opt ? opt->variance_reduction : 0;
     if (bpc <= 0) bpc = transport_blocks_per_cu(block, fd, vr);
     if (!(opt && opt->hist_per_lane > 0)) {
-        // automatic claim size (results do not depend on it): half the
-        // default when there are fewer than 2048 histories per resident
-        // wavefront, which spreads small calls better (measured: 1e6
-        // histories on one view 0.33 against 0.35 ms; 1e7 and more: 16 best)
+        // automatic claim size (results do not depend on it).  Analog: equal
+        // shares, W histories per resident wavefront in the fewest claims of at
+        // most 1024, so a small call is one claim per wave (1e6 histories at
+        // 128^3: 78 us of transport with claims of 384, 83 with 512, 99 with
+        // 64; from 1e7 on 256 to 1024 measure within 2 %).  Forced detection
+        // costs more, and less evenly, per history: four claims or more per
+        // wave, of at most 256 (1e6: 361 us with 128, 381 with 512; 1e7:
+        // 2.78 ms with 256, 2.91 with 1024).
         uint64_t work = 0;
         for (int i = 0; i < n_problems; ++i) work += hd[i].work_count;
         const uint64_t waves = (uint64_t)n_cu * (uint64_t)bpc * (uint64_t)(block / 64);
-        hpl = work < 2048ull * (waves ? waves : 1) ? DEFAULT_HIST_PER_LANE / 2 : DEFAULT_HIST_PER_LANE;
+        const uint64_t share = std::max<uint64_t>(1, (work + waves - 1) / std::max<uint64_t>(1, waves));
+        if (fd) {
+            hpl = (int)std::min<uint64_t>(4, (share + 255) / 256);
+        } else {
+            const uint64_t most = 64 * DEFAULT_HIST_PER_LANE, claims = (share + most - 1) / most;
+            hpl = (int)((share + 64 * claims - 1) / (64 * claims));
+        }
     }
     const uint32_t chunk = (uint32_t)(64 * hpl);
     e = launch_prepare_call(d_desc, n_problems, (uint64_t*)(ws + L.prefix),
-                            (CallState*)(ws + L.state), status,
-                            (unsigned long long*)n_events, tally, tally_elems, tally_sq,
-                            fates, energy, counters, chunk, st);
+                            status, (unsigned long long*)n_events, tally, tally_elems, tally_sq,
+                            chunk, st);
     if (e != hipSuccess) return hip_fail(e);
     TransportArgs a;
     a.descs = d_desc;
@@ -313,7 +322,7 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
     a.work_prefix = (const uint64_t*)(ws + L.prefix);
     a.total_work = 0;
     a.chunk = chunk;
-    a.state = (CallState*)(ws + L.state);
+    a.queues = hd[0].block_sums + ACC_COPIES * ACC_WORDS;
     a.tally = tally;
     a.tally_sq = tally_sq;
     a.fates = fates;
@@ -334,7 +343,7 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
     if (ev1 && (e = hipEventRecord(ev1, st)) != hipSuccess) return hip_fail(e);
     for (int i = 0; cfd && i < (int)hd.size(); ++i)
         if ((e = launch_cfd_convolve(d_desc + i, hd[i], tally, st)) != hipSuccess) return hip_fail(e);
-    if ((e = launch_tally_check(d_desc, n_problems, tally, fates, status, st)) != hipSuccess) return hip_fail(e);
+    if ((e = launch_finish(a, st)) != hipSuccess) return hip_fail(e);
     return MC_OK;
 }
 

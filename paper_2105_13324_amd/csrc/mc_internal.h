@@ -90,7 +90,7 @@ struct ProbDesc {
     uint8_t* q8;                    // palette codes, same layout (when pal_state == 0)
     uint32_t* palette;              // PALETTE_N thresholds, open-addressing hash table
     uint4* runs;                    // emission runs (EmitRun layout), n_runs entries
-    uint64_t* block_sums;           // scan scratch: activity per block
+    uint64_t* block_sums;           // scan scratch: activity per block; then the call's totals
     uint32_t* block_cnt;            // scan scratch: runs starting in each block
     uint2* guide;                   // emission buckets (EmitBucket layout), n_buckets entries
     float2* views;                  // (cos, sin) per view
@@ -180,11 +180,17 @@ __device__ inline uint32_t brick_index(uint32_t ix, uint32_t iy, uint32_t iz, ui
     return (brick << (3 * b)) | local;
 }
 
-// Global counters of one call (in the workspace).
-struct CallState {
-    unsigned long long next_chunk;
-    unsigned long long pad[7];
-};
+// Scratch of the transport call in a problem's block_sums (idle once staging
+// is done; at least BLOCK_SCRATCH_MIN words): ACC_COPIES copies of the
+// problem's totals, one 128-byte line each (the waves spread over them, so the
+// flushes do not queue on one address), and in problem 0's after them the
+// N_QUEUES claim counters, one line each.
+constexpr int ACC_COPIES = 64;
+constexpr int ACC_WORDS = 16;       // uint64 per copy (one 128-byte line)
+enum { ACC_FATES = 0, ACC_ESC = 7, ACC_COUNTERS = 8, ACC_CAPPED = 14 };
+constexpr int N_QUEUES = 32;        // at most 64: a wavefront looks at all at once
+constexpr int BLOCK_SCRATCH_MIN = 2048;
+static_assert((ACC_COPIES + N_QUEUES) * ACC_WORDS <= BLOCK_SCRATCH_MIN, "transport scratch");
 
 // Host launchers (cgsm.hip): block-summed source; coarse projection expanded
 // to the normal pixels.
@@ -226,7 +232,7 @@ struct TransportArgs {
     uint64_t total_work;
     uint32_t chunk;                 // work indices per claim (per wave)
     int32_t forced_detection;       // 1: forced detection in the tally; 2: into CFD layers
-    CallState* state;
+    uint64_t* queues;               // claim counters (N_QUEUES lines of ACC_WORDS)
     int64_t* tally;
     int64_t* tally_sq;
     int64_t* fates;
@@ -241,17 +247,16 @@ struct TransportArgs {
 };
 constexpr int32_t VR_FORCED_DIRECTION = 1, VR_FORCED_INTERACTION = 2;
 hipError_t launch_transport(const TransportArgs& a, int grid, int block, hipStream_t s);
-// After every tally writer of a forward call: MC_STATUS_TALLY_OVERFLOW when a
-// problem's tally may have left the Q31.32 range.
-hipError_t launch_tally_check(const ProbDesc* d_desc, int n_problems, const int64_t* tally,
-                              const int64_t* fates, int64_t* status, hipStream_t s);
+// After every tally writer of a forward call: fates, energies and counters
+// summed from the waves' totals, the status, and MC_STATUS_TALLY_OVERFLOW when
+// a problem's tally may have left the Q31.32 range.
+hipError_t launch_finish(const TransportArgs& a, hipStream_t s);
 hipError_t launch_replay(const ProbDesc* d_desc, const int32_t* views, const uint64_t* hists,
                          int64_t n, mc_record* out, int64_t* status, int block, int32_t vr_flags,
                          float vr_omc, hipStream_t s);
 hipError_t launch_prepare_call(const ProbDesc* descs, int32_t n_problems, uint64_t* work_prefix,
-                               CallState* state, int64_t* status, unsigned long long* n_events,
+                               int64_t* status, unsigned long long* n_events,
                                int64_t* tally, uint64_t tally_elems, int64_t* tally_sq,
-                               int64_t* fates, int64_t* energy, int64_t* counters,
                                uint32_t chunk, hipStream_t s);
 
 // Host launcher (adjoint.hip)

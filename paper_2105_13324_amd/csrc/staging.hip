@@ -652,10 +652,11 @@ hipError_t launch_staging_batch(ProbDesc* d, const ProbDesc* h, int n, hipStream
 }
 
 // Entries (uint64) of a problem's block-sum scratch: the scan's block sums,
-// and before them k_reduce's partials.
+// before them k_reduce's partials, after them the transport's totals.
 size_t staging_block_scratch_u64(uint64_t nvox) {
     const uint64_t nb = (nvox + SCAN_ITEMS - 1) / SCAN_ITEMS;
     const uint64_t red = (uint64_t)REDUCE_BLOCKS * REDUCE_PART_U64;
+    static_assert(REDUCE_BLOCKS * REDUCE_PART_U64 >= BLOCK_SCRATCH_MIN, "transport scratch");
     return (size_t)(nb > red ? nb : red);
 }
 

@@ -11,14 +11,14 @@
 //    picks the counter and what the four words mean, so the dominant cost --
 //    the 10 Philox rounds -- runs with all lanes in lockstep, and only the
 //    short per-state tails diverge.
-//  * Emission is converged: a wavefront emits the next 128 histories of its
-//    chunk into an LDS stage in one phase (two per lane), and a lane whose
-//    history ends starts the next staged one.  Chunks come from one global
-//    atomic and never straddle problems, and a wavefront finishes the
+//  * Emission is converged: a wavefront emits the next histories of its
+//    chunk into an LDS stage in one phase, and a lane whose
+//    history ends starts the next staged one.  Chunks come from N_QUEUES claim
+//    counters and never straddle problems, and a wavefront finishes the
 //    histories of one problem before it starts another, so every problem
 //    constant is wave-uniform (scalar registers) even in the batched launch.
 //  * Fate counts, energies and work counters stay in registers and are
-//    reduced across the wavefront before one atomic per value; tallies are
+//    reduced across the wavefront into one of 64 copies of the totals; tallies are
 //    64-bit fixed-point integer atomics, so every sum is exact and
 //    order-independent: results are bit-identical from run to run.
 //  * Woodcock tracking: one threshold gather per tentative collision (a
@@ -59,57 +59,120 @@ __device__ __forceinline__ long long wsum64(long long v) {
     return v;
 }
 
-// Wave-wide flush of one problem's accumulators (all 64 lanes must call).
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Claims of work.  The chunks of a call (all problems, in order) are cut into
+// N_QUEUES contiguous ranges, one queue each with a counter on a line of its
+// own; workgroup b takes from queue b mod N_QUEUES.  A wave's first chunk is
+// its rank within its queue, without an atomic; later ones come from the
+// counter, and once the queue is empty from the next queue that still holds
+// chunks (all counters read at once, one lane each).  Why: a claim from one
+// counter for the whole device took 13 ns whatever the waves did, so 3072
+// resident waves waited up to 40 us for their first chunk and again for the
+// refusal at the end (10^4 histories: 67 us); and with contiguous ranges a
+// wave works on one or two of a batch's problems instead of all of them, and
+// an XCD (workgroups b mod 8) on an eighth, so it drains less often and its L2
+// holds fewer problems' tables.
+enum : int { CLAIM_FIRST = 0, CLAIM_HOME, CLAIM_OTHERS };
+
+__device__ __forceinline__ uint64_t queue_begin(uint64_t n_chunks, uint32_t q) {
+    return (n_chunks * q) / N_QUEUES;
+}
+// Waves that start on queue q: they take its first chunks without a claim.
+__device__ __forceinline__ uint32_t queue_waves(uint32_t q) {
+    return (gridDim.x + N_QUEUES - 1 - q) / N_QUEUES * (blockDim.x >> 6);
+}
+
+// This wave's queue, its rank among the queue's waves, and its copy of the
+// totals (recomputed where needed: scalar registers are short in the loop).
+__device__ __forceinline__ uint32_t wave_queue() { return blockIdx.x % N_QUEUES; }
+__device__ __forceinline__ uint32_t wave_rank() {
+    return blockIdx.x / N_QUEUES * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+__device__ __forceinline__ uint64_t* wave_totals(const TransportArgs& T, int p) {
+    return T.descs[p].block_sums + (wave_rank() * N_QUEUES + wave_queue()) % ACC_COPIES * ACC_WORDS;
+}
+
+// The next chunk, or n_chunks when none is left (wave-uniform; all lanes
+// call).  phase: CLAIM_FIRST at the start, kept by the caller.
+__device__ inline uint64_t claim_chunk(int& phase, uint64_t n_chunks, uint64_t* queues, int lane) {
+    const auto take = [&](uint32_t q) -> uint64_t {
+        unsigned long long k = 0;
+        if (lane == 0) k = atomicAdd((unsigned long long*)queues + q * ACC_WORDS, 1ull);
+        const uint64_t at = queue_begin(n_chunks, q) + queue_waves(q) + uniform64(k);
+        return at < queue_begin(n_chunks, q + 1) ? at : n_chunks;
+    };
+    const uint32_t home = wave_queue();
+    if (phase == CLAIM_FIRST) {
+        const uint64_t size = queue_begin(n_chunks, home + 1) - queue_begin(n_chunks, home);
+        phase = size > queue_waves(home) ? CLAIM_HOME : CLAIM_OTHERS;
+        if (wave_rank() < size) return queue_begin(n_chunks, home) + wave_rank();
+    }
+    if (phase == CLAIM_HOME) {
+        const uint64_t at = take(home);
+        if (at < n_chunks) return at;
+        phase = CLAIM_OTHERS;
+    }
+    // every failed claim means its queue has since run empty: this ends
+    for (;;) {
+        const uint32_t q = (uint32_t)lane;
+        uint64_t dealt = 0;                        // chunks the queue's counter hands out
+        if (q < N_QUEUES) {
+            const uint64_t size = queue_begin(n_chunks, q + 1) - queue_begin(n_chunks, q);
+            dealt = size > queue_waves(q) ? size - queue_waves(q) : 0;
+        }
+        bool some = dealt > 0;
+        if (__ballot(some) == 0) return n_chunks;
+        if (some)
+            some = __hip_atomic_load(queues + q * ACC_WORDS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < dealt;
+        const uint64_t left = __ballot(some);
+        if (left == 0) return n_chunks;
+        const uint64_t after = left & ~((2ull << home) - 1ull);
+        const uint64_t at = take((uint32_t)__builtin_ctzll(after ? after : left));
+        if (at < n_chunks) return at;
+    }
+}
+
+// Wave-wide flush of one problem's accumulators (all 64 lanes must call) into
+// the wave's copy of its totals; k_finish adds the copies up.  Lane i adds
+// word i, so a flush is one atomic instruction on one 128-byte line.  (Every
+// wave's atomics on the same eleven output words, about 13 ns per address
+// and wave, had cost a call up to 40 us at its end.)
 // fc: wave-uniform fate counts; A: the lane's tentative collisions, real
 // collisions and Kahn attempts (advance() counts them; summed here, which
 // costs less than three ballots per iteration); e_esc: the lane's escaped
-// energy (Q40.23);
-// rays / pieces: the lane's forced-copy ray walks and the voxels they
-// visited.  The deposited energy is filled in after the kernel (k_finalize).
-// count_tallied: add the tallied histories to T.n_events (an analog run
-// without an event list, whose count needs no per-history atomic).
+// energy (Q40.23); rays / pieces: the lane's forced-copy ray walks and the
+// voxels they visited.  The deposited energy is filled in after the kernel.
 __device__ inline void flush(long long& e_esc, uint32_t* fc, Acc& A, uint32_t& rays,
-                             uint32_t& pieces, int p, const TransportArgs& T, int lane,
-                             bool count_tallied) {
+                             uint32_t& pieces, int p, const TransportArgs& T, int lane) {
     const long long ee = wsum64(e_esc);
     const long long n_rays = wsum64(rays), n_pieces = wsum64(pieces);
     const long long n_tent = wsum64(A.n_tent), n_real = wsum64(A.n_real), n_kahn = wsum64(A.n_kahn);
     uint32_t nh = 0;
 #pragma unroll
     for (int i = 0; i < 7; ++i) nh += fc[i];
-    if (lane == 0 && nh > 0) {
-        unsigned long long* fa = (unsigned long long*)(T.fates + (size_t)p * MC_N_FATES);
+    if (nh > 0) {
+        unsigned long long v = 0;
 #pragma unroll
-        for (int i = 0; i < 7; ++i) if (fc[i]) atomicAdd(fa + i, (unsigned long long)fc[i]);
-        if (T.energy) atomicAdd((unsigned long long*)(T.energy + (size_t)p * 4 + 1), (unsigned long long)ee);
-        if (count_tallied && fc[MC_TALLIED]) atomicAdd(T.n_events, (unsigned long long)fc[MC_TALLIED]);
-        if (T.counters) {
-            unsigned long long* ca = (unsigned long long*)(T.counters + (size_t)p * MC_N_COUNTERS);
-            atomicAdd(ca + 0, (unsigned long long)n_tent);
-            atomicAdd(ca + 1, (unsigned long long)n_real);
-            atomicAdd(ca + 2, (unsigned long long)n_kahn);
-            atomicAdd(ca + 3, (unsigned long long)nh);
-            if (n_rays) {
-                atomicAdd(ca + 4, (unsigned long long)n_rays);
-                atomicAdd(ca + 5, (unsigned long long)n_pieces);
-            }
-        }
-        if (fc[MC_CAPPED_FATE]) {
-            atomicOr((unsigned long long*)T.status, (unsigned long long)MC_STATUS_CAPPED);
-            atomicAdd((unsigned long long*)(T.status + 1), (unsigned long long)fc[MC_CAPPED_FATE]);
-        }
+        for (int i = 0; i < 7; ++i) if (lane == ACC_FATES + i) v = fc[i];
+        if (lane == ACC_ESC) v = (unsigned long long)ee;
+        if (lane == ACC_COUNTERS + 0) v = (unsigned long long)n_tent;
+        if (lane == ACC_COUNTERS + 1) v = (unsigned long long)n_real;
+        if (lane == ACC_COUNTERS + 2) v = (unsigned long long)n_kahn;
+        if (lane == ACC_COUNTERS + 3) v = nh;
+        if (lane == ACC_COUNTERS + 4) v = (unsigned long long)n_rays;
+        if (lane == ACC_COUNTERS + 5) v = (unsigned long long)n_pieces;
+        if (v != 0) atomicAdd((unsigned long long*)wave_totals(T, p) + lane, v);
     }
     e_esc = 0;
     rays = pieces = 0;
 #pragma unroll
     for (int i = 0; i < 7; ++i) fc[i] = 0;
     acc_zero(A);
-}
-
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
 }
 
 __device__ __forceinline__ long long readlane64(long long v, int l) {
@@ -306,7 +369,6 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
     constexpr bool VR = MODE == 3;
     const bool vr_dir = VR && (T.vr_flags & VR_FORCED_DIRECTION);
     const bool vr_fi = VR && (T.vr_flags & VR_FORCED_INTERACTION);
-    const bool count_tallied = !FD && T.n_events && !T.events;
     const int lane = threadIdx.x & 63;
     uint32_t fd_head = 0, fd_tail = 0;    // wave-uniform ring cursors (FD)
     uint32_t jq_head = 0, jq_tail = 0;    // wave-uniform job queue cursors (FD)
@@ -337,6 +399,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
     // chunk prefix lives after the work prefix: [n_problems + 1] entries
     const uint64_t* __restrict__ chunk_prefix = T.work_prefix + (T.n_problems + 1);
     const uint64_t n_chunks = chunk_prefix[T.n_problems];
+    int claim_phase = CLAIM_FIRST;
 
     MC_REGION(-1);
     for (;;) {
@@ -353,9 +416,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
                 // stage empty: emit the next batch of the chunk (claim one if needed)
                 if (c_next >= c_end) {
                     if (!have_pending) {
-                        unsigned long long base = 0;
-                        if (lane == 0) base = atomicAdd(&T.state->next_chunk, 1ull);
-                        pending = uniform64(base);
+                        pending = claim_chunk(claim_phase, n_chunks, T.queues, lane);
                         have_pending = true;
                         if (pending >= n_chunks) exhausted = true;
                     }
@@ -374,7 +435,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
                             if (np != p) {
                                 if (p >= 0) {
                                     if (PACK_FATES) fold_fates(fpk, fc);
-                                    flush(e_esc, fc, A, fd_rays, fd_pieces, p, T, lane, count_tallied);
+                                    flush(e_esc, fc, A, fd_rays, fd_pieces, p, T, lane);
                                 }
                                 p = np;
                                 C = load_cst(T.descs + p);
@@ -480,9 +541,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
                 // outgoing energy: escaped, or left at the step cap (rare: booked at once)
                 const float out = ((fate == MC_ABSORBED) | (fate == MC_CUT)) ? 0.0f : L.e;
                 if (fate == MC_CAPPED_FATE) {
-                    if (T.energy)
-                        atomicAdd((unsigned long long*)(T.energy + (size_t)p * 4 + 2),
-                                  (unsigned long long)to_q23(out));
+                    atomicAdd((unsigned long long*)wave_totals(T, p) + ACC_CAPPED, (unsigned long long)to_q23(out));
                 } else {
                     // Q40.23 as to_q23, zero-extended: the energy is never negative
                     e_esc += (long long)(uint32_t)__float2int_rn(out * 8388608.0f);
@@ -583,7 +642,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
         }
     }
     if (PACK_FATES) fold_fates(fpk, fc);
-    if (p >= 0) flush(e_esc, fc, A, fd_rays, fd_pieces, p, T, lane, count_tallied);
+    if (p >= 0) flush(e_esc, fc, A, fd_rays, fd_pieces, p, T, lane);
     if (fd_list) flush_events(T, ev_stage, ev_count, lane);
     MC_REGION(-2);
 }
@@ -666,118 +725,138 @@ __global__ __launch_bounds__(256) void k_replay(const ProbDesc* __restrict__ d,
     out[i] = r;
 }
 
-// Per-call preparation: zero outputs and counters, work and chunk prefixes.
+// Per-call preparation: zero tallies, totals and claim counters, work and
+// chunk prefixes (one wavefront, a problem per lane).
 __global__ __launch_bounds__(256) void k_prepare(const ProbDesc* __restrict__ descs, int n_problems,
-                                                 uint64_t* work_prefix, uint32_t chunk,
-                                                 CallState* state, int64_t* status,
+                                                 uint64_t* work_prefix, uint32_t chunk, int64_t* status,
                                                  unsigned long long* n_events,
-                                                 int64_t* tally, uint64_t tally_elems,
-                                                 int64_t* tally_sq, int64_t* fates, int64_t* energy,
-                                                 int64_t* counters) {
+                                                 int64_t* tally, uint64_t tally_elems, int64_t* tally_sq) {
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = tid; i < tally_elems; i += stride) {
         tally[i] = 0;
         if (tally_sq) tally_sq[i] = 0;
     }
-    for (uint64_t i = tid; i < (uint64_t)n_problems * MC_N_FATES; i += stride) fates[i] = 0;
-    for (uint64_t i = tid; i < (uint64_t)n_problems * 4; i += stride)
-        if (energy) energy[i] = 0;
-    for (uint64_t i = tid; i < (uint64_t)n_problems * MC_N_COUNTERS; i += stride)
-        if (counters) counters[i] = 0;
-    if (tid == 0) {
-        uint64_t w = 0, c = 0;
+    for (uint64_t i = tid; i < (uint64_t)n_problems * BLOCK_SCRATCH_MIN; i += stride)
+        descs[i / BLOCK_SCRATCH_MIN].block_sums[i % BLOCK_SCRATCH_MIN] = 0;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {
+        const int lane = (int)threadIdx.x;
+        uint64_t w = 0, c = 0;                 // totals of the problems before this round's
         uint64_t* chunk_prefix = work_prefix + (n_problems + 1);
-        for (int p = 0; p < n_problems; ++p) {
-            work_prefix[p] = w;
-            chunk_prefix[p] = c;
-            const uint64_t cnt = descs[p].work_count;
-            w += cnt;
-            c += (cnt + chunk - 1) / chunk;
+        for (int p0 = 0; p0 < n_problems; p0 += 64) {
+            const int p = p0 + lane;
+            const uint64_t cnt = p < n_problems ? descs[p].work_count : 0;
+            const uint64_t nc = (cnt + chunk - 1) / chunk;
+            uint64_t sw = cnt, sc = nc;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint64_t yw = (uint64_t)__shfl_up((long long)sw, o, 64);
+                const uint64_t yc = (uint64_t)__shfl_up((long long)sc, o, 64);
+                if (lane >= o) { sw += yw; sc += yc; }
+            }
+            if (p < n_problems) {
+                work_prefix[p] = w + sw - cnt;
+                chunk_prefix[p] = c + sc - nc;
+            }
+            w += (uint64_t)__shfl((long long)sw, 63, 64);
+            c += (uint64_t)__shfl((long long)sc, 63, 64);
         }
-        work_prefix[n_problems] = w;
-        chunk_prefix[n_problems] = c;
-        state->next_chunk = 0;
-        status[0] = 0; status[1] = 0; status[2] = 0; status[3] = 0;
-        if (n_events) *n_events = 0;
+        if (lane == 0) {
+            work_prefix[n_problems] = w;
+            chunk_prefix[n_problems] = c;
+            if (n_events) *n_events = 0;
+        }
+        if (lane < 4) status[lane] = 0;
     }
 }
 
-// After transport: fold staging flags and list overflow into status.
-__global__ void k_finalize(const ProbDesc* __restrict__ descs, int n_problems, int64_t* status,
-                           const unsigned long long* n_events, uint64_t capacity,
-                           const int64_t* fates, int64_t* energy) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    uint64_t f = 0;
-    int64_t n_pal = 0;
-    for (int p = 0; p < n_problems; ++p) {
-        f |= descs[p].flags;
-        n_pal += descs[p].pal_state == 0;
-        if (energy) {
-            // every history started at the line energy: what did not leave
-            // (escaped or capped) was deposited
+// After transport: the waves' totals added up into fates, energies and
+// counters, the staging flags and list overflow folded into the status, and
+// the tally range checked, FINISH_BLOCKS workgroups per problem (the first
+// one also does the rest).  A source of one sign adds weights of one sign (at
+// most 2^32 each), so a bin that crossed 2^63 reads negative: any negative bin
+// is an overflow.  A difference source adds both signs; its analog bins stay
+// in range while fewer than 2^31 histories are tallied in all (each adds
+// +-2^32), which is what is checked for it (its forced-detection and weighted
+// forms are not checked: each history then scores up to one weight per
+// collision).
+constexpr int FINISH_BLOCKS = 128;   // ~16 elements per thread on a 60-view 64x64 tally
+
+__global__ __launch_bounds__(256) void k_finish(TransportArgs T) {
+    const int p = blockIdx.x / FINISH_BLOCKS, part = blockIdx.x % FINISH_BLOCKS;
+    const ProbDesc& d = T.descs[p];
+    if (part == 0 && threadIdx.x < 64) {
+        const int lane = (int)threadIdx.x;
+        static_assert(ACC_COPIES == 64, "one copy per lane");
+        long long v[ACC_CAPPED + 1];
+#pragma unroll
+        for (int i = 0; i <= ACC_CAPPED; ++i) v[i] = (long long)d.block_sums[lane * ACC_WORDS + i];
+#pragma unroll
+        for (int i = 0; i <= ACC_CAPPED; ++i) v[i] = wsum64(v[i]);
+        if (lane == 0) {
+            int64_t* f = T.fates + (size_t)p * MC_N_FATES;
             int64_t nh = 0;
-            for (int k = 0; k < MC_N_FATES; ++k) nh += fates[(size_t)p * MC_N_FATES + k];
-            int64_t* e = energy + (size_t)p * 4;
-            e[0] = nh * (int64_t)llrint((double)descs[p].e0 * 8388608.0) - e[1] - e[2];
+#pragma unroll
+            for (int i = 0; i < 7; ++i) { f[i] = v[ACC_FATES + i]; nh += v[ACC_FATES + i]; }
+            f[7] = 0;
+            if (T.energy) {
+                // every history started at the line energy: what did not leave
+                // (escaped or capped) was deposited
+                int64_t* e = T.energy + (size_t)p * 4;
+                e[0] = nh * (int64_t)llrint((double)d.e0 * 8388608.0) - v[ACC_ESC] - v[ACC_CAPPED];
+                e[1] = v[ACC_ESC];
+                e[2] = v[ACC_CAPPED];
+                e[3] = 0;
+            }
+            if (T.counters) {
+                int64_t* c = T.counters + (size_t)p * MC_N_COUNTERS;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) c[i] = v[ACC_COUNTERS + i];
+                c[6] = c[7] = 0;
+            }
+            uint64_t bits = d.flags;
+            const long long capped = v[ACC_FATES + MC_CAPPED_FATE], tallied = v[ACC_FATES + MC_TALLIED];
+            if (capped) {
+                bits |= MC_STATUS_CAPPED;
+                atomicAdd((unsigned long long*)(T.status + 1), (unsigned long long)capped);
+            }
+            // an analog run without a list only counts its tallied histories
+            // (the count cannot overflow a list); a list counted its own entries
+            if (T.n_events && !T.events && !T.forced_detection && tallied)
+                atomicAdd(T.n_events, (unsigned long long)tallied);
+            if (T.events && p == 0 && *T.n_events > T.event_capacity) bits |= MC_STATUS_LIST_OVERFLOW;
+            if (d.act_prev && tallied >= (1ll << 31)) bits |= MC_STATUS_TALLY_OVERFLOW;
+            if (bits) atomicOr((unsigned long long*)T.status, (unsigned long long)bits);
+            if (d.pal_state == 0) atomicAdd((unsigned long long*)(T.status + 2), 1ull);
         }
     }
-    if (n_events && capacity != UINT64_MAX && *n_events > capacity) f |= MC_STATUS_LIST_OVERFLOW;
-    status[0] |= (int64_t)f;
-    status[2] = n_pal;
-}
-
-// Tally range check, TALLY_CHECK_BLOCKS workgroups per problem.  A source
-// of one sign adds weights of one sign (at most 2^32 each), so a bin that
-// crossed 2^63 reads negative: any negative bin is an overflow.  A
-// difference source adds both signs; its analog bins stay in range while
-// fewer than 2^31 histories are tallied in all (each adds +-2^32), which is
-// what is checked for it (its forced-detection and weighted forms are not
-// checked: each history then scores up to one weight per collision).
-constexpr int TALLY_CHECK_BLOCKS = 128;   // ~16 elements per thread on a 60-view 64x64 tally
-
-__global__ __launch_bounds__(256) void k_tally_check(const ProbDesc* __restrict__ descs,
-                                                     const int64_t* __restrict__ tally,
-                                                     const int64_t* __restrict__ fates,
-                                                     int64_t* status) {
-    const int p = blockIdx.x / TALLY_CHECK_BLOCKS, part = blockIdx.x % TALLY_CHECK_BLOCKS;
-    const ProbDesc& d = descs[p];
+    if (d.act_prev) return;
     bool bad = false;
-    if (d.act_prev) {
-        bad = part == 0 && threadIdx.x == 0 && fates[(size_t)p * MC_N_FATES + MC_TALLIED] >= (1ll << 31);
-    } else {
-        const uint64_t n = (uint64_t)d.n_views * 2u * (uint64_t)d.nv * (uint64_t)d.nu;
-        const int64_t* t = tally + d.tally_offset;
+    const uint64_t n = (uint64_t)d.n_views * 2u * (uint64_t)d.nv * (uint64_t)d.nu;
+    const int64_t* t = T.tally + d.tally_offset;
 #pragma unroll 4
-        for (uint64_t i = (uint64_t)part * 256 + threadIdx.x; i < n; i += TALLY_CHECK_BLOCKS * 256)
-            bad |= t[i] < 0;
-    }
+    for (uint64_t i = (uint64_t)part * 256 + threadIdx.x; i < n; i += FINISH_BLOCKS * 256)
+        bad |= t[i] < 0;
     if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0)
-        atomicOr((unsigned long long*)status, (unsigned long long)MC_STATUS_TALLY_OVERFLOW);
+        atomicOr((unsigned long long*)T.status, (unsigned long long)MC_STATUS_TALLY_OVERFLOW);
 }
 
-__global__ void k_zero_status(int64_t* status) {
-    if (blockIdx.x == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;
+// Replay: the staging flags as the status.
+__global__ void k_replay_status(const ProbDesc* __restrict__ d, int64_t* status) {
+    if (blockIdx.x == 0 && threadIdx.x < 4)
+        status[threadIdx.x] = threadIdx.x == 0 ? (int64_t)d->flags : threadIdx.x == 2 ? d->pal_state == 0 : 0;
 }
 
 }  // namespace
 
 hipError_t launch_prepare_call(const ProbDesc* descs, int32_t n_problems, uint64_t* work_prefix,
-                               CallState* state, int64_t* status, unsigned long long* n_events,
-                               int64_t* tally, uint64_t tally_elems, int64_t* tally_sq,
-                               int64_t* fates, int64_t* energy, int64_t* counters, uint32_t chunk,
+                               int64_t* status, unsigned long long* n_events,
+                               int64_t* tally, uint64_t tally_elems, int64_t* tally_sq, uint32_t chunk,
                                hipStream_t s) {
     uint64_t g = (tally_elems + 255) / 256;
     if (g < 1) g = 1;
     if (g > 4096) g = 4096;
-    k_prepare<<<(int)g, 256, 0, s>>>(descs, n_problems, work_prefix, chunk, state, status, n_events,
-                                     tally, tally_elems, tally_sq, fates, energy, counters);
-    return hipGetLastError();
-}
-
-hipError_t launch_tally_check(const ProbDesc* d_desc, int n_problems, const int64_t* tally,
-                              const int64_t* fates, int64_t* status, hipStream_t s) {
-    k_tally_check<<<n_problems * TALLY_CHECK_BLOCKS, 256, 0, s>>>(d_desc, tally, fates, status);
+    k_prepare<<<(int)g, 256, 0, s>>>(descs, n_problems, work_prefix, chunk, status, n_events,
+                                     tally, tally_elems, tally_sq);
     return hipGetLastError();
 }
 
@@ -786,21 +865,22 @@ hipError_t launch_transport(const TransportArgs& a, int grid, int block, hipStre
     else if (a.forced_detection == 2) k_transport_cfd<<<grid, block, 0, s>>>(a);
     else if (a.forced_detection) k_transport_fd<<<grid, block, 0, s>>>(a);
     else k_transport<<<grid, block, 0, s>>>(a);
-    // without a list the count is informational and cannot overflow
-    k_finalize<<<1, 64, 0, s>>>(a.descs, a.n_problems, a.status, a.n_events,
-                                a.events ? a.event_capacity : UINT64_MAX, a.fates, a.energy);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const TransportArgs& a, hipStream_t s) {
+    k_finish<<<a.n_problems * FINISH_BLOCKS, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
 hipError_t launch_replay(const ProbDesc* d_desc, const int32_t* views, const uint64_t* hists,
                          int64_t n, mc_record* out, int64_t* status, int block, int32_t vr_flags,
                          float vr_omc, hipStream_t s) {
-    k_zero_status<<<1, 64, 0, s>>>(status);
     if (n > 0) {
         const int64_t g = (n + block - 1) / block;
         k_replay<<<(int)g, block, 0, s>>>(d_desc, views, hists, n, out, vr_flags, vr_omc);
     }
-    k_finalize<<<1, 64, 0, s>>>(d_desc, 1, status, nullptr, 0, nullptr, nullptr);
+    k_replay_status<<<1, 64, 0, s>>>(d_desc, status);
     return hipGetLastError();
 }
 

@@ -269,12 +269,14 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
     ProbDesc* d_desc = (ProbDesc*)(ws + L.desc);
+    const int fd = opt ? opt->forced_detection : 0;
     uint64_t tally_elems = 0;
     std::vector<ProbDesc> hd;
     hd.reserve(n_problems);
     for (int i = 0; i < n_problems; ++i) {
         const mc_problem& p = problems[i];
         hd.push_back(host_desc(p, ws, L, i, tally_elems, brick, qbytes, cfd));
+        hd.back().mu_codes = fd != 0;
         tally_elems += (uint64_t)p.n_views * 2 * p.nv * p.nu;
     }
     {
@@ -288,7 +290,6 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
     if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e);
     if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
         return hip_fail(e);
-    const int fd = opt ? opt->forced_detection : 0;
     const int vr = opt ? opt->variance_reduction : 0;
     if (bpc <= 0) bpc = transport_blocks_per_cu(block, fd, vr);
     if (!(opt && opt->hist_per_lane > 0)) {
@@ -316,6 +317,8 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
                             status, (unsigned long long*)n_events, tally, tally_elems, tally_sq,
                             chunk, st);
     if (e != hipSuccess) return hip_fail(e);
+    if (fd && qbytes != 4 && (e = launch_mu_codes(d_desc, hd.data(), n_problems, st)) != hipSuccess)
+        return hip_fail(e);
     TransportArgs a;
     a.descs = d_desc;
     a.n_problems = n_problems;

@@ -115,7 +115,7 @@ struct Cst {
     float ln2_mu;                                 // ln 2 / max mu
     uint32_t seed, pid, max_steps, shift;
     uint64_t total, q_per_view, r_extra, work_begin, tally_offset;
-    uint32_t flags, use_pal;
+    uint32_t flags, use_pal, use_codes;
     int brick;
     uint32_t bmask, nbx, nby;
 };
@@ -196,6 +196,7 @@ __device__ inline Cst load_cst(const ProbDesc* __restrict__ d) {
     c.work_begin = d->work_begin; c.tally_offset = d->tally_offset;
     c.flags = d->flags;
     c.use_pal = d->pal_state == 0;
+    c.use_codes = d->mu_codes != 0 && c.use_pal && d->mu_pal_bad == 0;
     c.brick = d->brick_log2;
     c.bmask = (1u << c.brick) - 1u;
     c.nbx = (uint32_t)d->nbx; c.nby = (uint32_t)d->nby;
@@ -597,6 +598,56 @@ struct FdPoint {
 
 constexpr int RAY_BATCH = 8;
 
+// A ray p + t o (t >= 0, o a unit vector) through the grid: its first voxel,
+// per axis the parameter of the next plane and the plane spacing, and the
+// parameter where the walk ends: the exit of the grid, or of the attenuation
+// box if the ray starts in it (mu is zero outside it).  Plane parameters use
+// the reciprocals of the direction's components (one division per axis).
+struct RayGeom {
+    int ix, iy, iz;
+    float tx, ty, tz, ddx, ddy, ddz, t_exit;
+    bool near_edge;       // ends within rounding of an edge of the grid (two faces)
+};
+
+__device__ __forceinline__ RayGeom ray_geom(const Cst& C, float x, float y, float z, float ox, float oy,
+                                            float oz) {
+    RayGeom g;
+    const float px = x + C.hx, py = y + C.hy, pz = z + C.hz;
+    const int ix = g.ix = min(max((int)(px * C.inv_vox), 0), C.nx - 1);
+    const int iy = g.iy = min(max((int)(py * C.inv_vox), 0), C.ny - 1);
+    const int iz = g.iz = min(max((int)(pz * C.inv_vox), 0), C.nz - 1);
+    const float inf = __builtin_huge_valf();
+    // 1 / o per axis (inf for a zero component: never selected)
+    const float rx = ox != 0.0f ? 1.0f / ox : inf, ry = oy != 0.0f ? 1.0f / oy : inf;
+    const float rz = oz != 0.0f ? 1.0f / oz : inf;
+    g.tx = ox != 0.0f ? fmaxf(((float)(ix + (ox > 0.0f)) * C.vox - px) * rx, 0.0f) : inf;
+    g.ty = oy != 0.0f ? fmaxf(((float)(iy + (oy > 0.0f)) * C.vox - py) * ry, 0.0f) : inf;
+    g.tz = oz != 0.0f ? fmaxf(((float)(iz + (oz > 0.0f)) * C.vox - pz) * rz, 0.0f) : inf;
+    g.ddx = ox != 0.0f ? C.vox * fabsf(rx) : inf;
+    g.ddy = oy != 0.0f ? C.vox * fabsf(ry) : inf;
+    g.ddz = oz != 0.0f ? C.vox * fabsf(rz) : inf;
+    // exit of the grid, and of the attenuation box: per axis the far plane,
+    // (plane - p) / o; the nearest of the three
+    const float ex = ox > 0.0f ? (C.lx - px) * rx : (ox < 0.0f ? -px * rx : inf);
+    const float ey = oy > 0.0f ? (C.ly - py) * ry : (oy < 0.0f ? -py * ry : inf);
+    const float ez = oz > 0.0f ? (C.lz - pz) * rz : (oz < 0.0f ? -pz * rz : inf);
+    g.t_exit = fmaxf(fminf(ex, fminf(ey, ez)), 0.0f);
+    if (in_box(C, ix, iy, iz)) {
+        const float bx = ox > 0.0f ? ((float)((C.bbx >> 16) + 1u) * C.vox - px) * rx
+                                   : (ox < 0.0f ? ((float)(C.bbx & 0xFFFFu) * C.vox - px) * rx : inf);
+        const float by = oy > 0.0f ? ((float)((C.bby >> 16) + 1u) * C.vox - py) * ry
+                                   : (oy < 0.0f ? ((float)(C.bby & 0xFFFFu) * C.vox - py) * ry : inf);
+        const float bz = oz > 0.0f ? ((float)((C.bbz >> 16) + 1u) * C.vox - pz) * rz
+                                   : (oz < 0.0f ? ((float)(C.bbz & 0xFFFFu) * C.vox - pz) * rz : inf);
+        g.t_exit = fminf(g.t_exit, fmaxf(fminf(bx, fminf(by, bz)), 0.0f));
+    }
+    // two of the grid's exits at or before the walk's end, within what the
+    // plane parameters can be off: half an ulp per step, taken twice
+    const float lim = fmaf(g.t_exit, (float)(max(C.nx, max(C.ny, C.nz)) + 32) * 0x1p-23f, g.t_exit);
+    g.near_edge = ((ex <= lim) & (ey <= lim)) | ((ex <= lim) & (ez <= lim)) | ((ey <= lim) & (ez <= lim));
+    return g;
+}
+
 // State of a voxel walk: the current voxel (linear index), the planes
 // crossed, the ray parameter reached, the next plane per axis, and whether
 // it has ended.
@@ -653,54 +704,26 @@ __device__ __forceinline__ void ray_add(float& sum, const float (&mu)[RAY_BATCH]
     for (int k = 0; k < RAY_BATCH; ++k) sum = fmaf(mu[k], lb[k], sum);
 }
 
-// Integral of mu140 along p + t o (t >= 0, o a unit vector) to the grid edge:
-// voxel walk (Amanatides & Woo 1987) with the advancing axis chosen by
-// selects, so the lanes of a wavefront stay together.  The walk runs
-// RAY_BATCH crossings of pure arithmetic and issues their RAY_BATCH mu
-// gathers together; two batches alternate buffers, so a batch's gathered
-// values are summed after the next batch has been walked and its gathers
-// issued, and a gather's latency overlaps a whole batch of work (the sum is
-// still taken piece by piece in walk order).  Plane parameters use the
-// reciprocals of the direction's components (one division per axis); the
-// gathers take a 32-bit offset from the map's base in scalar registers.
-__device__ inline float ray_mu(const Cst& C, float x, float y, float z, float ox, float oy, float oz,
-                               uint32_t& pieces) {
-    const float px = x + C.hx, py = y + C.hy, pz = z + C.hz;
+// Integral of mu140 along a ray to the end of its walk: voxel walk (Amanatides
+// & Woo 1987) with the advancing axis chosen by selects, so the lanes of a
+// wavefront stay together.  The walk runs RAY_BATCH crossings of pure
+// arithmetic and issues their RAY_BATCH mu gathers together; two batches
+// alternate buffers, so a batch's gathered values are summed after the next
+// batch has been walked and its gathers issued, and a gather's latency
+// overlaps a whole batch of work (the sum is still taken piece by piece in
+// walk order).  The gathers take a 32-bit offset from the map's base in
+// scalar registers.
+__device__ inline float ray_mu(const Cst& C, const RayGeom& g, float ox, float oy, float oz, uint32_t& pieces) {
     RayWalk w;
-    const int ix = min(max((int)(px * C.inv_vox), 0), C.nx - 1);
-    const int iy = min(max((int)(py * C.inv_vox), 0), C.ny - 1);
-    const int iz = min(max((int)(pz * C.inv_vox), 0), C.nz - 1);
-    const float inf = __builtin_huge_valf();
-    // 1 / o per axis (inf for a zero component: never selected)
-    const float rx = ox != 0.0f ? 1.0f / ox : inf, ry = oy != 0.0f ? 1.0f / oy : inf;
-    const float rz = oz != 0.0f ? 1.0f / oz : inf;
     RaySteps s;
-    w.tx = ox != 0.0f ? fmaxf(((float)(ix + (ox > 0.0f)) * C.vox - px) * rx, 0.0f) : inf;
-    w.ty = oy != 0.0f ? fmaxf(((float)(iy + (oy > 0.0f)) * C.vox - py) * ry, 0.0f) : inf;
-    w.tz = oz != 0.0f ? fmaxf(((float)(iz + (oz > 0.0f)) * C.vox - pz) * rz, 0.0f) : inf;
-    s.ddx = ox != 0.0f ? C.vox * fabsf(rx) : inf;
-    s.ddy = oy != 0.0f ? C.vox * fabsf(ry) : inf;
-    s.ddz = oz != 0.0f ? C.vox * fabsf(rz) : inf;
-    // exit of the grid, and of the attenuation box (mu is zero outside it):
-    // per axis the far plane, (plane - p) / o; the nearest of the three
-    const float ex = ox > 0.0f ? (C.lx - px) * rx : (ox < 0.0f ? -px * rx : inf);
-    const float ey = oy > 0.0f ? (C.ly - py) * ry : (oy < 0.0f ? -py * ry : inf);
-    const float ez = oz > 0.0f ? (C.lz - pz) * rz : (oz < 0.0f ? -pz * rz : inf);
-    s.t_exit = fmaxf(fminf(ex, fminf(ey, ez)), 0.0f);
-    if (in_box(C, ix, iy, iz)) {
-        const float bx = ox > 0.0f ? ((float)((C.bbx >> 16) + 1u) * C.vox - px) * rx
-                                   : (ox < 0.0f ? ((float)(C.bbx & 0xFFFFu) * C.vox - px) * rx : inf);
-        const float by = oy > 0.0f ? ((float)((C.bby >> 16) + 1u) * C.vox - py) * ry
-                                   : (oy < 0.0f ? ((float)(C.bby & 0xFFFFu) * C.vox - py) * ry : inf);
-        const float bz = oz > 0.0f ? ((float)((C.bbz >> 16) + 1u) * C.vox - pz) * rz
-                                   : (oz < 0.0f ? ((float)(C.bbz & 0xFFFFu) * C.vox - pz) * rz : inf);
-        s.t_exit = fminf(s.t_exit, fmaxf(fminf(bx, fminf(by, bz)), 0.0f));
-    }
+    w.tx = g.tx; w.ty = g.ty; w.tz = g.tz;
+    s.ddx = g.ddx; s.ddy = g.ddy; s.ddz = g.ddz;
+    s.t_exit = g.t_exit;
     s.stx = ox > 0.0f ? 1 : -1;
     s.sty = oy > 0.0f ? C.nx : -C.nx;
     s.stz = oz > 0.0f ? C.nx * C.ny : -(C.nx * C.ny);
     s.vmax = (uint32_t)(C.nx * C.ny * C.nz - 1);
-    w.v = ix + C.nx * (iy + C.ny * iz);
+    w.v = g.ix + C.nx * (g.iy + C.ny * g.iz);
     w.n = 0;
     w.t = 0.0f;
     w.done = false;
@@ -728,6 +751,143 @@ __device__ inline float ray_mu(const Cst& C, float x, float y, float z, float ox
     return sum;
 }
 
+// The same walk over the map's one-byte codes in bricks (mu_code_address),
+// with the map values of the codes in LDS.  The FP32 map's walk is bound by
+// its gathers: nearly every lane of every gather is on a cache line of its
+// own, a line each 2 crossings (and on a 256^3 map, 64 MB, a miss of the L2);
+// a 128-byte brick of 16 x 8 codes serves about 10 crossings of a ray, and
+// the codes of a 128^3 map fit one XCD's L2.  Transport of 1e7 histories on
+// the 128^3 thorax: 2.78 -> 2.10 ms, on the 256^3 thorax (120
+// views) 11.3 -> 3.49 ms.
+//
+// A voxel's address is the bitwise or of one part per axis, and a part steps
+// by an add and a mask (dilated integers: the carry runs through the bits the
+// mask clears).  x and y are padded to powers of two for that, z is not.
+// Every piece but the last lies in the grid (a ray that ends at an edge of
+// the grid, where rounding can order the last planes of two axes either way,
+// goes to ray_mu: near_edge).  The last piece can lie one step past the grid
+// (ray_batch); it is taken after the walk, from the FP32 map at the same
+// clamped index as there, so both walks return the same bits.
+constexpr uint32_t MU_BRICK_X = 4, MU_BRICK_Y = 3;      // log2 of the brick, x and y
+
+struct CodeWalk {
+    uint32_t ax, ay, az;
+    float t, tx, ty, tz;
+    bool done;
+};
+struct CodeSteps {
+    uint32_t cx, cy, cz, mx, my, last;
+    float ddx, ddy, ddz, t_exit;
+};
+
+// RAY_BATCH pieces: as ray_batch, but a piece that reaches the exit has
+// length 0 here (it is added after the walk).  A finished walk no longer
+// moves, so its next plane keeps lying at or beyond the exit.  FLAT: the ray
+// has no z component (two axes: 1.02 against 1.21 ms of transport, 5e6
+// histories of the 128^3 thorax).
+template <bool FLAT>
+__device__ __forceinline__ void code_batch(const CodeSteps& s, CodeWalk& w, const uint8_t* __restrict__ codes,
+                                           uint32_t (&c)[RAY_BATCH], float (&lb)[RAY_BATCH]) {
+    uint32_t at[RAY_BATCH];
+#pragma unroll
+    for (int k = 0; k < RAY_BATCH; ++k) {
+        const float tn = FLAT ? fminf(w.tx, w.ty) : fminf(w.tx, fminf(w.ty, w.tz));
+        // x and y stay in the table by their masks; z can be one plane outside
+        at[k] = FLAT ? w.ax | w.ay | w.az : min(w.ax | w.ay | w.az, s.last);
+        const bool go = !(tn >= s.t_exit);
+        const bool x_first = FLAT ? w.tx <= w.ty : (w.tx <= w.ty) & (w.tx <= w.tz);
+        const bool y_first = FLAT || w.ty <= w.tz;
+        const bool bx = go & x_first, by = go & !x_first & y_first, bz = go & !x_first & !y_first;
+        const float t = go ? tn : w.t;
+        lb[k] = t - w.t;
+        w.t = t;
+        w.tx += bx ? s.ddx : 0.0f;
+        w.ty += by ? s.ddy : 0.0f;
+        w.ax = (w.ax + (bx ? s.cx : 0u)) & s.mx;
+        w.ay = (w.ay + (by ? s.cy : 0u)) & s.my;
+        if (!FLAT) {
+            w.tz += bz ? s.ddz : 0.0f;
+            w.az += bz ? s.cz : 0u;
+        }
+        w.done = !go;
+    }
+#pragma unroll
+    for (int k = 0; k < RAY_BATCH; ++k)
+        c[k] = ldg(codes + at[k]);
+}
+
+__device__ __forceinline__ void code_add(float& sum, const float* mu_of, const uint32_t (&c)[RAY_BATCH],
+                                         const float (&lb)[RAY_BATCH]) {
+#pragma unroll
+    for (int k = 0; k < RAY_BATCH; ++k) sum = fmaf(mu_of[c[k]], lb[k], sum);
+}
+
+// Coordinate of a walk on one axis, from its part's value i (modulo the
+// padded size m) and its start i0: it moved one way, if at all, by 1 to m.
+__device__ __forceinline__ int unwrap(int i, int i0, int m, bool up, bool moved) {
+    if (!moved) return i;
+    return up ? (i <= i0 ? i + m : i) : (i >= i0 ? i - m : i);
+}
+
+template <bool FLAT>
+__device__ inline float ray_mu_codes(const Cst& C, const float* mu_of, const RayGeom& g, float ox, float oy,
+                                     float oz, uint32_t& pieces) {
+    const uint32_t lx = mu_code_log2(C.nx, MU_BRICK_X), ly = mu_code_log2(C.ny, MU_BRICK_Y);
+    const uint32_t bx = (1u << MU_BRICK_X) - 1u, by = (1u << MU_BRICK_Y) - 1u;
+    CodeWalk w;
+    CodeSteps s;
+    w.tx = g.tx; w.ty = g.ty; w.tz = g.tz;
+    s.ddx = g.ddx; s.ddy = g.ddy; s.ddz = g.ddz;
+    s.t_exit = g.t_exit;
+    s.mx = mu_code_x((1u << lx) - 1u);
+    s.my = mu_code_y((1u << ly) - 1u, lx);
+    s.cx = ox > 0.0f ? 0u - s.mx : ~0u;
+    s.cy = oy > 0.0f ? 0u - s.my : 0u - (1u << MU_BRICK_X);
+    s.cz = oz > 0.0f ? 1u << (lx + ly) : 0u - (1u << (lx + ly));
+    w.ax = mu_code_x((uint32_t)g.ix);
+    w.ay = mu_code_y((uint32_t)g.iy, lx);
+    w.az = (uint32_t)g.iz << (lx + ly);
+    w.t = 0.0f;
+    float sum = 0.0f;
+    const int max_batches = (C.nx + C.ny + C.nz + 3) / RAY_BATCH + 1;
+    const uint8_t* __restrict__ codes = (const uint8_t*)uniform_ptr(C.q32);
+    s.last = ((uint32_t)C.nz << (lx + ly)) - 1u;
+    uint32_t c_a[RAY_BATCH], c_b[RAY_BATCH];
+    float lb_a[RAY_BATCH], lb_b[RAY_BATCH];
+    code_batch<FLAT>(s, w, codes, c_a, lb_a);
+    int it = 1;
+    for (; it + 1 < max_batches && !w.done; it += 2) {
+        code_batch<FLAT>(s, w, codes, c_b, lb_b);
+        code_add(sum, mu_of, c_a, lb_a);
+        code_batch<FLAT>(s, w, codes, c_a, lb_a);
+        code_add(sum, mu_of, c_b, lb_b);
+    }
+    if (it < max_batches && !w.done) {     // one batch left (max_batches even)
+        code_batch<FLAT>(s, w, codes, c_b, lb_b);
+        code_add(sum, mu_of, c_a, lb_a);
+        code_add(sum, mu_of, c_b, lb_b);
+    } else {
+        code_add(sum, mu_of, c_a, lb_a);
+    }
+    // the last voxel, and from it the planes crossed
+    const int ux = (int)((w.ax & bx) | (w.ax >> (MU_BRICK_X + MU_BRICK_Y) << MU_BRICK_X));
+    const int uy = (int)(((w.ay >> MU_BRICK_X) & by) | (w.ay >> (lx + MU_BRICK_Y) << MU_BRICK_Y));
+    const int ix = unwrap(ux, g.ix, 1 << lx, ox > 0.0f, w.tx != g.tx);
+    const int iy = unwrap(uy, g.iy, 1 << ly, oy > 0.0f, w.ty != g.ty);
+    const int iz = (int)w.az >> (lx + ly);
+    pieces = (uint32_t)(abs(ix - g.ix) + abs(iy - g.iy) + abs(iz - g.iz)) + 1u;
+    if (w.done) {
+        // the last piece, from t to the exit
+        float m;
+        if (((uint32_t)ix < (uint32_t)C.nx) & ((uint32_t)iy < (uint32_t)C.ny) & ((uint32_t)iz < (uint32_t)C.nz))
+            m = mu_of[ldg(codes + (w.ax | w.ay | w.az))];
+        else
+            m = ldg(C.mu + min((uint32_t)(ix + C.nx * (iy + C.ny * iz)), (uint32_t)(C.nx * C.ny * C.nz - 1)));
+        sum = fmaf(m, s.t_exit - w.t, sum);
+    }
+    return sum;
+}
+
 // A forced copy that scores, up to its ray walk: start point, direction,
 // weight before transmission, the attenuation scale g(E') of the walk's
 // integral, its target (tally bin, or index in the CFD depth layers), and
@@ -739,8 +899,16 @@ struct FdJob {
     uint32_t view, hist, voxel;
 };
 
-__device__ inline float fd_walk_score(const Cst& C, const FdJob& j, uint32_t& pieces) {
-    return j.w * __expf(-j.g * ray_mu(C, j.x, j.y, j.z, j.ox, j.oy, j.oz, pieces));
+// mu_of: the map values of the codes (LDS), read when C.use_codes.  FLAT: the
+// copy travels in a plane of constant z.
+template <bool FLAT>
+__device__ inline float fd_walk_score(const Cst& C, const FdJob& j, const float* mu_of, uint32_t& pieces) {
+    const RayGeom g = ray_geom(C, j.x, j.y, j.z, j.ox, j.oy, j.oz);
+    const bool by_code = C.use_codes && !g.near_edge;
+    float depth = 0.0f;
+    if (by_code) depth = ray_mu_codes<FLAT>(C, mu_of, g, j.ox, j.oy, j.oz, pieces);
+    if (!by_code) depth = ray_mu(C, g, j.ox, j.oy, j.oz, pieces);
+    return j.w * __expf(-j.g * depth);
 }
 
 // Set-up of one forced copy: false if it scores nothing (energy out of the

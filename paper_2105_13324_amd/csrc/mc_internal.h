@@ -105,7 +105,7 @@ struct ProbDesc {
     uint32_t pal_state;             // 0: palette in use; 1: 32-bit thresholds (host request
                                     // or more than PALETTE_N distinct values, set by staging)
     float omc_alpha;                // 1 - cos(alpha), from double precision (forced detection)
-    uint32_t pad2;
+    uint32_t mu_pal_bad;            // two map values share a threshold: no table by code
     int32_t bb_lo[3], bb_hi[3];     // attenuation box: voxel index range of mu > 0 (staging)
     // convolution-based forced detection (layers null otherwise)
     int64_t* layers;                // [V][cfd_L][2][nv][nu] deposits, Q31.32
@@ -115,8 +115,24 @@ struct ProbDesc {
     double alpha, cfd_pix, cfd_tan; // collimator half-angle (rad), pixel (cm), tan(alpha)
     const uint32_t* act_prev;       // nullable: the source is act - act_prev (signed)
     float e0;                       // emission line energy (keV)
-    uint32_t pad4;
+    uint32_t mu_codes;              // the call makes the brick table of codes (forced detection)
 };
+
+// Brick table of palette codes for the forced copies' ray walks: 16 x 8 x 1
+// voxels (x, y, z) of one byte each are 128 consecutive bytes, x and y padded
+// to powers of two.  It takes the place of the 32-bit thresholds, which
+// nothing reads once the one-byte codes are made (1 byte per voxel against 4,
+// so it fits whatever the padding).  Address: low x bits, low y bits, high x
+// bits, high y bits, z.
+__host__ __device__ inline uint32_t mu_code_log2(int n, uint32_t at_least) {
+    uint32_t l = at_least;
+    while ((1u << l) < (uint32_t)n) ++l;
+    return l;
+}
+__device__ __forceinline__ uint32_t mu_code_x(uint32_t ix) { return (ix & 15u) | (ix >> 4 << 7); }
+__device__ __forceinline__ uint32_t mu_code_y(uint32_t iy, uint32_t lx) {
+    return (iy & 7u) << 4 | iy >> 3 << (lx + 3);
+}
 
 // Emission weight of voxel i: the activity, or for a difference source the
 // magnitude of act - act_prev.
@@ -189,8 +205,10 @@ constexpr int ACC_COPIES = 64;
 constexpr int ACC_WORDS = 16;       // uint64 per copy (one 128-byte line)
 enum { ACC_FATES = 0, ACC_ESC = 7, ACC_COUNTERS = 8, ACC_CAPPED = 14 };
 constexpr int N_QUEUES = 32;        // at most 64: a wavefront looks at all at once
+constexpr int MU_PAL_AT = (ACC_COPIES + N_QUEUES) * ACC_WORDS;   // then (forced detection) the map
+                                    // value of each palette code, float bits + 1 (0: none)
 constexpr int BLOCK_SCRATCH_MIN = 2048;
-static_assert((ACC_COPIES + N_QUEUES) * ACC_WORDS <= BLOCK_SCRATCH_MIN, "transport scratch");
+static_assert(MU_PAL_AT + 256 / 2 <= BLOCK_SCRATCH_MIN, "transport scratch");
 
 // Host launchers (cgsm.hip): block-summed source; coarse projection expanded
 // to the normal pixels.
@@ -222,6 +240,9 @@ __host__ __device__ inline uint64_t guide_capacity(uint64_t nvox) {
     while (c < nvox) c <<= 1;
     return c;
 }
+// forced detection: the brick table of codes and the codes' map values (after
+// the staging and the call's preparation)
+hipError_t launch_mu_codes(ProbDesc* d_descs, const ProbDesc* h_descs, int n, hipStream_t s);
 hipError_t launch_staging_batch(ProbDesc* d_descs, const ProbDesc* h_descs, int n, hipStream_t s);
 
 // Host launchers (transport.hip)

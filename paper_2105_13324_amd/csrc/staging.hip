@@ -379,6 +379,66 @@ __global__ __launch_bounds__(RED_THREADS) void k_codes(ProbDesc* descs) {
     }
 }
 
+// Forced detection: the brick table of codes (in the place of the 32-bit
+// thresholds) and the map value of each code.  Two map values that share a
+// threshold (their difference is below 2^-24 of the maximum) cannot share a
+// table entry: mu_pal_bad is set and the walks read the map itself.  A
+// workgroup collects the values of its voxels in LDS and merges them into the
+// problem's table once.  Threads run along x: reads and writes are whole
+// brick rows.
+__global__ __launch_bounds__(RED_THREADS) void k_mu_codes(ProbDesc* descs) {
+    ProbDesc* pd = descs + blockIdx.y;
+    if (pd->pal_state != 0) return;
+    __shared__ uint32_t val[PALETTE_N];      // float bits + 1
+    __shared__ uint32_t clash;
+    for (int k = threadIdx.x; k < PALETTE_N; k += blockDim.x) val[k] = 0;
+    if (threadIdx.x == 0) clash = 0;
+    __syncthreads();
+    const float* __restrict__ mu = pd->mu;
+    const uint8_t* __restrict__ q8 = pd->q8;
+    uint8_t* __restrict__ out = (uint8_t*)pd->q32;
+    const uint32_t nx = (uint32_t)pd->nx, ny = (uint32_t)pd->ny;
+    const uint32_t nrows = ny * (uint32_t)pd->nz;
+    const int b = pd->brick_log2;
+    const uint32_t m = (1u << b) - 1u;
+    const uint32_t nbx = (uint32_t)pd->nbx, nby = (uint32_t)pd->nby;
+    const uint32_t lx = mu_code_log2(pd->nx, 4), ly = mu_code_log2(pd->ny, 3);
+    uint32_t last_c = PALETTE_N, last_v = 0;    // the pair this lane put in the table last
+    for (uint32_t r0 = blockIdx.x; r0 < nrows; r0 += ROWS * gridDim.x)
+    for (uint32_t ix = threadIdx.x; ix < nx; ix += blockDim.x) {
+        uint32_t c[ROWS], v[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const uint32_t r = r0 + (uint32_t)u * gridDim.x;
+            const bool ok = r < nrows;
+            c[u] = ok ? q8[brick_index(ix, r % ny, r / ny, nx, ny, b, m, nbx, nby)] : 0u;
+            v[u] = ok ? __float_as_uint(mu[(uint64_t)r * nx + ix]) + 1u : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const uint32_t r = r0 + (uint32_t)u * gridDim.x;
+            if (r >= nrows) break;
+            out[mu_code_x(ix) | mu_code_y(r % ny, lx) | (r / ny) << (lx + ly)] = (uint8_t)c[u];
+            if (c[u] == last_c && v[u] == last_v) continue;
+            last_c = c[u];
+            last_v = v[u];
+            uint32_t cur = __hip_atomic_load(val + c[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (cur == 0) cur = atomicCAS(val + c[u], 0u, v[u]);
+            if (cur != 0 && cur != v[u]) clash = 1;
+        }
+    }
+    __syncthreads();
+    uint32_t* __restrict__ table = (uint32_t*)(pd->block_sums + MU_PAL_AT);
+    for (int k = threadIdx.x; k < PALETTE_N; k += blockDim.x) {
+        if (val[k] == 0) continue;
+        uint32_t cur = __hip_atomic_load(table + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur == 0) cur = atomicCAS(table + k, 0u, val[k]);
+        if (cur != 0 && cur != val[k]) clash = 1;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && clash) atomicOr(&pd->mu_pal_bad, 1u);
+}
+
 // --- three-pass scan of the activity map: uint64 sums of the source weight
 // and the runs of equal weight, so the emission tables hold one entry per run
 // (a segmented phantom has ~1e4 runs against ~1e6 active voxels) ---
@@ -648,6 +708,19 @@ hipError_t launch_staging_batch(ProbDesc* d, const ProbDesc* h, int n, hipStream
     k_scan_final<<<dim3((unsigned)max_nb, ny), SCAN_THREADS, 0, st>>>(d);
     k_guide<<<dim3((unsigned)grid_for(max_cap, RED_THREADS, 8192), ny), RED_THREADS, 0, st>>>(d);
     k_kn_table<<<dim3((KN_TABLE_N + 255) / 256, ny), 256, 0, st>>>(d);
+    return hipGetLastError();
+}
+
+hipError_t launch_mu_codes(ProbDesc* d, const ProbDesc* h, int n, hipStream_t st) {
+    uint64_t max_rows = 1;
+    int max_nx = 1;
+    for (int i = 0; i < n; ++i) {
+        max_rows = std::max<uint64_t>(max_rows, (uint64_t)h[i].ny * h[i].nz);
+        max_nx = std::max(max_nx, h[i].nx);
+    }
+    const int row_threads = (int)std::min<uint64_t>(RED_THREADS, ((uint64_t)max_nx + 63) / 64 * 64);
+    const unsigned blocks = (unsigned)std::min<uint64_t>((max_rows + ROWS - 1) / ROWS, 1024);
+    k_mu_codes<<<dim3(blocks, (unsigned)n), row_threads, 0, st>>>(d);
     return hipGetLastError();
 }
 

@@ -231,7 +231,7 @@ constexpr uint32_t FD_JOBS = 128;         // scoring jobs waiting for their walk
 // Events of listed forced copies staged per wave before one atomic appends
 // them: the list's counter is one address for the whole device, so one
 // atomic per few hundred events instead of one per scored batch.
-constexpr uint32_t EV_STAGE = 160;
+constexpr uint32_t EV_STAGE = 136;
 
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -272,12 +272,12 @@ __device__ __forceinline__ bool fd_setup_mode(const Cst& C, const ProbDesc* __re
 // detection deposits into the depth layer instead (no events, no sum of
 // squares).  All 64 lanes call.
 template <int MODE>
-__device__ inline void fd_score(const Cst& C, int p, const FdJob& j, bool valid, int lane,
+__device__ inline void fd_score(const Cst& C, int p, const FdJob& j, bool valid, const float* mu_of, int lane,
                                 const TransportArgs& T, uint32_t& rays, uint32_t& pieces,
                                 mc_event* stage, uint32_t& ev_count) {
     uint32_t pc = 0;
     float sc = 0.0f;
-    if (valid) sc = fd_walk_score(C, j, pc);
+    if (valid) sc = fd_walk_score<MODE == 2>(C, j, mu_of, pc);
     rays += pc != 0;
     pieces += pc;
     if constexpr (MODE == 2) {
@@ -337,13 +337,13 @@ __device__ inline void fd_drain(const Cst& C, int p, const FdPoint* ring, uint32
 // (all 64 lanes call).
 template <int MODE>
 __device__ inline void fd_walk_jobs(const Cst& C, int p, const FdJob* jq, uint32_t& jq_head, uint32_t n,
-                                    int lane, const TransportArgs& T, uint32_t& rays, uint32_t& pieces,
-                                    mc_event* stage, uint32_t& ev_count) {
+                                    const float* mu_of, int lane, const TransportArgs& T, uint32_t& rays,
+                                    uint32_t& pieces, mc_event* stage, uint32_t& ev_count) {
     wave_sync_lds();
     const bool valid = (uint32_t)lane < n;
     FdJob j = {};
     if (valid) j = jq[(jq_head + (uint32_t)lane) & (FD_JOBS - 1)];
-    fd_score<MODE>(C, p, j, valid, lane, T, rays, pieces, stage, ev_count);
+    fd_score<MODE>(C, p, j, valid, mu_of, lane, T, rays, pieces, stage, ev_count);
     jq_head += n;
 }
 
@@ -356,7 +356,7 @@ __device__ inline void fd_walk_jobs(const Cst& C, int p, const FdJob* jq, uint32
 // (forced direction and / or forced interaction; arrivals add their weight).
 template <int MODE>
 __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restrict__ my,
-                                               uint32_t* __restrict__ my_pal,
+                                               uint32_t* __restrict__ my_pal, float* __restrict__ my_mu,
                                                FdPoint* __restrict__ ring,
                                                FdJob* __restrict__ jq,
                                                mc_event* __restrict__ ev_stage) {
@@ -444,6 +444,16 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
 #pragma unroll
                                     for (int k = 0; k < PALETTE_N / 64; ++k)
                                         my_pal[k * 64 + lane] = ldg(C.pal + k * 64 + lane);
+                                    if constexpr (FD) {
+                                        const uint32_t* t = (const uint32_t*)(T.descs[p].block_sums + MU_PAL_AT);
+#pragma unroll
+                                        for (int k = 0; k < PALETTE_N / 64; ++k) {
+                                            // finite for every code: a finished walk, or the
+                                            // padding's codes, add it times 0
+                                            const uint32_t v = ldg(t + k * 64 + lane);
+                                            my_mu[k * 64 + lane] = v ? __uint_as_float(v - 1u) : 0.0f;
+                                        }
+                                    }
                                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                                     __builtin_amdgcn_wave_barrier();
                                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -491,7 +501,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
                         if constexpr (FD) {
                             FdJob j;
                             const bool ok = idx < n_rec && fd_setup_mode<MODE>(C, T.descs + p, q, j);
-                            fd_score<MODE>(C, p, j, ok, lane, T, fd_rays, fd_pieces, ev_stage, ev_count);
+                            fd_score<MODE>(C, p, j, ok, my_mu, lane, T, fd_rays, fd_pieces, ev_stage, ev_count);
                         }
                     }
                     // the records are read by other lanes of this wavefront
@@ -579,7 +589,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
             const uint32_t nj = jq_tail - jq_head;
             if (nj >= 64 || (nj != 0 && none_busy && fd_tail == fd_head)) {
                 if (fd_list && ev_count > EV_STAGE - 64) flush_events(T, ev_stage, ev_count, lane);
-                fd_walk_jobs<MODE>(C, p, jq, jq_head, nj < 64 ? nj : 64u, lane, T, fd_rays, fd_pieces,
+                fd_walk_jobs<MODE>(C, p, jq, jq_head, nj < 64 ? nj : 64u, my_mu, lane, T, fd_rays, fd_pieces,
                                    ev_stage, ev_count);
             }
         }
@@ -650,7 +660,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_transport(TransportArgs T) {
     __shared__ EmitRec stage[WAVES_PER_BLOCK_MAX][EMIT_BATCH];
     __shared__ uint32_t pal_copy[WAVES_PER_BLOCK_MAX][PALETTE_N];
-    transport_body<0>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], nullptr, nullptr, nullptr);
+    transport_body<0>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], nullptr, nullptr, nullptr, nullptr);
 }
 
 __global__ __launch_bounds__(256) void k_transport_fd(TransportArgs T) {
@@ -659,14 +669,15 @@ __global__ __launch_bounds__(256) void k_transport_fd(TransportArgs T) {
     __shared__ FdPoint ring[WAVES_PER_BLOCK_MAX][FD_RING];
     __shared__ FdJob jobs[WAVES_PER_BLOCK_MAX][FD_JOBS];
     __shared__ mc_event ev_stage[WAVES_PER_BLOCK_MAX][EV_STAGE];
-    transport_body<1>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6],
+    __shared__ float mu_copy[WAVES_PER_BLOCK_MAX][PALETTE_N];
+    transport_body<1>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], mu_copy[threadIdx.x >> 6],
                       ring[threadIdx.x >> 6], jobs[threadIdx.x >> 6], ev_stage[threadIdx.x >> 6]);
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_transport_vr(TransportArgs T) {
     __shared__ EmitRec stage[WAVES_PER_BLOCK_MAX][EMIT_BATCH];
     __shared__ uint32_t pal_copy[WAVES_PER_BLOCK_MAX][PALETTE_N];
-    transport_body<3>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], nullptr, nullptr, nullptr);
+    transport_body<3>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], nullptr, nullptr, nullptr, nullptr);
 }
 
 __global__ __launch_bounds__(256) void k_transport_cfd(TransportArgs T) {
@@ -674,7 +685,8 @@ __global__ __launch_bounds__(256) void k_transport_cfd(TransportArgs T) {
     __shared__ uint32_t pal_copy[WAVES_PER_BLOCK_MAX][PALETTE_N];
     __shared__ FdPoint ring[WAVES_PER_BLOCK_MAX][FD_RING];
     __shared__ FdJob jobs[WAVES_PER_BLOCK_MAX][FD_JOBS];
-    transport_body<2>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6],
+    __shared__ float mu_copy[WAVES_PER_BLOCK_MAX][PALETTE_N];
+    transport_body<2>(T, stage[threadIdx.x >> 6], pal_copy[threadIdx.x >> 6], mu_copy[threadIdx.x >> 6],
                       ring[threadIdx.x >> 6], jobs[threadIdx.x >> 6], nullptr);
 }
 

@@ -221,18 +221,52 @@ __device__ inline void seen_insert(uint32_t* set, uint32_t* n, uint32_t q, uint3
     }
 }
 
-// Slot of q in the palette, inserting it if absent; PALETTE_N when it is full
-// or has overflowed elsewhere (looked at with each probe, a round trip to
-// memory: the two loads overlap).
-__device__ inline uint32_t palette_insert(uint32_t* pal, uint32_t q, const uint32_t* overflow) {
-    uint32_t h = palette_hash(q);
-    for (int probe = 0; probe < PALETTE_N; ++probe, h = (h + 1) & (PALETTE_N - 1)) {
-        if (__hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return PALETTE_N;
-        uint32_t cur = __hip_atomic_load(pal + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == PALETTE_EMPTY) cur = atomicCAS(pal + h, PALETTE_EMPTY, q);
-        if (cur == PALETTE_EMPTY || cur == q) return h;
+// Put a workgroup's n (<= PALETTE_N) distinct values into the palette (all
+// threads call).  Rounds of one look at the whole table (one round trip to
+// memory), then one attempt per missing value at the first free slot of its
+// probe order in that look.  When the values there and the missing ones are
+// more than the table holds, the map has no palette, and a workgroup sees
+// that in the round after the table has filled up: probing a full table slot
+// by slot, a round trip each, had taken 400 us on maps whose workgroups hold
+// just under 256 values each.
+__device__ inline void palette_merge(uint32_t* pal, uint32_t* overflow, const uint32_t* vals, uint32_t n) {
+    __shared__ uint32_t snap[PALETTE_N];
+    __shared__ uint32_t n_there, n_missing;
+    constexpr uint32_t PRESENT = PALETTE_N + 1;
+    // where v would go: PRESENT when it is there, PALETTE_N when no slot is free
+    const auto free_slot = [&](uint32_t v) -> uint32_t {
+        uint32_t h = palette_hash(v);
+        for (int probe = 0; probe < PALETTE_N; ++probe, h = (h + 1) & (PALETTE_N - 1)) {
+            if (snap[h] == v) return PRESENT;
+            if (snap[h] == PALETTE_EMPTY) return h;
+        }
+        return PALETTE_N;
+    };
+    for (;;) {
+        __syncthreads();                     // the last round's reads are done
+        if (threadIdx.x == 0) {
+            n_missing = 0;
+            // overflowed elsewhere already: nothing reads the palette
+            n_there = __hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 2u * PALETTE_N : 0u;
+        }
+        for (uint32_t k = threadIdx.x; k < (uint32_t)PALETTE_N; k += blockDim.x)
+            snap[k] = __hip_atomic_load(pal + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        for (uint32_t k = threadIdx.x; k < (uint32_t)PALETTE_N; k += blockDim.x)
+            if (snap[k] != PALETTE_EMPTY) atomicAdd(&n_there, 1u);
+        for (uint32_t k = threadIdx.x; k < n; k += blockDim.x)
+            if (free_slot(vals[k]) != PRESENT) atomicAdd(&n_missing, 1u);
+        __syncthreads();
+        if (n_missing == 0 || n_there > (uint32_t)PALETTE_N) return;
+        if (n_there + n_missing > (uint32_t)PALETTE_N) {
+            if (threadIdx.x == 0) atomicOr(overflow, 1u);
+            return;
+        }
+        for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) {
+            const uint32_t slot = free_slot(vals[k]);
+            if (slot != PRESENT && slot != (uint32_t)PALETTE_N) atomicCAS(pal + slot, PALETTE_EMPTY, vals[k]);
+        }
     }
-    return PALETTE_N;
 }
 
 // Q_v in double precision: mu_v * 2^24 is exact, the division is correctly
@@ -240,10 +274,10 @@ __device__ inline uint32_t palette_insert(uint32_t* pal, uint32_t q, const uint3
 // so a brick is a few whole cache lines (the layout never changes a result).
 // Each distinct Q also goes into the palette: a workgroup collects its distinct
 // values in LDS and puts them into the global table once at its end, all at a
-// time.  A workgroup with more than PALETTE_N of them (a scanned map) marks
-// the palette as overflowed instead and leaves the table alone: probing a
-// full global table value by value took 2.8 ms on a 128^3 map of distinct
-// values, against 23 us now (segmented map: 20 against 14 us).
+// time (palette_merge).  A workgroup with more than PALETTE_N of them (a
+// scanned map) marks the palette as overflowed instead and leaves the table
+// alone: probing a full global table value by value took 2.8 ms on a 128^3
+// map of distinct values, against 26 us now (segmented map: 20 against 17 us).
 __global__ __launch_bounds__(RED_THREADS) void k_thresholds(ProbDesc* descs) {
     ProbDesc* pd = descs + blockIdx.y;
     const uint64_t nvox = pd->nvox;
@@ -317,11 +351,16 @@ __global__ __launch_bounds__(RED_THREADS) void k_thresholds(ProbDesc* descs) {
     }
     if (!pal) return;
     __syncthreads();
-    // overflowed elsewhere already: nothing reads the palette
-    if (__hip_atomic_load(&pd->pal_state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+    if (n_seen > (uint32_t)PALETTE_N) return;      // *overflow is set
+    // the set as a list
+    __shared__ uint32_t vals[PALETTE_N];
+    __shared__ uint32_t n_vals;
+    if (threadIdx.x == 0) n_vals = 0;
+    __syncthreads();
     for (uint32_t k = threadIdx.x; k < SEEN_N; k += blockDim.x)
-        if (seen[k] != PALETTE_EMPTY && palette_insert(pd->palette, seen[k], &pd->pal_state) == PALETTE_N)
-            atomicOr(&pd->pal_state, 1u);
+        if (seen[k] != PALETTE_EMPTY) vals[atomicAdd(&n_vals, 1u)] = seen[k];
+    __syncthreads();
+    palette_merge(pd->palette, &pd->pal_state, vals, n_vals);
 }
 
 // One-byte palette codes in the threshold layout (skipped when the palette

@@ -279,12 +279,6 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
         hd.back().mu_codes = fd != 0;
         tally_elems += (uint64_t)p.n_views * 2 * p.nv * p.nu;
     }
-    {
-        hipError_t e = launch_staging_batch(d_desc, hd.data(), n_problems, st);
-        if (e != hipSuccess) return hip_fail(e);
-        for (int i = 0; cfd && i < n_problems; ++i)
-            if ((e = launch_cfd_setup(d_desc + i, hd[i], st)) != hipSuccess) return hip_fail(e);
-    }
     hipError_t e = hipSuccess;
     int dev = 0, n_cu = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e);
@@ -313,10 +307,11 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
         }
     }
     const uint32_t chunk = (uint32_t)(64 * hpl);
-    e = launch_prepare_call(d_desc, n_problems, (uint64_t*)(ws + L.prefix),
-                            status, (unsigned long long*)n_events, tally, tally_elems, tally_sq,
-                            chunk, st);
-    if (e != hipSuccess) return hip_fail(e);
+    const CallPrep prep = {(uint64_t*)(ws + L.prefix), chunk, status, (unsigned long long*)n_events,
+                           tally, tally_sq, tally_elems};
+    if ((e = launch_staging_batch(d_desc, hd.data(), n_problems, &prep, st)) != hipSuccess) return hip_fail(e);
+    for (int i = 0; cfd && i < n_problems; ++i)
+        if ((e = launch_cfd_setup(d_desc + i, hd[i], st)) != hipSuccess) return hip_fail(e);
     if (fd && qbytes != 4 && (e = launch_mu_codes(d_desc, hd.data(), n_problems, st)) != hipSuccess)
         return hip_fail(e);
     TransportArgs a;

@@ -240,10 +240,19 @@ __host__ __device__ inline uint64_t guide_capacity(uint64_t nvox) {
     while (c < nvox) c <<= 1;
     return c;
 }
-// forced detection: the brick table of codes and the codes' map values (after
-// the staging and the call's preparation)
+// forced detection: the brick table of codes and the codes' map values (after the staging)
 hipError_t launch_mu_codes(ProbDesc* d_descs, const ProbDesc* h_descs, int n, hipStream_t s);
-hipError_t launch_staging_batch(ProbDesc* d_descs, const ProbDesc* h_descs, int n, hipStream_t s);
+struct CallPrep {       // what a forward call has prepared together with its staging
+    uint64_t* work_prefix;          // [n + 1], then the chunk prefix
+    uint32_t chunk;
+    int64_t* status;
+    unsigned long long* n_events;
+    int64_t* tally;
+    int64_t* tally_sq;
+    uint64_t tally_elems;
+};
+hipError_t launch_staging_batch(ProbDesc* d_descs, const ProbDesc* h_descs, int n, const CallPrep* call,
+                                hipStream_t s);
 
 // Host launchers (transport.hip)
 struct TransportArgs {
@@ -275,10 +284,6 @@ hipError_t launch_finish(const TransportArgs& a, hipStream_t s);
 hipError_t launch_replay(const ProbDesc* d_desc, const int32_t* views, const uint64_t* hists,
                          int64_t n, mc_record* out, int64_t* status, int block, int32_t vr_flags,
                          float vr_omc, hipStream_t s);
-hipError_t launch_prepare_call(const ProbDesc* descs, int32_t n_problems, uint64_t* work_prefix,
-                               int64_t* status, unsigned long long* n_events,
-                               int64_t* tally, uint64_t tally_elems, int64_t* tally_sq,
-                               uint32_t chunk, hipStream_t s);
 
 // Host launcher (adjoint.hip)
 hipError_t launch_adjoint(const ProbDesc* d, const mc_event* events, const uint64_t* n_events,

@@ -20,8 +20,9 @@
 //  * the Klein-Nishina attenuation shape sigma_KN(E)/sigma_KN(140) at 1/4 keV
 //    steps, evaluated in double precision.
 //
-// Every pass streams the grid once with coalesced loads; the whole staging of
-// a 128^3 phantom moves ~40 MB and is far below the transport cost.
+// Four launches: one over everything that only needs the inputs, one workgroup
+// per problem that combines it, the runs and thresholds, the guide table and
+// codes.
 #include <algorithm>
 
 #include "mc_internal.h"
@@ -30,9 +31,7 @@ namespace mcs {
 namespace {
 
 constexpr int RED_THREADS = 256;
-constexpr int ROWS = 4;        // grid rows a row pass loads at once
-constexpr int REDUCE_BLOCKS = 512;      // most workgroups of k_reduce per problem
-constexpr int REDUCE_PART_U64 = 4;      // partial results per workgroup
+constexpr int ROWS = 4;        // values a pass loads at once
 
 __device__ inline uint64_t wave_sum_u64(uint64_t v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -47,149 +46,293 @@ __device__ inline uint32_t wave_or_u32(uint32_t v) {
     return v;
 }
 
-__global__ void k_write_desc(ProbDesc d, ProbDesc* out) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *out = d;
+// Launch 1: everything that needs the caller's inputs and nothing else.  Its
+// workgroups take one of the following by blockIdx.x (blockIdx.y: problem):
+//  * [0, scan_blocks): SCAN_ITEMS voxels each of both maps, read once: max mu
+//    (as bits: order-preserving for non-negative floats), bad-value flag and
+//    attenuation box of the stretch (StagePart), its activity and the runs
+//    starting in it;
+//  * 1: the descriptor (passed by value, so the launch can be captured in a
+//    graph), the work and chunk prefixes, the palette cleared, the view table;
+//  * KN_BLOCKS: the Klein-Nishina table;
+//  * the rest: the call's tallies cleared.
+// One launch for up to STAGE_MAX problems, so small problems overlap instead
+// of queueing.  On small problems staging is bound by its launches, 2 to 5 us
+// each whatever they do: 12 of them (with the call's preparation) took 55 us
+// at 32^3 and 95 us at 128^3, the four 24 and 45 us.
+constexpr int STAGE_MAX = 8;
+constexpr int KN_BLOCKS = (KN_TABLE_N + 255) / 256;
+
+struct StageArgs {
+    ProbDesc d[STAGE_MAX];
+    ProbDesc* out;                  // descriptor of the launch's first problem
+    uint32_t scan_blocks;
+    // the call's preparation (null / 0 for replay and adjoint)
+    uint64_t* work_prefix;          // [n_problems + 1], then as many of the chunk prefix
+    uint64_t work0, chunks0;        // work and chunks before the launch's first problem
+    uint32_t chunk;
+    int first, last, n_problems;    // the launch's problems of the call
+    int64_t* status;
+    unsigned long long* n_events;
+    int64_t* tally;
+    int64_t* tally_sq;
+    uint64_t tally_elems;
+    uint32_t zero_blocks;           // workgroups per problem that clear tallies
+};
+static_assert(sizeof(StageArgs) <= 4096, "kernel arguments");
+
+// What launch 1 finds in one stretch of voxels: max mu, STATUS flags | 1 << 31
+// when mu > 0 somewhere, and the box of those voxels (10 bits per axis).
+struct StagePart {
+    uint32_t mx, flags, lo, hi;
+};
+constexpr uint32_t PART_ANY = 1u << 31;
+
+// Klein-Nishina total cross-section per electron over 2 pi r_e^2 (closed form).
+__device__ double kn_bracket(double e) {
+    const double k = e / 510.99895;
+    const double a = 1.0 + 2.0 * k;
+    const double la = log(a);
+    return (1.0 + k) / (k * k) * (2.0 * (1.0 + k) / a - la / k) + la / (2.0 * k)
+           - (1.0 + 3.0 * k) / (a * a);
 }
 
-// Max mu (as bits: order-preserving for non-negative floats), bad-value flags,
-// activity total, view table.
-__global__ __launch_bounds__(RED_THREADS) void k_reduce(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
-    const uint64_t nvox = pd->nvox;
-    const float* __restrict__ mu = pd->mu;
-    const uint32_t* __restrict__ act = pd->act;
-    const uint32_t* __restrict__ prev = pd->act_prev;
-    const uint32_t nx = (uint32_t)pd->nx, ny = (uint32_t)pd->ny;
-    uint32_t mx = 0, flags = 0;
+// Voxel i starts a run: it is active and its row neighbour on the left (none
+// at ix = 0) has a different weight.
+__device__ inline bool run_start(uint32_t a, uint32_t a_left, uint32_t ix) {
+    return a > 0 && (ix == 0 || a_left != a);
+}
+
+__device__ inline void stage_scan(const ProbDesc& d) {
+    const uint64_t nvox = d.nvox;
+    const uint64_t base = (uint64_t)blockIdx.x * SCAN_ITEMS;
+    if (base >= nvox) return;               // past this problem's blocks
+    constexpr int PER = SCAN_ITEMS / SCAN_THREADS;
+    const float* __restrict__ mu = d.mu;
+    const uint32_t* __restrict__ act = d.act;
+    const uint32_t* __restrict__ prev = d.act_prev;
+    const uint32_t nx = (uint32_t)d.nx, ny = (uint32_t)d.ny;
+    // voxels base + j SCAN_THREADS + thread: coordinates by one division, then
+    // steps of SCAN_THREADS voxels
+    uint32_t i0 = (uint32_t)base + threadIdx.x;
+    uint32_t ix = i0 % nx, iy = i0 / nx % ny, iz = i0 / nx / ny;
+    const uint32_t sx = SCAN_THREADS % nx, sy = SCAN_THREADS / nx % ny, sz = SCAN_THREADS / nx / ny;
+    uint32_t mx = 0, flags = 0, runs = 0;
     uint64_t sum = 0;
-    int lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {-1, -1, -1};
-    // grid rows (iy, iz) per block step, threads along x: no index division;
-    // ROWS rows per step, their loads issued before any is used
-    const uint32_t nrows = ny * (uint32_t)pd->nz;
-    for (uint32_t r0 = blockIdx.x; r0 < nrows; r0 += ROWS * gridDim.x)
-    for (uint32_t ix = threadIdx.x; ix < nx; ix += blockDim.x) {
-        float m[ROWS];
-        uint32_t w[ROWS];
+    uint32_t lo[3] = {1023u, 1023u, 1023u}, hi[3] = {0u, 0u, 0u};
+#pragma unroll 4
+    for (int j0 = 0; j0 < PER; j0 += 4) {
+        float m[4];
+        uint32_t w[4], l[4];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            const uint32_t r = r0 + (uint32_t)u * gridDim.x;
-            const uint64_t i = (uint64_t)r * nx + ix;
-            m[u] = r < nrows ? mu[i] : 0.0f;
-            w[u] = r < nrows ? source_weight(act, prev, i) : 0u;
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t i = base + (uint64_t)(j0 + u) * SCAN_THREADS + threadIdx.x;
+            m[u] = i < nvox ? mu[i] : 0.0f;
+            w[u] = i < nvox ? source_weight(act, prev, i) : 0u;
+            l[u] = i < nvox && i > 0 ? source_weight(act, prev, i - 1) : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            const uint32_t r = r0 + (uint32_t)u * gridDim.x;
-            if (r >= nrows) break;
-            const int iy = (int)(r % ny), iz = (int)(r / ny);
+        for (int u = 0; u < 4; ++u) {
             if (!(m[u] >= 0.0f) || !isfinite(m[u])) flags |= MC_STATUS_BAD_MU;
             else if (m[u] > 0.0f) {
+                flags |= PART_ANY;
                 mx = max(mx, __float_as_uint(m[u]));
-                lo[0] = min(lo[0], (int)ix); hi[0] = max(hi[0], (int)ix);
+                lo[0] = min(lo[0], ix); hi[0] = max(hi[0], ix);
                 lo[1] = min(lo[1], iy); hi[1] = max(hi[1], iy);
                 lo[2] = min(lo[2], iz); hi[2] = max(hi[2], iz);
             }
             sum += w[u];
-        }
-    }
-    (void)nvox;
-    mx = wave_max_u32(mx);
-    flags = wave_or_u32(flags);
-    sum = wave_sum_u64(sum);
-    for (int a = 0; a < 3; ++a) {
-        for (int o = 32; o > 0; o >>= 1) {
-            lo[a] = min(lo[a], __shfl_xor(lo[a], o, 64));
-            hi[a] = max(hi[a], __shfl_xor(hi[a], o, 64));
-        }
-    }
-
-    // per-block partials (the scan's block-sum scratch, idle until the scan):
-    // k_reduce_final combines them.  One atomic per block on the same few
-    // descriptor fields serialised in memory.
-    __shared__ uint32_t s_mx[RED_THREADS / 64], s_fl[RED_THREADS / 64];
-    __shared__ uint64_t s_sum[RED_THREADS / 64];
-    __shared__ int s_lo[RED_THREADS / 64][3], s_hi[RED_THREADS / 64][3];
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        s_mx[w] = mx; s_fl[w] = flags; s_sum[w] = sum;
-        for (int a = 0; a < 3; ++a) { s_lo[w][a] = lo[a]; s_hi[w][a] = hi[a]; }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < (int)((blockDim.x + 63) >> 6); ++k) {
-            mx = max(mx, s_mx[k]); flags |= s_fl[k]; sum += s_sum[k];
-            for (int a = 0; a < 3; ++a) { lo[a] = min(lo[a], s_lo[k][a]); hi[a] = max(hi[a], s_hi[k][a]); }
-        }
-        uint64_t lo_p = 0, hi_p = 0;     // 16 bits per axis: lo (0xFFFF: none), hi + 1 (0: none)
-        for (int a = 0; a < 3; ++a) {
-            lo_p |= (uint64_t)(hi[a] >= 0 ? (uint32_t)lo[a] : 0xFFFFu) << (16 * a);
-            hi_p |= (uint64_t)(hi[a] >= 0 ? (uint32_t)hi[a] + 1u : 0u) << (16 * a);
-        }
-        uint64_t* part = pd->block_sums + (uint64_t)blockIdx.x * REDUCE_PART_U64;
-        part[0] = (uint64_t)mx | ((uint64_t)flags << 32);
-        part[1] = sum;
-        part[2] = lo_p;
-        part[3] = hi_p;
-    }
-    if (blockIdx.x == 0) {
-        if (pd->pal_state == 0)
-            for (int k = threadIdx.x; k < PALETTE_N; k += blockDim.x) pd->palette[k] = PALETTE_EMPTY;
-        for (int k = threadIdx.x; k < pd->n_views; k += blockDim.x) {
-            const double a = pd->angles[k];
-            if (!isfinite(a)) atomicOr(&pd->flags, (uint32_t)MC_STATUS_BAD_ANGLE);
-            pd->views[k] = make_float2((float)cos(a), (float)sin(a));
-        }
-    }
-}
-
-// Combine k_reduce's n_parts partials: max mu, flags, activity total and the
-// attenuation box, written to the descriptor (one workgroup per problem).
-__global__ __launch_bounds__(RED_THREADS) void k_reduce_final(ProbDesc* descs, int n_parts) {
-    ProbDesc* pd = descs + blockIdx.y;
-    uint32_t mx = 0, flags = 0;
-    uint64_t sum = 0;
-    uint32_t lo[3] = {0xFFFFu, 0xFFFFu, 0xFFFFu}, hi[3] = {0, 0, 0};
-    for (int b = threadIdx.x; b < n_parts; b += blockDim.x) {
-        const uint64_t* part = pd->block_sums + (uint64_t)b * REDUCE_PART_U64;
-        const uint64_t p0 = part[0], p2 = part[2], p3 = part[3];
-        mx = max(mx, (uint32_t)p0);
-        flags |= (uint32_t)(p0 >> 32);
-        sum += part[1];
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = min(lo[a], (uint32_t)(p2 >> (16 * a)) & 0xFFFFu);
-            hi[a] = max(hi[a], (uint32_t)(p3 >> (16 * a)) & 0xFFFFu);
+            runs += run_start(w[u], l[u], ix);
+            ix += sx; iy += sy; iz += sz;
+            if (ix >= nx) { ix -= nx; ++iy; }
+            if (iy >= ny) { iy -= ny; ++iz; }
         }
     }
     mx = wave_max_u32(mx);
     flags = wave_or_u32(flags);
     sum = wave_sum_u64(sum);
+    runs = (uint32_t)wave_sum_u64(runs);
     for (int a = 0; a < 3; ++a) {
         for (int o = 32; o > 0; o >>= 1) {
             lo[a] = min(lo[a], (uint32_t)__shfl_xor((int)lo[a], o, 64));
             hi[a] = max(hi[a], (uint32_t)__shfl_xor((int)hi[a], o, 64));
         }
     }
-    __shared__ uint32_t s_mx[RED_THREADS / 64], s_fl[RED_THREADS / 64];
-    __shared__ uint64_t s_sum[RED_THREADS / 64];
-    __shared__ uint32_t s_lo[RED_THREADS / 64][3], s_hi[RED_THREADS / 64][3];
-    const int w = threadIdx.x >> 6;
+    __shared__ StagePart part[SCAN_THREADS / 64];
+    __shared__ uint64_t part_sum[SCAN_THREADS / 64];
+    __shared__ uint32_t part_runs[SCAN_THREADS / 64];
     if ((threadIdx.x & 63) == 0) {
-        s_mx[w] = mx; s_fl[w] = flags; s_sum[w] = sum;
-        for (int a = 0; a < 3; ++a) { s_lo[w][a] = lo[a]; s_hi[w][a] = hi[a]; }
+        const int v = threadIdx.x >> 6;
+        part[v] = StagePart{mx, flags, lo[0] | lo[1] << 10 | lo[2] << 20, hi[0] | hi[1] << 10 | hi[2] << 20};
+        part_sum[v] = sum;
+        part_runs[v] = runs;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < (int)((blockDim.x + 63) >> 6); ++k) {
-            mx = max(mx, s_mx[k]); flags |= s_fl[k]; sum += s_sum[k];
-            for (int a = 0; a < 3; ++a) { lo[a] = min(lo[a], s_lo[k][a]); hi[a] = max(hi[a], s_hi[k][a]); }
+        StagePart p = part[0];
+        for (int v = 1; v < SCAN_THREADS / 64; ++v) {
+            const StagePart q = part[v];
+            p.mx = max(p.mx, q.mx);
+            p.flags |= q.flags;
+            uint32_t plo = 0, phi = 0;
+            for (int a = 0; a < 30; a += 10) {
+                plo |= min(p.lo >> a & 1023u, q.lo >> a & 1023u) << a;
+                phi |= max(p.hi >> a & 1023u, q.hi >> a & 1023u) << a;
+            }
+            p.lo = plo;
+            p.hi = phi;
+            sum += part_sum[v];
+            runs += part_runs[v];
         }
-        pd->mu_hat_bits = mx;
-        if (flags) pd->flags |= flags;
-        pd->total = sum;
-        if (hi[0] > 0) {
+        // in the threshold table's place: it is written from launch 3 on
+        ((StagePart*)d.q32)[blockIdx.x] = p;
+        d.block_sums[blockIdx.x] = sum;
+        d.block_cnt[blockIdx.x] = runs;
+    }
+}
+
+__global__ __launch_bounds__(SCAN_THREADS) void k_stage_scan(StageArgs A) {
+    const ProbDesc& d = A.d[blockIdx.y];
+    uint32_t b = blockIdx.x;
+    if (b < A.scan_blocks) {
+        stage_scan(d);
+        return;
+    }
+    b -= A.scan_blocks;
+    if (b == 0) {
+        __shared__ uint32_t bad_angle;
+        if (threadIdx.x == 0) bad_angle = 0;
+        __syncthreads();
+        if (d.pal_state == 0)
+            for (int k = threadIdx.x; k < PALETTE_N; k += SCAN_THREADS) d.palette[k] = PALETTE_EMPTY;
+        for (int k = threadIdx.x; k < d.n_views; k += SCAN_THREADS) {
+            const double a = d.angles[k];
+            if (!isfinite(a)) bad_angle = 1;
+            d.views[k] = make_float2((float)cos(a), (float)sin(a));
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            ProbDesc& out = A.out[blockIdx.y];
+            out = d;
+            if (bad_angle) out.flags |= (uint32_t)MC_STATUS_BAD_ANGLE;
+            if (A.work_prefix) {
+                const int p = A.first + (int)blockIdx.y;
+                uint64_t w = A.work0, c = A.chunks0;
+                for (int k = 0; k < (int)blockIdx.y; ++k) {
+                    w += A.d[k].work_count;
+                    c += (A.d[k].work_count + A.chunk - 1) / A.chunk;
+                }
+                uint64_t* chunk_prefix = A.work_prefix + (A.n_problems + 1);
+                A.work_prefix[p] = w;
+                chunk_prefix[p] = c;
+                if (p + 1 == A.n_problems) {
+                    A.work_prefix[p + 1] = w + d.work_count;
+                    chunk_prefix[p + 1] = c + (d.work_count + A.chunk - 1) / A.chunk;
+                }
+                if (p == 0) {
+                    for (int k = 0; k < 4; ++k) A.status[k] = 0;
+                    if (A.n_events) *A.n_events = 0;
+                }
+            }
+        }
+        return;
+    }
+    b -= 1;
+    if (b < (uint32_t)KN_BLOCKS) {
+        const int i = (int)(b * SCAN_THREADS + threadIdx.x);
+        if (i < KN_TABLE_N) {
+            const double e = fmax((double)d.e0 - 0.25 * i, 0.5);
+            d.kn_table[i] = (float)(kn_bracket(e) / kn_bracket(140.0));
+        }
+        return;
+    }
+    b -= KN_BLOCKS;
+    const uint64_t stride = (uint64_t)A.zero_blocks * gridDim.y * SCAN_THREADS;
+    for (uint64_t i = ((uint64_t)b * gridDim.y + blockIdx.y) * SCAN_THREADS + threadIdx.x; i < A.tally_elems;
+         i += stride) {
+        A.tally[i] = 0;
+        if (A.tally_sq) A.tally_sq[i] = 0;
+    }
+}
+
+// Launch 2, one workgroup of 1024 threads per problem: the stretches' results
+// combined into the descriptor (max mu, flags, box), their sums and run counts
+// scanned (each thread a contiguous stretch of blocks), the activity total and
+// the number of runs.
+__global__ __launch_bounds__(1024) void k_stage_top(ProbDesc* descs) {
+    ProbDesc* pd = descs + blockIdx.y;
+    const int n_blocks = (int)((pd->nvox + SCAN_ITEMS - 1) / SCAN_ITEMS);
+    __shared__ uint64_t tot[16];
+    __shared__ uint32_t totc[16];
+    __shared__ uint32_t s_mx, s_fl, s_lo[3], s_hi[3];
+    uint64_t* __restrict__ bs = pd->block_sums;
+    uint32_t* __restrict__ bc = pd->block_cnt;
+    const StagePart* __restrict__ parts = (const StagePart*)pd->q32;
+    if (threadIdx.x < 3) { s_lo[threadIdx.x] = 1023u; s_hi[threadIdx.x] = 0u; }
+    if (threadIdx.x == 3) s_mx = s_fl = 0;
+    const int per = (n_blocks + 1023) / 1024;
+    const int b0 = threadIdx.x * per;
+    uint64_t s = 0;
+    uint32_t c = 0, mx = 0, fl = 0, lo[3] = {1023u, 1023u, 1023u}, hi[3] = {0u, 0u, 0u};
+    for (int j = 0; j < per; ++j) {
+        if (b0 + j >= n_blocks) break;
+        s += bs[b0 + j];
+        c += bc[b0 + j];
+        const StagePart p = parts[b0 + j];
+        mx = max(mx, p.mx);
+        fl |= p.flags;
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = min(lo[a], p.lo >> (10 * a) & 1023u);
+            hi[a] = max(hi[a], p.hi >> (10 * a) & 1023u);
+        }
+    }
+    // wavefront scans, then the wavefronts' totals
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t x = s;
+    uint32_t xc = c;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = (uint64_t)__shfl_up((long long)x, o, 64);
+        const uint32_t yc = (uint32_t)__shfl_up((int)xc, o, 64);
+        if (lane >= o) { x += y; xc += yc; }
+    }
+    if (lane == 63) { tot[wave] = x; totc[wave] = xc; }
+    mx = wave_max_u32(mx);
+    fl = wave_or_u32(fl);
+    for (int a = 0; a < 3; ++a) {
+        for (int o = 32; o > 0; o >>= 1) {
+            lo[a] = min(lo[a], (uint32_t)__shfl_xor((int)lo[a], o, 64));
+            hi[a] = max(hi[a], (uint32_t)__shfl_xor((int)hi[a], o, 64));
+        }
+    }
+    __syncthreads();
+    if (lane == 0) {
+        atomicMax(&s_mx, mx);
+        atomicOr(&s_fl, fl);
+        for (int a = 0; a < 3; ++a) { atomicMin(&s_lo[a], lo[a]); atomicMax(&s_hi[a], hi[a]); }
+    }
+    uint64_t run = x - s;                  // exclusive prefix of this thread's stretch
+    uint32_t runc = xc - c;
+    for (int v = 0; v < wave; ++v) { run += tot[v]; runc += totc[v]; }
+    for (int j = 0; j < per; ++j) {
+        if (b0 + j < n_blocks) {
+            const uint64_t v = bs[b0 + j];
+            const uint32_t vc = bc[b0 + j];
+            bs[b0 + j] = run;
+            bc[b0 + j] = runc;
+            run += v;
+            runc += vc;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 1023) {
+        pd->total = run;
+        pd->n_runs = runc;
+        pd->mu_hat_bits = s_mx;
+        if (s_fl & ~PART_ANY) pd->flags |= s_fl & ~PART_ANY;
+        if (s_fl & PART_ANY) {
             for (int a = 0; a < 3; ++a) {
-                pd->bb_lo[a] = (int)lo[a];
-                pd->bb_hi[a] = (int)hi[a] - 1;
+                pd->bb_lo[a] = (int)s_lo[a];
+                pd->bb_hi[a] = (int)s_hi[a];
             }
         }
     }
@@ -269,6 +412,12 @@ __device__ inline void palette_merge(uint32_t* pal, uint32_t* overflow, const ui
     }
 }
 
+// Index of linear voxel i in the threshold layout.
+__device__ inline uint32_t table_index(uint32_t i, uint32_t nx, uint32_t ny, int b, uint32_t m, uint32_t nbx,
+                                       uint32_t nby) {
+    return b == 0 ? i : brick_index(i % nx, i / nx % ny, i / nx / ny, nx, ny, b, m, nbx, nby);
+}
+
 // Q_v in double precision: mu_v * 2^24 is exact, the division is correctly
 // rounded, ceil is exact.  Stored linear (b = 0) or in 2^b-voxel cubic bricks,
 // so a brick is a few whole cache lines (the layout never changes a result).
@@ -278,8 +427,7 @@ __device__ inline void palette_merge(uint32_t* pal, uint32_t* overflow, const ui
 // scanned map) marks the palette as overflowed instead and leaves the table
 // alone: probing a full global table value by value took 2.8 ms on a 128^3
 // map of distinct values, against 26 us now (segmented map: 20 against 17 us).
-__global__ __launch_bounds__(RED_THREADS) void k_thresholds(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
+__device__ inline void stage_thresholds(ProbDesc* pd, uint32_t block, uint32_t n_blocks) {
     const uint64_t nvox = pd->nvox;
     const float mu_hat = __uint_as_float(pd->mu_hat_bits);
     const float* __restrict__ mu = pd->mu;
@@ -288,75 +436,46 @@ __global__ __launch_bounds__(RED_THREADS) void k_thresholds(ProbDesc* descs) {
     const int b = pd->brick_log2;
     const uint32_t m = (1u << b) - 1u;
     const uint32_t nbx = (uint32_t)pd->nbx, nby = (uint32_t)pd->nby;
-    const uint32_t nrows = ny * (uint32_t)pd->nz;
     __shared__ uint32_t seen[SEEN_N];
-    __shared__ uint32_t n_seen, pal_off;
+    __shared__ uint32_t vals[PALETTE_N];
+    __shared__ uint32_t n_seen, n_vals, pal_off;
     for (uint32_t k = threadIdx.x; k < SEEN_N; k += blockDim.x) seen[k] = PALETTE_EMPTY;
     if (threadIdx.x == 0) {
-        n_seen = 0;
+        n_seen = n_vals = 0;
         pal_off = __hip_atomic_load(&pd->pal_state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     const bool pal = pal_off == 0;      // one answer for the workgroup: others may set it meanwhile
-    // Q of one value; the last value a lane has put in the set is not looked up again
+    // whole wavefronts stream the map, ROWS values per thread in flight; the
+    // last value a lane has put in the set is not looked up again
     uint32_t last = PALETTE_EMPTY;
-    auto threshold = [&](float mv, bool ok) -> uint32_t {
-        uint32_t v = 0;
-        if (ok && mu_hat > 0.0f && mv > 0.0f) {
-            const double t = ceil((double)mv * 16777216.0 / (double)mu_hat);
-            v = t >= 16777216.0 ? 16777216u : (uint32_t)t;
+    const uint64_t stride = (uint64_t)n_blocks * blockDim.x;
+    for (uint64_t i0 = (uint64_t)block * blockDim.x + threadIdx.x; i0 < nvox; i0 += ROWS * stride) {
+        float mv[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const uint64_t i = i0 + (uint64_t)u * stride;
+            mv[u] = i < nvox ? mu[i] : 0.0f;
         }
-        if (pal && ok && v != last) {
-            seen_insert(seen, &n_seen, v, &pd->pal_state);
-            last = v;
-        }
-        return v;
-    };
-    if (b == 0) {
-        // linear layout: the table index is the voxel index, so whole
-        // wavefronts stream the grid, ROWS values per thread in flight
-        const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-        for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < nvox; i0 += ROWS * stride) {
-            float mv[ROWS];
 #pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint64_t i = i0 + (uint64_t)u * stride;
-                mv[u] = i < nvox ? mu[i] : 0.0f;
+        for (int u = 0; u < ROWS; ++u) {
+            const uint64_t i = i0 + (uint64_t)u * stride;
+            if (i >= nvox) break;
+            uint32_t v = 0;
+            if (mu_hat > 0.0f && mv[u] > 0.0f) {
+                const double t = ceil((double)mv[u] * 16777216.0 / (double)mu_hat);
+                v = t >= 16777216.0 ? 16777216u : (uint32_t)t;
             }
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint64_t i = i0 + (uint64_t)u * stride;
-                const uint32_t v = threshold(mv[u], i < nvox);
-                if (i < nvox) q[i] = v;
-            }
-        }
-    } else {
-        for (uint32_t r0 = blockIdx.x; r0 < nrows; r0 += ROWS * gridDim.x)
-        for (uint32_t ix = threadIdx.x; ix < nx; ix += blockDim.x) {
-            // ROWS rows per step, their loads issued before any is used
-            float mrow[ROWS];
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint32_t r = r0 + (uint32_t)u * gridDim.x;
-                mrow[u] = r < nrows ? mu[(uint64_t)r * nx + ix] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint32_t r = r0 + (uint32_t)u * gridDim.x;
-                if (r >= nrows) break;
-                const uint32_t v = threshold(mrow[u], true);
-                q[brick_index(ix, r % ny, r / ny, nx, ny, b, m, nbx, nby)] = v;
+            q[table_index((uint32_t)i, nx, ny, b, m, nbx, nby)] = v;
+            if (pal && v != last) {
+                seen_insert(seen, &n_seen, v, &pd->pal_state);
+                last = v;
             }
         }
     }
     if (!pal) return;
     __syncthreads();
     if (n_seen > (uint32_t)PALETTE_N) return;      // *overflow is set
-    // the set as a list
-    __shared__ uint32_t vals[PALETTE_N];
-    __shared__ uint32_t n_vals;
-    if (threadIdx.x == 0) n_vals = 0;
-    __syncthreads();
     for (uint32_t k = threadIdx.x; k < SEEN_N; k += blockDim.x)
         if (seen[k] != PALETTE_EMPTY) vals[atomicAdd(&n_vals, 1u)] = seen[k];
     __syncthreads();
@@ -365,55 +484,30 @@ __global__ __launch_bounds__(RED_THREADS) void k_thresholds(ProbDesc* descs) {
 
 // One-byte palette codes in the threshold layout (skipped when the palette
 // overflowed or was not requested: the kernels then read the 32-bit table).
-__global__ __launch_bounds__(RED_THREADS) void k_codes(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
+// Table entries are taken in table order, whatever voxel they hold (padding
+// of a bricked layout holds no voxel and gets some code that nothing reads).
+__device__ inline void stage_codes(ProbDesc* pd, uint32_t block, uint32_t n_blocks) {
     if (pd->pal_state != 0) return;
-    const uint64_t nvox = pd->nvox;
+    const int b = pd->brick_log2;
+    const uint64_t n = b == 0 ? pd->nvox : (uint64_t)pd->nbx * pd->nby * pd->nbz << (3 * b);
     const uint32_t* __restrict__ q = pd->q32;
     const uint32_t* __restrict__ pal = pd->palette;
     uint8_t* __restrict__ code = pd->q8;
-    const uint32_t nx = (uint32_t)pd->nx, ny = (uint32_t)pd->ny;
-    const int b = pd->brick_log2;
-    const uint32_t m = (1u << b) - 1u;
-    const uint32_t nbx = (uint32_t)pd->nbx, nby = (uint32_t)pd->nby;
-    const uint32_t nrows = ny * (uint32_t)pd->nz;
-    auto code_of = [&](uint32_t v) {
-        uint32_t h = palette_hash(v);
-        for (int probe = 0; probe < PALETTE_N && pal[h] != v; ++probe) h = (h + 1) & (PALETTE_N - 1);
-        return (uint8_t)h;
-    };
-    if (b == 0) {
-        // linear layout: whole wavefronts stream the table, ROWS values per thread
-        const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-        for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < nvox; i0 += ROWS * stride) {
-            uint32_t v[ROWS];
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint64_t i = i0 + (uint64_t)u * stride;
-                v[u] = i < nvox ? q[i] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const uint64_t i = i0 + (uint64_t)u * stride;
-                if (i < nvox) code[i] = code_of(v[u]);
-            }
-        }
-        return;
-    }
-    for (uint32_t r0 = blockIdx.x; r0 < nrows; r0 += ROWS * gridDim.x)
-    for (uint32_t ix = threadIdx.x; ix < nx; ix += blockDim.x) {
-        // ROWS rows per step, their loads issued before any is used
-        uint32_t k[ROWS], v[ROWS];
+    const uint64_t stride = (uint64_t)n_blocks * blockDim.x;
+    for (uint64_t i0 = (uint64_t)block * blockDim.x + threadIdx.x; i0 < n; i0 += ROWS * stride) {
+        uint32_t v[ROWS];
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            const uint32_t r = r0 + (uint32_t)u * gridDim.x;
-            k[u] = brick_index(ix, r % ny, r / ny, nx, ny, b, m, nbx, nby);
-            v[u] = r < nrows ? q[k[u]] : 0u;
+            const uint64_t i = i0 + (uint64_t)u * stride;
+            v[u] = i < n ? q[i] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            if (r0 + (uint32_t)u * gridDim.x >= nrows) break;
-            code[k[u]] = code_of(v[u]);
+            const uint64_t i = i0 + (uint64_t)u * stride;
+            if (i >= n) break;
+            uint32_t h = palette_hash(v[u]);
+            for (int probe = 0; probe < PALETTE_N && pal[h] != v[u]; ++probe) h = (h + 1) & (PALETTE_N - 1);
+            code[i] = (uint8_t)h;
         }
     }
 }
@@ -478,96 +572,11 @@ __global__ __launch_bounds__(RED_THREADS) void k_mu_codes(ProbDesc* descs) {
     if (threadIdx.x == 0 && clash) atomicOr(&pd->mu_pal_bad, 1u);
 }
 
-// --- three-pass scan of the activity map: uint64 sums of the source weight
-// and the runs of equal weight, so the emission tables hold one entry per run
-// (a segmented phantom has ~1e4 runs against ~1e6 active voxels) ---
-
-// Voxel i starts a run: it is active and its row neighbour on the left (none
-// at ix = 0) has a different weight.
-__device__ inline bool run_start(uint32_t a, uint32_t a_left, uint64_t i, uint32_t nx) {
-    return a > 0 && (i % nx == 0 || a_left != a);
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_sums(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
-    const uint64_t nvox = pd->nvox;
-    if ((uint64_t)blockIdx.x * SCAN_ITEMS >= nvox) return;   // past this problem's blocks
-    const uint32_t* __restrict__ act = pd->act;
-    const uint32_t* __restrict__ prev = pd->act_prev;
-    const uint32_t nx = (uint32_t)pd->nx;
-    const uint64_t base = (uint64_t)blockIdx.x * SCAN_ITEMS;
-    uint64_t s = 0;
-    uint32_t c = 0;
-    for (int j = threadIdx.x; j < SCAN_ITEMS; j += SCAN_THREADS) {
-        const uint64_t i = base + j;
-        if (i < nvox) {
-            const uint32_t a = source_weight(act, prev, i);
-            const uint32_t l = i > 0 ? source_weight(act, prev, i - 1) : 0u;
-            s += a;
-            c += run_start(a, l, i, nx);
-        }
-    }
-    s = wave_sum_u64(s);
-    c = (uint32_t)wave_sum_u64(c);
-    __shared__ uint64_t part[SCAN_THREADS / 64];
-    __shared__ uint32_t partc[SCAN_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) { part[threadIdx.x >> 6] = s; partc[threadIdx.x >> 6] = c; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
-        uint32_t tc = 0;
-        for (int w = 0; w < SCAN_THREADS / 64; ++w) { t += part[w]; tc += partc[w]; }
-        pd->block_sums[blockIdx.x] = t;
-        pd->block_cnt[blockIdx.x] = tc;
-    }
-}
-
-// Exclusive scan of the block sums and run counts, one block of 1024
-// threads, each thread a contiguous stretch; also records the number of runs.
-__global__ __launch_bounds__(1024) void k_scan_top(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
-    const int n_blocks = (int)((pd->nvox + SCAN_ITEMS - 1) / SCAN_ITEMS);
-    __shared__ uint64_t tot[1024];
-    __shared__ uint32_t totc[1024];
-    uint64_t* __restrict__ bs = pd->block_sums;
-    uint32_t* __restrict__ bc = pd->block_cnt;
-    const int per = (n_blocks + 1023) / 1024;
-    const int b0 = threadIdx.x * per;
-    uint64_t s = 0;
-    uint32_t c = 0;
-    for (int j = 0; j < per; ++j) if (b0 + j < n_blocks) { s += bs[b0 + j]; c += bc[b0 + j]; }
-    tot[threadIdx.x] = s;
-    totc[threadIdx.x] = c;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint64_t v = threadIdx.x >= (unsigned)off ? tot[threadIdx.x - off] : 0;
-        const uint32_t vc = threadIdx.x >= (unsigned)off ? totc[threadIdx.x - off] : 0;
-        __syncthreads();
-        tot[threadIdx.x] += v;
-        totc[threadIdx.x] += vc;
-        __syncthreads();
-    }
-    if (threadIdx.x == 1023) pd->n_runs = totc[1023];
-    uint64_t run = tot[threadIdx.x] - s;   // exclusive prefix of this thread's stretch
-    uint32_t runc = totc[threadIdx.x] - c;
-    for (int j = 0; j < per; ++j) {
-        if (b0 + j < n_blocks) {
-            const uint64_t v = bs[b0 + j];
-            const uint32_t vc = bc[b0 + j];
-            bs[b0 + j] = run;
-            bc[b0 + j] = runc;
-            run += v;
-            runc += vc;
-        }
-    }
-}
-
 // Per block: 16 consecutive voxels per thread, thread-local scans, block
 // exclusive scans of the thread totals, plus the block offsets; each voxel
 // that starts a run writes the run (cumulative weight before it, its packed
 // coordinates, its weight) at its compacted slot.
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_final(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
+__device__ inline void stage_runs(const ProbDesc* pd) {
     constexpr int PER = SCAN_ITEMS / SCAN_THREADS;
     const uint64_t nvox = pd->nvox;
     if ((uint64_t)blockIdx.x * SCAN_ITEMS >= nvox) return;   // past this problem's blocks
@@ -578,6 +587,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_final(ProbDesc* descs) {
     const uint32_t nx = (uint32_t)pd->nx, ny = (uint32_t)pd->ny;
     uint32_t a[PER];
     const uint32_t left0 = (base > 0 && base < nvox) ? source_weight(act, prev, base - 1) : 0u;
+    const uint32_t ix0 = (uint32_t)base % nx;
     uint64_t s = 0;
     uint32_t c = 0;
 #pragma unroll
@@ -587,27 +597,29 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_final(ProbDesc* descs) {
         s += a[j];
     }
     uint32_t starts = 0;        // bit j: voxel base + j starts a run
+    uint32_t rx = ix0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const uint32_t l = j > 0 ? a[j - 1] : left0;
-        if (base + j < nvox && run_start(a[j], l, base + j, nx)) starts |= 1u << j;
+        if (base + j < nvox && run_start(a[j], l, rx)) starts |= 1u << j;
+        if (++rx == nx) rx = 0;
     }
     c = __popc(starts);
-    __shared__ uint64_t tot[SCAN_THREADS];
-    __shared__ uint32_t totc[SCAN_THREADS];
-    tot[threadIdx.x] = s;
-    totc[threadIdx.x] = c;
-    __syncthreads();
-    for (int off = 1; off < SCAN_THREADS; off <<= 1) {
-        const uint64_t t = threadIdx.x >= (unsigned)off ? tot[threadIdx.x - off] : 0;
-        const uint32_t tc = threadIdx.x >= (unsigned)off ? totc[threadIdx.x - off] : 0;
-        __syncthreads();
-        tot[threadIdx.x] += t;
-        totc[threadIdx.x] += tc;
-        __syncthreads();
+    __shared__ uint64_t tot[SCAN_THREADS / 64];
+    __shared__ uint32_t totc[SCAN_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t x = s;
+    uint32_t xc = c;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = (uint64_t)__shfl_up((long long)x, o, 64);
+        const uint32_t yc = (uint32_t)__shfl_up((int)xc, o, 64);
+        if (lane >= o) { x += y; xc += yc; }
     }
-    uint64_t before = pd->block_sums[blockIdx.x] + tot[threadIdx.x] - s;   // weight before voxel base
-    uint32_t k = pd->block_cnt[blockIdx.x] + totc[threadIdx.x] - c;
+    if (lane == 63) { tot[wave] = x; totc[wave] = xc; }
+    __syncthreads();
+    uint64_t before = pd->block_sums[blockIdx.x] + x - s;   // weight before voxel base
+    uint32_t k = pd->block_cnt[blockIdx.x] + xc - c;
+    for (int v = 0; v < wave; ++v) { before += tot[v]; k += totc[v]; }
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         if (starts & (1u << j)) {
@@ -641,13 +653,12 @@ __device__ inline uint64_t first_run_above(const uint4* __restrict__ runs, uint6
     return lo;
 }
 
-__global__ __launch_bounds__(RED_THREADS) void k_guide(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
+__device__ inline void stage_guide(ProbDesc* pd, uint32_t block, uint32_t n_blocks) {
     const uint64_t nb_cap = guide_capacity(pd->nvox);
     const uint64_t total = pd->total;
     const uint64_t R = pd->n_runs;
     if (total == 0 || R == 0) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&pd->flags, (uint32_t)MC_STATUS_NO_ACTIVITY);
+        if (block == 0 && threadIdx.x == 0) atomicOr(&pd->flags, (uint32_t)MC_STATUS_NO_ACTIVITY);
         return;
     }
     uint64_t cap = 1;
@@ -656,7 +667,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_guide(ProbDesc* descs) {
     uint32_t s = 0;
     while (((total - 1) >> s) >= cap) ++s;
     const uint64_t B = ((total - 1) >> s) + 1;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (block == 0 && threadIdx.x == 0) {
         pd->shift = s;
         pd->n_buckets = (uint32_t)B;
     }
@@ -669,8 +680,8 @@ __global__ __launch_bounds__(RED_THREADS) void k_guide(ProbDesc* descs) {
     // consecutive buckets, one search per lane, and completes 63 of them with
     // its neighbour's.
     const int lane = threadIdx.x & 63;
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint64_t n_waves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+    const uint64_t wave = ((uint64_t)block * blockDim.x + threadIdx.x) >> 6;
+    const uint64_t n_waves = ((uint64_t)n_blocks * blockDim.x) >> 6;
     for (uint64_t grp = wave; grp * 63 < B; grp += n_waves) {
         const uint64_t b = grp * 63 + (uint64_t)lane;
         const uint64_t fa = b < B ? first_run_above(runs, R, b << s) : R;   // >= 1
@@ -690,21 +701,25 @@ __global__ __launch_bounds__(RED_THREADS) void k_guide(ProbDesc* descs) {
     }
 }
 
-// Klein-Nishina total cross-section per electron over 2 pi r_e^2 (closed form).
-__device__ double kn_bracket(double e) {
-    const double k = e / 510.99895;
-    const double a = 1.0 + 2.0 * k;
-    const double la = log(a);
-    return (1.0 + k) / (k * k) * (2.0 * (1.0 + k) / a - la / k) + la / (2.0 * k)
-           - (1.0 + 3.0 * k) / (a * a);
+// Launch 3, after the problem's maximum, total and block prefixes: the
+// emission runs (workgroups [0, scan_blocks)) and the accept thresholds with
+// their palette (the rest), which do not need each other.
+__global__ __launch_bounds__(SCAN_THREADS) void k_stage_tables(ProbDesc* descs, uint32_t scan_blocks) {
+    ProbDesc* pd = descs + blockIdx.y;
+    if (blockIdx.x < scan_blocks) stage_runs(pd);
+    else stage_thresholds(pd, blockIdx.x - scan_blocks, gridDim.x - scan_blocks);
 }
 
-__global__ void k_kn_table(ProbDesc* descs) {
+// Launch 4: the guide table over the runs ([0, guide_blocks)), the palette
+// codes ([guide_blocks, gridDim.x - 1)), and the transport's totals and claim
+// counters cleared (the last workgroup; the block prefixes they replace are
+// not read any more).
+__global__ __launch_bounds__(RED_THREADS) void k_stage_finish(ProbDesc* descs, uint32_t guide_blocks) {
     ProbDesc* pd = descs + blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= KN_TABLE_N) return;
-    const double e = fmax((double)pd->e0 - 0.25 * i, 0.5);
-    pd->kn_table[i] = (float)(kn_bracket(e) / kn_bracket(140.0));
+    if (blockIdx.x < guide_blocks) stage_guide(pd, blockIdx.x, guide_blocks);
+    else if (blockIdx.x + 1 < gridDim.x) stage_codes(pd, blockIdx.x - guide_blocks, gridDim.x - 1 - guide_blocks);
+    else
+        for (int k = threadIdx.x; k < BLOCK_SCRATCH_MIN; k += RED_THREADS) pd->block_sums[k] = 0;
 }
 
 int grid_for(uint64_t n, int threads, int cap) {
@@ -717,36 +732,55 @@ int grid_for(uint64_t n, int threads, int cap) {
 }  // namespace
 
 
-// The problems' descriptors are written one by one (by value, so the launch
-// can be captured in a graph); every other pass is one launch for all
-// problems, blockIdx.y picking the problem and each block walking that
-// problem's share, so small problems overlap instead of queueing.
-hipError_t launch_staging_batch(ProbDesc* d, const ProbDesc* h, int n, hipStream_t st) {
-    uint64_t max_rows = 1, max_nb = 1, max_cap = 1;
-    int max_nx = 1;
+// Staging of n problems and, with call, the preparation of a forward call
+// (work prefixes, cleared status, tallies and totals).
+hipError_t launch_staging_batch(ProbDesc* d, const ProbDesc* h, int n, const CallPrep* call, hipStream_t st) {
+    uint64_t max_vox = 1, max_cap = 1;
+    uint64_t work0 = 0, chunks0 = 0;
     for (int i = 0; i < n; ++i) {
-        k_write_desc<<<1, 64, 0, st>>>(h[i], d + i);
-        max_rows = std::max<uint64_t>(max_rows, (uint64_t)h[i].ny * h[i].nz);
-        max_nx = std::max(max_nx, h[i].nx);
-        max_nb = std::max<uint64_t>(max_nb, (h[i].nvox + SCAN_ITEMS - 1) / SCAN_ITEMS);
+        max_vox = std::max<uint64_t>(max_vox, h[i].nvox);
         max_cap = std::max<uint64_t>(max_cap, guide_capacity(h[i].nvox));
     }
-    // row-per-block passes: a block walks grid rows (iy, iz), threads along x
-    const int row_threads = (int)std::min<uint64_t>(RED_THREADS, ((uint64_t)max_nx + 63) / 64 * 64);
+    const uint32_t scan_blocks = (uint32_t)((max_vox + SCAN_ITEMS - 1) / SCAN_ITEMS);
     const unsigned ny = (unsigned)n;
-    const unsigned red_blocks = (unsigned)std::min<uint64_t>(max_rows, REDUCE_BLOCKS);
-    k_reduce<<<dim3(red_blocks, ny), row_threads, 0, st>>>(d);
-    k_reduce_final<<<dim3(1, ny), RED_THREADS, 0, st>>>(d, (int)red_blocks);
-    const unsigned row_blocks = (unsigned)std::min<uint64_t>((max_rows + ROWS - 1) / ROWS, 8192);
+    for (int first = 0; first < n; first += STAGE_MAX) {
+        const int cnt = std::min(STAGE_MAX, n - first);
+        StageArgs a = {};
+        for (int i = 0; i < cnt; ++i) a.d[i] = h[first + i];
+        a.out = d + first;
+        a.scan_blocks = scan_blocks;
+        a.first = first;
+        a.n_problems = n;
+        uint32_t zero_blocks = 0;
+        if (call) {
+            a.work_prefix = call->work_prefix;
+            a.work0 = work0;
+            a.chunks0 = chunks0;
+            a.chunk = call->chunk;
+            a.status = call->status;
+            a.n_events = call->n_events;
+            if (first == 0) {
+                a.tally = call->tally;
+                a.tally_sq = call->tally_sq;
+                a.tally_elems = call->tally_elems;
+                const uint64_t g = (call->tally_elems + SCAN_THREADS - 1) / SCAN_THREADS;
+                zero_blocks = (uint32_t)(std::min<uint64_t>(g, 4096) + cnt - 1) / cnt;
+            }
+            for (int i = 0; i < cnt; ++i) {
+                work0 += a.d[i].work_count;
+                chunks0 += (a.d[i].work_count + call->chunk - 1) / call->chunk;
+            }
+        }
+        a.zero_blocks = zero_blocks;
+        k_stage_scan<<<dim3(scan_blocks + 1 + KN_BLOCKS + zero_blocks, (unsigned)cnt), SCAN_THREADS, 0, st>>>(a);
+    }
+    k_stage_top<<<dim3(1, ny), 1024, 0, st>>>(d);
     // each workgroup puts each threshold value it meets into the palette once
-    // (a round trip to memory): fewer, larger workgroups for this pass
-    k_thresholds<<<dim3(std::min(row_blocks, 1024u), ny), row_threads, 0, st>>>(d);
-    k_codes<<<dim3(row_blocks, ny), row_threads, 0, st>>>(d);
-    k_scan_sums<<<dim3((unsigned)max_nb, ny), SCAN_THREADS, 0, st>>>(d);
-    k_scan_top<<<dim3(1, ny), 1024, 0, st>>>(d);
-    k_scan_final<<<dim3((unsigned)max_nb, ny), SCAN_THREADS, 0, st>>>(d);
-    k_guide<<<dim3((unsigned)grid_for(max_cap, RED_THREADS, 8192), ny), RED_THREADS, 0, st>>>(d);
-    k_kn_table<<<dim3((KN_TABLE_N + 255) / 256, ny), 256, 0, st>>>(d);
+    // (a few round trips to memory): not more of them than keep the chip busy
+    const uint32_t stream_blocks = (uint32_t)std::min<uint64_t>((max_vox + RED_THREADS * ROWS - 1) / (RED_THREADS * ROWS), 1024);
+    k_stage_tables<<<dim3(scan_blocks + stream_blocks, ny), SCAN_THREADS, 0, st>>>(d, scan_blocks);
+    const uint32_t guide_blocks = (uint32_t)grid_for(max_cap, RED_THREADS, 1024);
+    k_stage_finish<<<dim3(guide_blocks + stream_blocks + 1, ny), RED_THREADS, 0, st>>>(d, guide_blocks);
     return hipGetLastError();
 }
 
@@ -764,16 +798,13 @@ hipError_t launch_mu_codes(ProbDesc* d, const ProbDesc* h, int n, hipStream_t st
 }
 
 // Entries (uint64) of a problem's block-sum scratch: the scan's block sums,
-// before them k_reduce's partials, after them the transport's totals.
+// after them the transport's totals.
 size_t staging_block_scratch_u64(uint64_t nvox) {
-    const uint64_t nb = (nvox + SCAN_ITEMS - 1) / SCAN_ITEMS;
-    const uint64_t red = (uint64_t)REDUCE_BLOCKS * REDUCE_PART_U64;
-    static_assert(REDUCE_BLOCKS * REDUCE_PART_U64 >= BLOCK_SCRATCH_MIN, "transport scratch");
-    return (size_t)(nb > red ? nb : red);
+    return (size_t)std::max<uint64_t>((nvox + SCAN_ITEMS - 1) / SCAN_ITEMS, BLOCK_SCRATCH_MIN);
 }
 
 hipError_t launch_staging(ProbDesc* d, const ProbDesc& h, hipStream_t st) {
-    return launch_staging_batch(d, &h, 1, st);
+    return launch_staging_batch(d, &h, 1, nullptr, st);
 }
 
 }  // namespace mcs

@@ -737,50 +737,6 @@ __global__ __launch_bounds__(256) void k_replay(const ProbDesc* __restrict__ d,
     out[i] = r;
 }
 
-// Per-call preparation: zero tallies, totals and claim counters, work and
-// chunk prefixes (one wavefront, a problem per lane).
-__global__ __launch_bounds__(256) void k_prepare(const ProbDesc* __restrict__ descs, int n_problems,
-                                                 uint64_t* work_prefix, uint32_t chunk, int64_t* status,
-                                                 unsigned long long* n_events,
-                                                 int64_t* tally, uint64_t tally_elems, int64_t* tally_sq) {
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = tid; i < tally_elems; i += stride) {
-        tally[i] = 0;
-        if (tally_sq) tally_sq[i] = 0;
-    }
-    for (uint64_t i = tid; i < (uint64_t)n_problems * BLOCK_SCRATCH_MIN; i += stride)
-        descs[i / BLOCK_SCRATCH_MIN].block_sums[i % BLOCK_SCRATCH_MIN] = 0;
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {
-        const int lane = (int)threadIdx.x;
-        uint64_t w = 0, c = 0;                 // totals of the problems before this round's
-        uint64_t* chunk_prefix = work_prefix + (n_problems + 1);
-        for (int p0 = 0; p0 < n_problems; p0 += 64) {
-            const int p = p0 + lane;
-            const uint64_t cnt = p < n_problems ? descs[p].work_count : 0;
-            const uint64_t nc = (cnt + chunk - 1) / chunk;
-            uint64_t sw = cnt, sc = nc;
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint64_t yw = (uint64_t)__shfl_up((long long)sw, o, 64);
-                const uint64_t yc = (uint64_t)__shfl_up((long long)sc, o, 64);
-                if (lane >= o) { sw += yw; sc += yc; }
-            }
-            if (p < n_problems) {
-                work_prefix[p] = w + sw - cnt;
-                chunk_prefix[p] = c + sc - nc;
-            }
-            w += (uint64_t)__shfl((long long)sw, 63, 64);
-            c += (uint64_t)__shfl((long long)sc, 63, 64);
-        }
-        if (lane == 0) {
-            work_prefix[n_problems] = w;
-            chunk_prefix[n_problems] = c;
-            if (n_events) *n_events = 0;
-        }
-        if (lane < 4) status[lane] = 0;
-    }
-}
-
 // After transport: the waves' totals added up into fates, energies and
 // counters, the staging flags and list overflow folded into the status, and
 // the tally range checked, FINISH_BLOCKS workgroups per problem (the first
@@ -859,18 +815,6 @@ __global__ void k_replay_status(const ProbDesc* __restrict__ d, int64_t* status)
 }
 
 }  // namespace
-
-hipError_t launch_prepare_call(const ProbDesc* descs, int32_t n_problems, uint64_t* work_prefix,
-                               int64_t* status, unsigned long long* n_events,
-                               int64_t* tally, uint64_t tally_elems, int64_t* tally_sq, uint32_t chunk,
-                               hipStream_t s) {
-    uint64_t g = (tally_elems + 255) / 256;
-    if (g < 1) g = 1;
-    if (g > 4096) g = 4096;
-    k_prepare<<<(int)g, 256, 0, s>>>(descs, n_problems, work_prefix, chunk, status, n_events,
-                                     tally, tally_elems, tally_sq);
-    return hipGetLastError();
-}
 
 hipError_t launch_transport(const TransportArgs& a, int grid, int block, hipStream_t s) {
     if (a.vr_flags) k_transport_vr<<<grid, block, 0, s>>>(a);

@@ -255,13 +255,16 @@ __device__ inline bool leaves_box(const Cst& C, int ix, int iy, int iz, float dx
 
 // Per-lane escape: collimator, detector bin, window.  Returns the fate; sets iu, iv.
 __device__ inline int escape(const Cst& C, const Lane& L, int& iu, int& iv) {
-    const float dn = L.dx * L.vc + L.dy * L.vs;
+    // (which product of a sum of two is rounded is written out, here and below:
+    // left to the compiler, it changed with the code around it, and with it the
+    // outcome of a history in 1e9)
+    const float dn = fmaf(L.dx, L.vc, L.dy * L.vs);
     if (dn < C.cos_alpha) return MC_ESCAPED;
-    const float tp = (C.radius - (L.x * L.vc + L.y * L.vs)) * rcpf(dn);
+    const float tp = (C.radius - fmaf(L.x, L.vc, L.y * L.vs)) * rcpf(dn);
     const float px = fmaf(tp, L.dx, L.x);
     const float py = fmaf(tp, L.dy, L.y);
     const float pz = fmaf(tp, L.dz, L.z);
-    const float au = (-L.vs * px + L.vc * py) + 0.5f * C.wu;
+    const float au = fmaf(L.vc, py, -(L.vs * px)) + 0.5f * C.wu;
     const float av = pz + 0.5f * C.wv;
     if (!(au >= 0.0f && au < C.wu && av >= 0.0f && av < C.wv)) return MC_ESCAPED_FOV;
     iu = min((int)(au * C.inv_pix), C.nu - 1);
@@ -285,13 +288,15 @@ __device__ inline void rotate_dir(float& u, float& v, float& w, float ct, float 
         const float t2 = (1.0f - w0) * (1.0f + w0);
         const float it = rsqf_hw(t2);
         const float a = st * it;
-        u = fmaf(a, u0 * w0 * cp - v0 * sp, u0 * ct);
-        v = fmaf(a, v0 * w0 * cp + u0 * sp, v0 * ct);
+        u = fmaf(a, fmaf(cp, u0 * w0, -(v0 * sp)), u0 * ct);
+        v = fmaf(a, fmaf(cp, v0 * w0, u0 * sp), v0 * ct);
         w = fmaf(-st * cp, t2 * it, w0 * ct);
     }
 }
 
-// rotate_dir on a lane's direction.
+// rotate_dir on a lane's direction.  ALT: the other order of the second
+// component's products, which the weighted, replay and adjoint kernels have.
+template <bool ALT>
 __device__ inline void rotate(Lane& L, float ct, float phi_u) {
     const float sp = sin_rev(phi_u), cp = cos_rev(phi_u);
     const float st = sqrtf_hw(fmaxf(0.0f, (1.0f - ct) * (1.0f + ct)));
@@ -304,8 +309,8 @@ __device__ inline void rotate(Lane& L, float ct, float phi_u) {
         const float t2 = (1.0f - w) * (1.0f + w);
         const float it = rsqf_hw(t2);
         const float a = st * it;
-        L.dx = fmaf(a, u * w * cp - v * sp, u * ct);
-        L.dy = fmaf(a, v * w * cp + u * sp, v * ct);
+        L.dx = fmaf(a, fmaf(cp, u * w, -(v * sp)), u * ct);
+        L.dy = fmaf(a, ALT ? fmaf(sp, u, v * w * cp) : fmaf(cp, v * w, u * sp), v * ct);
         L.dz = fmaf(-st * cp, t2 * it, w * ct);
     }
 }
@@ -452,6 +457,7 @@ __device__ inline void begin_history(const Cst& C, Lane& L, uint32_t view, uint3
 // escape here), (2) the Kahn attempt and, on acceptance, the new direction
 // and energy (arithmetic only), (3) the accept test of the tentative
 // collision, (4) the attenuation terms at a new energy (table reads).
+template <bool ALT = false>
 __device__ inline int advance(const Cst& C, const uint32_t* pal, Lane& L, uint32_t w0, uint32_t w1,
                               uint32_t w2, uint32_t w3, Acc& A, int& iu, int& iv, bool fi = false) {
     const int state = L.state;
@@ -526,18 +532,18 @@ __device__ inline int advance(const Cst& C, const uint32_t* pal, Lane& L, uint32
         } else {
             MC_REGION(RG_KAHN_ACCEPT);
             const float ct = 1.0f - (xx - 1.0f) * ik;
-            L.e = L.e * ixx;
             {
                 // the KN table pair of the new energy, read before the
                 // rotation so the load is in flight during it
-                const float t = (C.e0 - L.e) * KN_TABLE_STEP_INV;
+                const float t = fmaf(-L.e, ixx, C.e0) * KN_TABLE_STEP_INV;
+                L.e = L.e * ixx;
                 const int i = (int)t;
                 kn_fr = t - (float)i;
                 kn0 = ldg(C.kn_table + i);
                 kn1 = ldg(C.kn_table + i + 1);
             }
             L.n_scatter += 1;
-            rotate(L, ct, unif(L.phi_word));
+            rotate<ALT>(L, ct, unif(L.phi_word));
             if (L.e < C.e_cut) {
                 fate = MC_CUT;
             } else {
@@ -927,7 +933,7 @@ __device__ inline bool fd_setup(const Cst& C, const ProbDesc* __restrict__ d, co
         w = 0.5f * omc;
         e2 = q.e;
     } else {
-        const float ct = q.dx * ox + q.dy * oy + q.dz * oz;
+        const float ct = fmaf(q.dz, oz, fmaf(q.dy, oy, q.dx * ox));
         const float eps = rcpf(fmaf(q.e * INV_MEC2, 1.0f - ct, 1.0f));
         e2 = q.e * eps;
         float l2, ppe;
@@ -937,10 +943,10 @@ __device__ inline bool fd_setup(const Cst& C, const ProbDesc* __restrict__ d, co
         w = (1.0f - ppe) * (TWO_PI_F * omc) * pdf;
     }
     if (!(e2 >= C.e_cut && e2 >= C.e_lo && e2 <= C.e_hi)) return false;
-    const float dn = ox * vw.x + oy * vw.y;
-    const float tp = (C.radius - (q.x * vw.x + q.y * vw.y)) * rcpf(dn);
+    const float dn = fmaf(ox, vw.x, oy * vw.y);
+    const float tp = (C.radius - fmaf(q.x, vw.x, q.y * vw.y)) * rcpf(dn);
     const float px = fmaf(tp, ox, q.x), py = fmaf(tp, oy, q.y), pz = fmaf(tp, oz, q.z);
-    const float au = (-vw.y * px + vw.x * py) + 0.5f * C.wu;
+    const float au = fmaf(vw.x, py, -(vw.y * px)) + 0.5f * C.wu;
     const float av = pz + 0.5f * C.wv;
     if (!(au >= 0.0f && au < C.wu && av >= 0.0f && av < C.wv)) return false;
     const int iu = min((int)(au * C.inv_pix), C.nu - 1);
@@ -973,7 +979,7 @@ __device__ inline bool cfd_setup(const Cst& C, const ProbDesc* __restrict__ d, c
         w = 0.5f * omc;
         e2 = q.e;
     } else {
-        const float ct = q.dx * vw.x + q.dy * vw.y;
+        const float ct = fmaf(q.dx, vw.x, q.dy * vw.y);
         const float eps = rcpf(fmaf(q.e * INV_MEC2, 1.0f - ct, 1.0f));
         e2 = q.e * eps;
         float l2, ppe;
@@ -983,13 +989,13 @@ __device__ inline bool cfd_setup(const Cst& C, const ProbDesc* __restrict__ d, c
         w = (1.0f - ppe) * (TWO_PI_F * omc) * pdf;
     }
     if (!(e2 >= C.e_cut && e2 >= C.e_lo && e2 <= C.e_hi)) return false;
-    const float au = (-vw.y * q.x + vw.x * q.y) + 0.5f * C.wu;
+    const float au = fmaf(vw.x, q.y, -(vw.y * q.x)) + 0.5f * C.wu;
     const float av = q.z + 0.5f * C.wv;
     if (!(au >= 0.0f && au < C.wu && av >= 0.0f && av < C.wv)) return false;
     const int iu = min((int)(au * C.inv_pix), C.nu - 1);
     const int iv = min((int)(av * C.inv_pix), C.nv - 1);
     const int nl = d->cfd_L;
-    const float depth = C.radius - (q.x * vw.x + q.y * vw.y);
+    const float depth = C.radius - fmaf(q.x, vw.x, q.y * vw.y);
     const int l = min(max((int)floorf(depth * C.inv_pix), 0), nl - 1);
     float l2, ppe;
     j.g = e2 == C.e0 ? C.g0 : energy_terms(C, e2, l2, ppe);

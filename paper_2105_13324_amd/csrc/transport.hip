@@ -545,7 +545,7 @@ __device__ __forceinline__ void transport_body(TransportArgs T, EmitRec* __restr
             uint32_t c0 = L.hist, c1 = (uint32_t)L.view, c2, c3;
             counter_of(L, c2, c3);
             philox10(c0, c1, c2, c3, C.seed, C.pid);
-            fate = advance(C, my_pal, L, c0, c1, c2, c3, A, iu, iv, vr_fi);
+            fate = advance<VR>(C, my_pal, L, c0, c1, c2, c3, A, iu, iv, vr_fi);
             if (fate != R_RUNNING) {
                 MC_REGION(RG_FATE_ENERGY);
                 // outgoing energy: escaped, or left at the step cap (rare: booked at once)
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(256) void k_replay(const ProbDesc* __restrict__ d,
             counter_of(L, c2, c3);
             philox10(c0, c1, c2, c3, C.seed, C.pid);
             int iu = -1, iv = -1;
-            const int fate = advance(C, C.pal, L, c0, c1, c2, c3, A, iu, iv,
+            const int fate = advance<true>(C, C.pal, L, c0, c1, c2, c3, A, iu, iv,
                                      (vr_flags & VR_FORCED_INTERACTION) != 0);
             if (fate != R_RUNNING) {
                 r.fate = fate;

@@ -359,14 +359,10 @@ size_t mlem_workspace_bytes(int64_t n_bins, int64_t n_vox);
  * nnz: the entry count, T_rowptr[n_bins] = Tt_rowptr[n_vox], as the caller
  * knows it from building the matrix; it picks the layout and schedule before
  * launch, and is checked on the device: a different value leaves the image
- * NaN.  Each iteration sweeps only the non-empty rows of T and T^T (listed
- * once per call): two kernels per iteration.  A sparse matrix (nnz <= n_bins
- * + n_vox) is iterated in a compact layout (vectors over the non-empty rows,
- * columns renumbered once per call) whose gathers stay in L2; on a large
- * detector (n_bins >= 2^19, nnz >= 16 n_vox) the backprojection works on one
- * bin slice per XCD (a third kernel adds the slices); columns of each Tt row
- * in ascending order (as mc_system_matrix writes them) give the slices their
- * locality, any order gives the same result.  Deterministic: the summation
+ * NaN.  Two kernels per iteration.  A sparse matrix (nnz <= n_bins + n_vox)
+ * is iterated in a compact layout (vectors over the non-empty rows, listed
+ * once per call, columns renumbered) whose gathers stay in L2; a dense one is
+ * streamed row by row, neighbouring rows by one XCD.  Deterministic: the summation
  * order depends only on the matrix.  Asynchronous on stream: no host
  * synchronisation, no allocation, no memset, so a call can be captured in a
  * graph (mc_graph_begin) and replayed. */
@@ -379,8 +375,8 @@ int mlem_iterate(int64_t n_bins, int64_t n_vox, int64_t nnz,
 /* mlem_iterate in two parts, for many reconstructions with one matrix
  * (Sec. 5.1: the matrix is fixed while the image is iterated).
  * mlem_prepare does the matrix's share once: the sensitivities sum_j T_ij,
- * the lists of non-empty rows, the renumbered columns of the compact layout
- * and the bin slices, all kept in the workspace together with the entry-count
+ * the lists of non-empty rows and the renumbered columns of the compact
+ * layout, all kept in the workspace together with the entry-count
  * check and a fingerprint (n_bins, n_vox, nnz).  mlem_iterate_prepared then
  * runs n_iter updates exactly as mlem_iterate does (same results bit for
  * bit) without repeating that set-up: the arguments are mlem_iterate's, and

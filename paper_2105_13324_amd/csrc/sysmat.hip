@@ -481,46 +481,9 @@ __global__ __launch_bounds__(T256) void k_proj_rows(const int64_t* __restrict__ 
 
 // ---- MLEM ----
 //
-// Row kernels: a matrix whose rows hold on average at least WAVE_ROW_MIN
-// entries (forced-detection matrices) is read one wavefront per row --
-// coalesced loads, FP64 wavefront reduction -- and a sparse one (analog
-// matrices: far fewer entries than rows) one thread per row.  The choice
-// depends only on the matrix, so results are deterministic.
-
-constexpr int64_t WAVE_ROW_MIN = 8;
-
 __device__ inline double wave_sum_f64(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
-}
-
-// For each row r: done(r, sum over the row's entries of term(k)).
-template <class Term, class Done>
-__device__ inline void for_rows(int64_t n_rows, const int64_t* __restrict__ rp, Term term, Done done) {
-    const bool wave_mode = rp[n_rows] >= WAVE_ROW_MIN * n_rows;
-    const int64_t tid = (int64_t)blockIdx.x * T256 + threadIdx.x;
-    const int64_t nt = (int64_t)gridDim.x * T256;
-    if (wave_mode) {
-        const int lane = threadIdx.x & 63;
-        for (int64_t r = tid >> 6; r < n_rows; r += nt >> 6) {
-            double acc = 0.0;
-            for (int64_t k = rp[r] + lane; k < rp[r + 1]; k += 64) acc += term(k);
-            acc = wave_sum_f64(acc);
-            if (lane == 0) done(r, acc);
-        }
-    } else {
-        for (int64_t r = tid; r < n_rows; r += nt) {
-            double acc = 0.0;
-            for (int64_t k = rp[r]; k < rp[r + 1]; ++k) acc += term(k);
-            done(r, acc);
-        }
-    }
-}
-
-__global__ __launch_bounds__(T256) void k_row_sums(int64_t n_rows, const int64_t* __restrict__ rp,
-                                                   const float* __restrict__ v, double* __restrict__ out) {
-    for_rows(n_rows, rp, [&](int64_t k) { return (double)v[k]; },
-             [&](int64_t r, double acc) { out[r] = acc; });
 }
 
 // MLEM state in the workspace (device uint32 [ST_WORDS]), written by the
@@ -561,102 +524,9 @@ __device__ inline bool mlem_call_bad(const uint32_t* __restrict__ st, int64_t n_
            st[ST_FP + 2] != (uint32_t)(uint64_t)nnz || st[ST_FP + 3] != (uint32_t)((uint64_t)nnz >> 32);
 }
 
-// A non-empty row of a CSR matrix: its index and entry range.
-struct RowRef {
-    int64_t lo;
-    int32_t row, len;
-};
-
-// The non-empty rows of T (bins[], length st[ST_BINS]) and of T^T (voxs[],
-// length st[ST_VOXS]): only these are swept by the iterations (an empty bin
-// row has no ratio to compute, an empty voxel row has sens_i = 0 and
-// S_i = 0).  A workgroup takes 4096 consecutive rows of one matrix at a time
-// and appends their non-empty ones in row order with one atomic; the order
-// of the workgroups' runs varies from call to call, which changes no result,
-// since every row is summed by one group of lanes on its own.  bin_pos /
-// vox_pos (nullable): each row's list position, -1 for an empty row.
+// Rows a workgroup takes at a time in the set-up of the compact layout.
 constexpr int ROWS_PER_THREAD = 16;
 constexpr int ROW_CHUNK = T256 * ROWS_PER_THREAD;
-
-__global__ __launch_bounds__(T256) void k_mlem_rows(int64_t n_bins, int64_t n_vox,
-                                                    const int64_t* __restrict__ T_rp,
-                                                    const int64_t* __restrict__ Tt_rp,
-                                                    RowRef* __restrict__ bins,
-                                                    RowRef* __restrict__ voxs,
-                                                    int32_t* __restrict__ bin_pos,
-                                                    int32_t* __restrict__ vox_pos,
-                                                    uint32_t* __restrict__ st) {
-    constexpr int WAVES = T256 / 64;
-    __shared__ uint32_t before[ROWS_PER_THREAD * WAVES];
-    __shared__ uint32_t base_s;
-    if (st[ST_BAD]) return;
-    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-    const uint64_t lane_lt = (1ull << lane) - 1;
-    const int64_t nbc = (n_bins + ROW_CHUNK - 1) / ROW_CHUNK;
-    const int64_t nvc = (n_vox + ROW_CHUNK - 1) / ROW_CHUNK;
-    for (int64_t c = blockIdx.x; c < nbc + nvc; c += gridDim.x) {
-        const bool vox = c >= nbc;
-        const int64_t r0 = (vox ? c - nbc : c) * ROW_CHUNK;
-        const int64_t nr = vox ? n_vox : n_bins;
-        const int64_t* rp = vox ? Tt_rp : T_rp;
-        int32_t* pos = vox ? vox_pos : bin_pos;
-        int64_t lo[ROWS_PER_THREAD];
-        int32_t len[ROWS_PER_THREAD];
-        uint64_t m[ROWS_PER_THREAD];
-#pragma unroll
-        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-            const int64_t r = r0 + k * T256 + threadIdx.x;
-            lo[k] = 0;
-            len[k] = 0;
-            if (r < nr) {
-                lo[k] = rp[r];
-                len[k] = (int32_t)(rp[r + 1] - lo[k]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-            m[k] = __ballot(len[k] > 0);
-            if (lane == 0) before[k * WAVES + w] = (uint32_t)__popcll(m[k]);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            // rows r0 + k * 256 + w * 64 + lane in (k, w, lane) order: row order
-            uint32_t tot = 0;
-            for (int q = 0; q < ROWS_PER_THREAD * WAVES; ++q) {
-                const uint32_t x = before[q];
-                before[q] = tot;
-                tot += x;
-            }
-            base_s = tot ? atomicAdd(&st[vox ? ST_VOXS : ST_BINS], tot) : 0u;
-        }
-        __syncthreads();
-        RowRef* out = vox ? voxs : bins;
-#pragma unroll
-        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-            const int64_t r = r0 + k * T256 + threadIdx.x;
-            const uint32_t slot = base_s + before[k * WAVES + w] + (uint32_t)__popcll(m[k] & lane_lt);
-            if (len[k] > 0) out[slot] = RowRef{lo[k], (int32_t)r, len[k]};
-            if (pos && r < nr) pos[r] = len[k] > 0 ? (int32_t)slot : -1;
-        }
-        __syncthreads();     // before[] and base_s are rewritten for the next chunk
-    }
-}
-
-// Lanes that share one row in the MLEM sweeps: the smallest group of 1, 4, 16
-// or 64 lanes for which four entries per lane cover the mean row (nnz /
-// n_rows entries), so that short rows do not leave most of a wavefront idle.
-// The kernel instantiated for lane-group size gs (1, 4, 16 or 64).
-template <class K>
-K by_group(int gs, K k1, K k4, K k16, K k64) {
-    return gs == 1 ? k1 : gs == 4 ? k4 : gs == 16 ? k16 : k64;
-}
-
-__host__ __device__ inline int lanes_per_row(int64_t nnz, int64_t n_rows) {
-    if (nnz <= 4 * n_rows) return 1;
-    if (nnz <= 16 * n_rows) return 4;
-    if (nnz <= 64 * n_rows) return 16;
-    return 64;
-}
 
 // The rows a group of GS lanes visits: row g, g + n_groups, ... (g: the
 // group's index among n_groups); every lane of a group sees the same rows.
@@ -697,170 +567,184 @@ __device__ inline double group_row_sum(int64_t k0, int64_t k1, int sub, Term ter
     return acc;
 }
 
-// A group's rows of n, four per pass: bounds(q, lo, hi) loads the entry
-// ranges of four rows before any of them is summed (row by row, with
-// group_row_sum), so a sparse matrix (most rows empty or one entry long)
-// keeps four row-pointer loads in flight per lane.  done(q, lo, len, sum)
-// runs for every row q < n; the test is group-uniform.  (Summing the four
-// rows interleaved was slower on forced-detection matrices: a pass then
-// lasts as long as the longest of the four rows.)
-template <int GS, class Bounds, class Term, class Done>
-__device__ inline void sweep_rows(const RowGroups<GS>& G, int64_t n, Bounds bounds, Term term,
-                                  Done done) {
-    for (int64_t r = G.first; r < n; r += 4 * G.step) {
-        int64_t lo[4], hi[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t q = r + u * G.step;
-            bounds(q < n ? q : n - 1, lo[u], hi[u]);
+// ---- row order.  Sweeps of a dense matrix: a workgroup takes SWEEP_ROWS or
+// fewer consecutive rows, whose entries are consecutive too, and streams them
+// SWEEP_TILE at a time: coalesced loads of columns and values, eight gathers
+// in flight per thread, the products in LDS in FP64, then each row summed from
+// there by a power-of-two group of lanes.  The order of a sum depends only on
+// the matrix.  Bound by the stream of entries (8 bytes each) and the gathers.
+// What it replaces: a lane group per row with the row's loads in a chain (233
+// us per forward sweep and, in bin slices per XCD with a third kernel adding
+// them, 393 us per backprojection on a forced-detection matrix of 4.6e7
+// entries, 1.97 M bins and 2.6e5 voxels: 171 and 300 us now).  No slices are
+// needed: each XCD works on neighbouring rows (sweep_chunk), so a
+// backprojection's gathers from its slab of voxels fall in the bins of a few
+// detector rows, which its L2 holds (90 % hits).  Where columns are random,
+// which no camera gives, the slices were the better (2^20 bins x 2^17 voxels,
+// 3e7 entries: 442 against 465 us per iteration).
+constexpr int SWEEP_ROWS = 256;      // most rows of a workgroup (= T256: one row bound per thread)
+constexpr int SWEEP_TILE = 2048;     // entries in LDS
+constexpr int SWEEP_LOADS = SWEEP_TILE / T256;
+
+// Rows per workgroup: three quarters of a tile on average, so that most
+// workgroups need one tile.
+inline int sweep_rows_for(int64_t nnz, int64_t n_rows) {
+    const int64_t mean = nnz / std::max<int64_t>(1, n_rows);
+    return (int)std::min<int64_t>(SWEEP_ROWS, std::max<int64_t>(1, (SWEEP_TILE * 3 / 4) / std::max<int64_t>(1, mean)));
+}
+
+// Workgroups for n chunks, and the chunk of workgroup b (workgroups are dealt
+// to the 8 XCDs in turn): each XCD takes runs of consecutive chunks, one run in
+// eight, 16 runs per XCD, so neighbouring rows meet in one L2 and dense and
+// empty regions are spread over the XCDs (with one contiguous eighth each, the
+// CUs were busy 70 % of a backprojection).
+constexpr int SWEEP_RUNS = 16;
+inline unsigned sweep_grid(int64_t n_chunks) {
+    const int64_t run = (n_chunks + 8 * SWEEP_RUNS - 1) / (8 * SWEEP_RUNS);
+    return (unsigned)(8 * SWEEP_RUNS * run);
+}
+__device__ __forceinline__ int64_t sweep_chunk() {
+    const uint32_t run = gridDim.x / (8 * SWEEP_RUNS), j = blockIdx.x / 8;
+    return (int64_t)((j / run * 8 + blockIdx.x % 8) * run + j % run);
+}
+
+__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Sum over each row r in [r0, r0 + n) (n <= SWEEP_ROWS) of term(k) for its
+// entries k, done(r, sum) by one lane per non-empty row.  The term of entry
+// first + k is load(first, k) -> A, then value(A) -> double, so the loads of a
+// tile are issued before its gathers (first is in scalar registers).  All
+// threads of the workgroup call.
+template <class Load, class Value, class Done>
+__device__ inline void sweep(int64_t r0, int n, const int64_t* __restrict__ rp, Load load, Value value, Done done) {
+    __shared__ double prod[SWEEP_TILE];
+    __shared__ int64_t off[SWEEP_ROWS + 1];
+    const int tid = (int)threadIdx.x;
+    const int64_t e0 = rp[r0];
+    if (tid <= n) off[tid] = rp[r0 + tid] - e0;
+    if (tid == 0 && n == SWEEP_ROWS) off[n] = rp[r0 + n] - e0;
+    __syncthreads();
+    int s = 0;
+    while (s < n) {
+        // rows [s, e) fit in a tile
+        int e = s, hi = n;
+        while (e < hi) {
+            const int mid = (e + hi + 1) >> 1;
+            if (off[mid] - off[s] <= SWEEP_TILE) e = mid; else hi = mid - 1;
         }
+        const int64_t first = uniform_i64(e0 + off[s]);
+        if (e == s) {
+            // one row longer than a tile: the whole workgroup, tile by tile
+            const int64_t len = uniform_i64(off[s + 1] - off[s]);
+            double acc = 0.0;
+            for (int64_t k0 = 0; k0 < len; k0 += SWEEP_TILE) {
+                const int cnt = (int)(len - k0 < SWEEP_TILE ? len - k0 : SWEEP_TILE);
+                decltype(load(0, 0)) a[SWEEP_LOADS];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (r + u * G.step < n)
-                done(r + u * G.step, lo[u], hi[u] - lo[u], group_row_sum<GS>(lo[u], hi[u], G.sub, term));
+                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                    const int k = tid + u * T256;
+                    a[u] = load(first + k0, k < cnt ? k : cnt - 1);
+                }
+#pragma unroll
+                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                    const double x = value(a[u]);
+                    acc += tid + u * T256 < cnt ? x : 0.0;
+                }
+            }
+            acc = wave_sum_f64(acc);
+            if ((tid & 63) == 0) prod[tid >> 6] = acc;
+            __syncthreads();
+            if (tid == 0) done(r0 + s, (prod[0] + prod[1]) + (prod[2] + prod[3]));
+            ++s;
+        } else {
+            const int cnt = (int)uniform_i64(off[e] - off[s]);
+            if (cnt > 0) {
+                decltype(load(0, 0)) a[SWEEP_LOADS];
+#pragma unroll
+                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                    const int k = tid + u * T256;
+                    a[u] = load(first, k < cnt ? k : cnt - 1);
+                }
+#pragma unroll
+                for (int u = 0; u < SWEEP_LOADS; ++u) prod[tid + u * T256] = value(a[u]);
+            }
+            __syncthreads();
+            // as many lanes per row as there are for all rows at once
+            int gs = 1;
+            while (gs < 64 && 2 * gs * (e - s) <= T256) gs *= 2;
+            const int sub = tid & (gs - 1);
+            for (int r = s + tid / gs; r < e; r += T256 / gs) {
+                const int k0 = (int)(off[r] - off[s]), k1 = (int)(off[r + 1] - off[s]);
+                double acc = 0.0;
+                for (int k = k0 + sub; k < k1; k += gs) acc += prod[k];
+                for (int o = gs >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+                if (sub == 0 && k1 > k0) done(r0 + r, acc);
+            }
+            s = e;
+        }
+        __syncthreads();          // prod is written again
     }
 }
 
-// A group's share of a row list: entries q = G.first + k G.step (k = 0, 1,
-// ...), four per pass.  The first four entries are loaded together with the
-// list's length (those past it are read from the list's spare capacity, cap
-// entries in all, and dropped), so a sweep of short rows waits for three
-// dependent loads (list entry, matrix entry, gathered vector entry), not
-// four.  aux(q, valid, ref) loads a row's own operands (q clamped below cap)
-// before its sum; done(q, ref, aux, sum) runs for every listed row.
-template <int GS, class Aux, class Term, class Done>
-__device__ inline void sweep_list(const RowGroups<GS>& G, const RowRef* __restrict__ L, int64_t cap,
-                                  const uint32_t* __restrict__ count, const uint32_t* __restrict__ call_bad,
-                                  Aux aux, Term term, Done done) {
-    if (G.first >= cap) return;
-    RowRef ref[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int64_t q = G.first + u * G.step;
-        ref[u] = L[q < cap ? q : cap - 1];
-    }
-    const uint32_t n_listed = *count, bad = *call_bad;
-    // all six loads in flight before any is used (the compiler would
-    // otherwise issue the rows' loads only once the length test has passed)
-    asm volatile("" ::"v"(ref[0].lo), "v"(ref[1].lo), "v"(ref[2].lo), "v"(ref[3].lo), "s"(n_listed),
-                 "s"(bad));
-    const uint32_t n32 = bad ? 0u : n_listed;   // a call that does not match the set-up sweeps nothing
-    const int64_t n = n32;
-    for (int64_t r = G.first; r < n; r += 4 * G.step) {
-        if (r != G.first) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t q = r + u * G.step;
-                ref[u] = L[q < n ? q : n - 1];
-            }
-        }
-        bool ok[4];
-        decltype(aux(0, false, ref[0])) a[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t q = r + u * G.step;
-            ok[u] = q < n;
-            a[u] = aux(q < cap ? q : cap - 1, ok[u], ref[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (ok[u])
-                done(r + u * G.step, ref[u], a[u],
-                     group_row_sum<GS>(ref[u].lo, ref[u].lo + ref[u].len, G.sub, term));
-    }
+// An entry and the matrix's product with a vector.
+struct Entry {
+    int32_t col;
+    float val;
+};
+__device__ __forceinline__ Entry load_entry(const int32_t* __restrict__ col, const float* __restrict__ val,
+                                            int64_t first, int k) {
+    return Entry{__builtin_nontemporal_load(col + first + (uint32_t)k),
+                 __builtin_nontemporal_load(val + first + (uint32_t)k)};
+}
+
+// out[r] = sum of the row's values (sens), 0 for an empty row.
+__global__ __launch_bounds__(T256) void k_sweep_sums(int64_t n_rows, int per, const int64_t* __restrict__ rp,
+                                                     const float* __restrict__ v, double* __restrict__ out) {
+    const int64_t r0 = sweep_chunk() * per;
+    if (r0 >= n_rows) return;
+    const int n = (int)std::min<int64_t>(per, n_rows - r0);
+    if ((int)threadIdx.x < n && rp[r0 + threadIdx.x] == rp[r0 + threadIdx.x + 1]) out[r0 + threadIdx.x] = 0.0;
+    sweep(r0, n, rp, [&](int64_t first, int k) { return __builtin_nontemporal_load(v + first + (uint32_t)k); }, [](float x) { return (double)x; },
+          [&](int64_t r, double acc) { out[r] = acc; });
 }
 
 // y_j = sum_i T_ij S_i; ratio_j = P_j / y_j (0 when y_j = 0), over the
 // non-empty bin rows (an empty one is referred to by no entry of T^T, so its
-// ratio is never read).
-template <int GS>
-__global__ __launch_bounds__(T256) void k_mlem_forward(const RowRef* __restrict__ L, int64_t cap,
-                                                       const uint32_t* __restrict__ count,
+// ratio is never read).  A call that does not match the set-up sweeps nothing.
+__global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, const int64_t* __restrict__ rp,
                                                        const uint32_t* __restrict__ call_bad,
                                                        const int32_t* __restrict__ col,
                                                        const float* __restrict__ val,
                                                        const double* __restrict__ S,
                                                        const float* __restrict__ P,
                                                        double* __restrict__ ratio) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    sweep_list(G, L, cap, count, call_bad,
-               [&](int64_t, bool ok, const RowRef& r) { return P[ok ? r.row : 0]; },
-               [&](int64_t k, bool ok) {
-                   const double x = (double)val[k] * S[col[k]];
-                   return ok ? x : 0.0;
-               },
-               [&](int64_t, const RowRef& r, float p, double y) {
-                   if (G.sub == 0) ratio[r.row] = y > 0.0 ? (double)p / y : 0.0;
-               });
-}
-
-// Backprojection by bin slices.  When the ratio vector is larger than one
-// XCD's L2 (4 MB) and T^T has at least 16 entries per voxel row, the bin
-// range is cut into MLEM_SEGS equal slices and workgroup b works on slice
-// b mod MLEM_SEGS only: workgroups are handed to the 8 XCDs in turn, so each
-// XCD gathers from one slice of ratio (under 4 MB at 2^22 bins) that stays in
-// its L2, instead of every gather missing to HBM.  Each voxel row is cut at
-// the slice boundaries (binary search over its ascending columns, once per
-// call); the MLEM_SEGS partial sums are added in slice order.  Any cut is
-// correct (the pieces always partition the row), so rows whose columns are
-// not ascending lose only the locality.
-constexpr int MLEM_SEGS = 8;
-constexpr int64_t MLEM_SEG_MIN_BINS = (int64_t)1 << 19;
-
-inline bool mlem_sliced(int64_t n_bins, int64_t nnz, int64_t n_vox) {
-    return n_bins >= MLEM_SEG_MIN_BINS && nnz >= 16 * n_vox;
-}
-
-// sb[i][s] (s = 0..MLEM_SEGS): first entry of voxel row i in slice s, with
-// sb[i][0] = rp[i] and sb[i][MLEM_SEGS] = rp[i + 1]; non-decreasing in s.
-__global__ __launch_bounds__(T256) void k_mlem_slices(int64_t n_vox, int64_t n_bins,
-                                                      const int64_t* __restrict__ rp,
-                                                      const int32_t* __restrict__ col,
-                                                      int64_t* __restrict__ sb) {
-    for (int64_t i = (int64_t)blockIdx.x * T256 + threadIdx.x; i < n_vox;
-         i += (int64_t)gridDim.x * T256) {
-        int64_t lo = rp[i];
-        const int64_t hi = rp[i + 1];
-        int64_t* out = sb + i * (MLEM_SEGS + 1);
-        out[0] = lo;
-        for (int s = 1; s < MLEM_SEGS; ++s) {
-            const int64_t bound = n_bins * s / MLEM_SEGS;
-            int64_t a = lo, b = hi;
-            while (a < b) {
-                const int64_t mid = (a + b) >> 1;
-                if ((int64_t)col[mid] < bound) a = mid + 1; else b = mid;
-            }
-            out[s] = a;
-            lo = a;
-        }
-        out[MLEM_SEGS] = hi;
-    }
+    const int64_t r0 = sweep_chunk() * per;
+    if (r0 >= n_bins || *call_bad) return;
+    sweep(r0, (int)std::min<int64_t>(per, n_bins - r0), rp,
+          [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+          [&](Entry e) { return (double)e.val * S[e.col]; },
+          [&](int64_t r, double y) { ratio[r] = y > 0.0 ? (double)P[r] / y : 0.0; });
 }
 
 // S_i <- S_i * (sum_j T_ij ratio_j) / sens_i over the non-empty voxel rows
 // (an empty row has sens_i = 0, so its S_i is already 0).
-template <int GS>
-__global__ __launch_bounds__(T256) void k_mlem_update(const RowRef* __restrict__ L, int64_t cap,
-                                                       const uint32_t* __restrict__ count,
-                                                       const uint32_t* __restrict__ call_bad,
+__global__ __launch_bounds__(T256) void k_mlem_update(int64_t n_vox, int per, const int64_t* __restrict__ rp,
+                                                      const uint32_t* __restrict__ call_bad,
                                                       const int32_t* __restrict__ col,
                                                       const float* __restrict__ val,
                                                       const double* __restrict__ ratio,
                                                       const double* __restrict__ sens,
                                                       double* __restrict__ S) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    sweep_list(G, L, cap, count, call_bad,
-               [&](int64_t, bool ok, const RowRef& r) {
-                   const int64_t i = ok ? r.row : 0;
-                   return double2{S[i], sens[i]};
-               },
-               [&](int64_t k, bool ok) {
-                   const double x = (double)val[k] * ratio[col[k]];
-                   return ok ? x : 0.0;
-               },
-               [&](int64_t, const RowRef& r, double2 ss, double b) {
-                   if (G.sub == 0) S[r.row] = ss.y > 0.0 ? ss.x * b / ss.y : 0.0;
-               });
+    const int64_t r0 = sweep_chunk() * per;
+    if (r0 >= n_vox || *call_bad) return;
+    sweep(r0, (int)std::min<int64_t>(per, n_vox - r0), rp,
+          [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+          [&](Entry e) { return (double)e.val * ratio[e.col]; },
+          [&](int64_t r, double b) { S[r] = sens[r] > 0.0 ? S[r] * b / sens[r] : 0.0; });
 }
 
 // ---- compact layout.  The non-empty rows of both matrices are listed in
@@ -1229,50 +1113,6 @@ __global__ __launch_bounds__(T256) void k_mlem_update_c(const ClassRef* __restri
                [&](uint32_t q, double2 ss, double v) { S[q] = ss.y > 0.0 ? ss.x * v / ss.y : 0.0; });
 }
 
-// part[s][i] = sum over the entries of voxel row i in slice s of T_ij ratio_j,
-// slice s = blockIdx.x mod MLEM_SEGS (gridDim.x is a multiple of MLEM_SEGS).
-template <int GS>
-__global__ __launch_bounds__(T256) void k_mlem_back_slices(int64_t n_vox,
-                                                           const int64_t* __restrict__ sb,
-                                                           const int32_t* __restrict__ col,
-                                                           const float* __restrict__ val,
-                                                           const double* __restrict__ ratio,
-                                                           double* __restrict__ part,
-                                                           const uint32_t* __restrict__ call_bad) {
-    if (*call_bad) return;   // the slices are the set-up's: a mismatched call reads none
-    const int seg = (int)(blockIdx.x % MLEM_SEGS);
-    const RowGroups<GS> G(blockIdx.x / MLEM_SEGS, gridDim.x / MLEM_SEGS);
-    sweep_rows(G, n_vox,
-               [&](int64_t i, int64_t& lo, int64_t& hi) {
-                   const int64_t* b = sb + i * (MLEM_SEGS + 1) + seg;
-                   lo = b[0];
-                   hi = b[1];
-               },
-               [&](int64_t k, bool ok) {
-                   const double x = (double)val[k] * ratio[col[k]];
-                   return ok ? x : 0.0;
-               },
-               [&](int64_t i, int64_t, int64_t, double acc) {
-                   if (G.sub == 0) part[(int64_t)seg * n_vox + i] = acc;
-               });
-}
-
-// Sliced backprojection, second half: S_i <- S_i * (sum_s part[s][i]) / sens_i.
-__global__ __launch_bounds__(T256) void k_mlem_combine(int64_t n_vox, const double* __restrict__ part,
-                                                       const double* __restrict__ sens,
-                                                       double* __restrict__ S,
-                                                       const uint32_t* __restrict__ call_bad) {
-    if (*call_bad) return;
-    for (int64_t i = (int64_t)blockIdx.x * T256 + threadIdx.x; i < n_vox;
-         i += (int64_t)gridDim.x * T256) {
-        double b = 0.0;
-#pragma unroll
-        for (int s = 0; s < MLEM_SEGS; ++s) b += part[(int64_t)s * n_vox + i];
-        const double si = sens[i];
-        S[i] = si > 0.0 ? S[i] * b / si : 0.0;
-    }
-}
-
 // image_i = S_i (row order; vox_pos given: S in list order, 0 for an empty
 // row), NaN throughout when the bad flag of st (nullable) is set.
 __global__ __launch_bounds__(T256) void k_mlem_out(int64_t n_vox, const double* __restrict__ S,
@@ -1404,76 +1244,48 @@ __global__ __launch_bounds__(T256) void k_os_init(int64_t n_vox, int32_t n_sub,
 }
 
 // subset k: y_j = sum_i c_ij S_i + s_j, ratio_j = P_j / y_j on the subset's
-// bins (row t of the subset is bin j of view k + n_sub * (t / bins_per_view));
-// rows swept as in MLEM, the group size following the whole matrix's density
-template <int GS>
-__device__ inline void os_forward_rows(int64_t n_sub_bins, int32_t bins_per_view, int32_t n_sub,
-                                       int32_t k, const int64_t* __restrict__ rp,
-                                       const int32_t* __restrict__ col,
-                                       const float* __restrict__ val,
-                                       const double* __restrict__ S, const float* __restrict__ P,
-                                       const float* __restrict__ scat, double* __restrict__ ratio) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    auto bin_of = [&](int64_t t) {
-        const int64_t view = k + (int64_t)n_sub * (t / bins_per_view);
-        return view * bins_per_view + t % bins_per_view;
-    };
-    sweep_rows(G, n_sub_bins,
-               [&](int64_t t, int64_t& lo, int64_t& hi) {
-                   const int64_t j = bin_of(t);
-                   lo = rp[j];
-                   hi = rp[j + 1];
-               },
-               [&](int64_t e, bool ok) {
-                   const double x = (double)val[e] * S[col[e]];
-                   return ok ? x : 0.0;
-               },
-               [&](int64_t t, int64_t, int64_t, double y) {
-                   if (G.sub != 0) return;
-                   const int64_t j = bin_of(t);
-                   y += scat ? (double)scat[j] : 0.0;
-                   ratio[j] = y > 0.0 ? (double)P[j] / y : 0.0;
-               });
-}
-
-__global__ __launch_bounds__(T256) void k_os_forward(int64_t n_sub_bins, int32_t bins_per_view,
-                                                     int32_t n_sub, int32_t k,
+// bins: views k, k + n_sub, ..., each in chunks of `per` rows.
+__global__ __launch_bounds__(T256) void k_os_forward(int64_t n_chunks, int32_t per_view, int per,
+                                                     int32_t bins_per_view, int32_t n_sub, int32_t k,
                                                      const int64_t* __restrict__ rp,
                                                      const int32_t* __restrict__ col,
                                                      const float* __restrict__ val,
                                                      const double* __restrict__ S,
                                                      const float* __restrict__ P,
                                                      const float* __restrict__ scat,
-                                                     double* __restrict__ ratio, int64_t n_bins) {
-    switch (lanes_per_row(rp[n_bins], n_bins)) {
-        case 1: os_forward_rows<1>(n_sub_bins, bins_per_view, n_sub, k, rp, col, val, S, P, scat, ratio); break;
-        case 4: os_forward_rows<4>(n_sub_bins, bins_per_view, n_sub, k, rp, col, val, S, P, scat, ratio); break;
-        case 16: os_forward_rows<16>(n_sub_bins, bins_per_view, n_sub, k, rp, col, val, S, P, scat, ratio); break;
-        default: os_forward_rows<64>(n_sub_bins, bins_per_view, n_sub, k, rp, col, val, S, P, scat, ratio); break;
-    }
+                                                     double* __restrict__ ratio) {
+    const int64_t c = sweep_chunk();
+    if (c >= n_chunks) return;
+    const int32_t in_view = (int32_t)(c % per_view) * per;
+    const int64_t r0 = (k + n_sub * (c / per_view)) * bins_per_view + in_view;
+    const int n = std::min(per, bins_per_view - in_view);
+    const auto done = [&](int64_t j, double y) {
+        y += scat ? (double)scat[j] : 0.0;
+        ratio[j] = y > 0.0 ? (double)P[j] / y : 0.0;
+    };
+    // a bin without entries still has its scatter term
+    if ((int)threadIdx.x < n && rp[r0 + threadIdx.x] == rp[r0 + threadIdx.x + 1]) done(r0 + threadIdx.x, 0.0);
+    sweep(r0, n, rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+          [&](Entry e) { return (double)e.val * S[e.col]; }, done);
 }
 
 // subset k: S_i <- S_i * (sum_{j in k} b_ij ratio_j) / sens_k,i (unchanged
 // where sens_k,i = 0), over subset k's rows of the split backprojector
 // (rp = off + k n_vox: row i spans [rp[i], rp[i + 1])).
-template <int GS>
-__global__ __launch_bounds__(T256) void k_os_update(int64_t n_vox, const int64_t* __restrict__ rp,
+__global__ __launch_bounds__(T256) void k_os_update(int64_t n_vox, int per, const int64_t* __restrict__ rp,
                                                     const int32_t* __restrict__ col,
                                                     const float* __restrict__ val,
                                                     const double* __restrict__ ratio,
                                                     const double* __restrict__ sens_k,
                                                     double* __restrict__ S) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    sweep_rows(G, n_vox, [&](int64_t i, int64_t& lo, int64_t& hi) { lo = rp[i]; hi = rp[i + 1]; },
-               [&](int64_t e, bool ok) {
-                   const double x = (double)val[e] * ratio[col[e]];
-                   return ok ? x : 0.0;
-               },
-               [&](int64_t i, int64_t, int64_t, double bsum) {
-                   if (G.sub != 0) return;
-                   const double si = sens_k[i];
-                   if (si > 0.0) S[i] = S[i] * bsum / si;
-               });
+    const int64_t r0 = sweep_chunk() * per;
+    if (r0 >= n_vox) return;
+    sweep(r0, (int)std::min<int64_t>(per, n_vox - r0), rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+          [&](Entry e) { return (double)e.val * ratio[e.col]; },
+          [&](int64_t i, double b) {
+              const double si = sens_k[i];
+              if (si > 0.0) S[i] = S[i] * b / si;
+          });
 }
 
 }  // namespace
@@ -1537,20 +1349,22 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
     if ((e = exclusive_scan(cnt, rows, off, (uint64_t*)(w + L.bsum), s)) != hipSuccess) return e;
     k_os_split_scatter<<<gw, T256, 0, s>>>(n_vox, Bt_rp, Bt_col, Bt_val, bins_per_view, n_sub, off, col_s,
                                            val_s, st);
-    k_row_sums<<<grid_for(rows, T256, 8192), T256, 0, s>>>((int64_t)rows, (const int64_t*)off, val_s, sens);
+    const int per_u = sweep_rows_for(bt_nnz, (int64_t)rows);
+    k_sweep_sums<<<sweep_grid(((int64_t)rows + per_u - 1) / per_u), T256, 0, s>>>((int64_t)rows, per_u,
+                                                                                 (const int64_t*)off, val_s, sens);
     k_os_init<<<gv, T256, 0, s>>>(n_vox, n_sub, image, sens, S);
-    // lanes per subset row from the mean subset row length
-    const int gs_u = lanes_per_row(bt_nnz / n_sub, n_vox);
-    auto ku = by_group(gs_u, k_os_update<1>, k_os_update<4>, k_os_update<16>, k_os_update<64>);
+    // the entry count of c is not known here: its rows as b's
+    const int per_f = sweep_rows_for(bt_nnz, n_bins);
+    const int32_t per_view = (bins_per_view + per_f - 1) / per_f;
     for (int it = 0; it < n_iter; ++it) {
         for (int k = 0; k < n_sub; ++k) {
-            const int64_t views_k = (n_views - k + n_sub - 1) / n_sub;
-            const int64_t nb = views_k * bins_per_view;
-            if (nb <= 0) continue;
-            k_os_forward<<<grid_for((uint64_t)nb, T256, 16384), T256, 0, s>>>(
-                nb, bins_per_view, n_sub, k, C_rp, C_col, C_val, S, proj, scatter, ratio, n_bins);
-            ku<<<gv, T256, 0, s>>>(n_vox, (const int64_t*)(off + (uint64_t)k * (uint64_t)n_vox), col_s, val_s,
-                                   ratio, sens + (uint64_t)k * (uint64_t)n_vox, S);
+            const int64_t chunks = (n_views - k + n_sub - 1) / n_sub * per_view;
+            if (chunks <= 0) continue;
+            k_os_forward<<<sweep_grid(chunks), T256, 0, s>>>(chunks, per_view, per_f, bins_per_view, n_sub, k, C_rp,
+                                                             C_col, C_val, S, proj, scatter, ratio);
+            k_os_update<<<sweep_grid((n_vox + per_u - 1) / per_u), T256, 0, s>>>(
+                n_vox, per_u, (const int64_t*)(off + (uint64_t)k * (uint64_t)n_vox), col_s, val_s, ratio,
+                sens + (uint64_t)k * (uint64_t)n_vox, S);
         }
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
@@ -1666,10 +1480,10 @@ namespace {
 
 // Byte offsets of mlem_iterate's workspace, for n_bins x n_vox (every array
 // 256-byte aligned).  The compact layout's arrays are sized for its largest
-// entry count, n_bins + n_vox; the slice arrays exist for n_bins >= 2^19.
+// entry count, n_bins + n_vox.
 struct MlemLayout {
     size_t sens, S, ratio, bin_rows, vox_rows, st, sens_l, P_l, bin_pos, vox_pos, Tc, Ttc, bin_short, vox_short;
-    size_t sb, part, total;
+    size_t total;
 };
 
 MlemLayout mlem_layout(uint64_t nb, uint64_t nv) {
@@ -1694,10 +1508,6 @@ MlemLayout mlem_layout(uint64_t nb, uint64_t nv) {
     L.Ttc = take(4 * (nb + nv));
     L.bin_short = take(sizeof(ShortRow) * nb);
     L.vox_short = take(sizeof(ShortRow) * nv);
-    if ((int64_t)nb >= MLEM_SEG_MIN_BINS) {
-        L.sb = take(8 * (MLEM_SEGS + 1) * nv);
-        L.part = take(8 * MLEM_SEGS * nv);
-    }
     L.total = o;
     return L;
 }
@@ -1705,24 +1515,6 @@ MlemLayout mlem_layout(uint64_t nb, uint64_t nv) {
 }  // namespace
 
 size_t mlem_workspace(uint64_t n_bins, uint64_t n_vox) { return mlem_layout(n_bins, n_vox).total; }
-
-namespace {
-
-// Workgroups for a sweep of at most `rows` rows by groups of gs lanes, four
-// rows per group and pass: one pass when the device holds it, else one
-// resident round (the sweeps are grid-strided; more workgroups would only
-// cost dispatch time and a ragged last round).
-template <class K>
-hipError_t sweep_grid(K kernel, int64_t rows, int gs, int n_cu, int* grid) {
-    int bpc = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, kernel, T256, 0);
-    if (e != hipSuccess) return e;
-    const uint64_t threads = ((uint64_t)std::max<int64_t>(rows, 1) + 3) / 4 * (uint64_t)gs;
-    *grid = grid_for(threads, T256, std::max(1, n_cu * bpc));
-    return hipSuccess;
-}
-
-}  // namespace
 
 hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t* T_rp,
                        const int32_t* T_col, const float* T_val, const int64_t* Tt_rp,
@@ -1734,14 +1526,13 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     double* sens = (double*)(w + Lo.sens);
     double* S = (double*)(w + Lo.S);
     double* ratio = (double*)(w + Lo.ratio);
-    RowRef* bin_rows = (RowRef*)(w + Lo.bin_rows);
-    RowRef* vox_rows = (RowRef*)(w + Lo.vox_rows);
     uint32_t* st = (uint32_t*)(w + Lo.st);
     const bool setup = (phases & MLEM_SETUP) != 0, iterate = (phases & MLEM_ITERATE) != 0;
     // Layout: compact when the matrix is sparse (its renumbered columns fit
-    // the workspace), else bin slices on large detectors, else row order.
+    // the workspace), else row order.
     const bool compact = nnz <= n_bins + n_vox;
-    const bool sliced = !compact && mlem_sliced(n_bins, nnz, n_vox);
+    const int per_b = sweep_rows_for(nnz, n_bins), per_v = sweep_rows_for(nnz, n_vox);
+    const unsigned grid_b = sweep_grid((n_bins + per_b - 1) / per_b), grid_v = sweep_grid((n_vox + per_v - 1) / per_v);
     int dev = 0, n_cu = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -1749,7 +1540,7 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     const int gv = grid_for(nv, T256, 8192);
     const int gr = grid_for((nb + ROW_CHUNK - 1) / ROW_CHUNK + (nv + ROW_CHUNK - 1) / ROW_CHUNK, 1, 2048);
     if (setup) {
-        k_row_sums<<<gv, T256, 0, s>>>(n_vox, Tt_rp, Tt_val, sens);
+        k_sweep_sums<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, Tt_val, sens);
         k_mlem_setup<<<1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
     }
     if (compact) {
@@ -1805,43 +1596,11 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
         k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, vox_pos, st, image);
         return hipGetLastError();
     }
-    int64_t* sb = sliced ? (int64_t*)(w + Lo.sb) : nullptr;
-    double* part = sliced ? (double*)(w + Lo.part) : nullptr;
-    if (setup) {
-        k_mlem_rows<<<gr, T256, 0, s>>>(n_bins, n_vox, T_rp, Tt_rp, bin_rows, vox_rows, nullptr, nullptr, st);
-        if (sliced) k_mlem_slices<<<gv, T256, 0, s>>>(n_vox, n_bins, Tt_rp, Tt_col, sb);
-    }
     if (!iterate) return hipGetLastError();
-    // Group sizes from the mean row length over all rows that can be
-    // non-empty (at most nnz of them): the summation order depends only on
-    // the matrix.
-    const int64_t bin_rows_max = std::min(n_bins, std::max<int64_t>(nnz, 1));
-    const int64_t vox_rows_max = std::min(n_vox, std::max<int64_t>(nnz, 1));
-    const int gs_f = lanes_per_row(nnz, bin_rows_max);
-    const int gs_u = sliced ? lanes_per_row(nnz, n_vox * MLEM_SEGS) : lanes_per_row(nnz, vox_rows_max);
-    auto kf = by_group(gs_f, k_mlem_forward<1>, k_mlem_forward<4>, k_mlem_forward<16>, k_mlem_forward<64>);
-    auto ku = by_group(gs_u, k_mlem_update<1>, k_mlem_update<4>, k_mlem_update<16>, k_mlem_update<64>);
-    auto kb = by_group(gs_u, k_mlem_back_slices<1>, k_mlem_back_slices<4>, k_mlem_back_slices<16>,
-                       k_mlem_back_slices<64>);
-    int gb = 1, gu = 1;
-    if ((e = sweep_grid(kf, bin_rows_max, gs_f, n_cu, &gb)) != hipSuccess) return e;
-    if (sliced) {
-        // one grid of slices: workgroup b on slice b mod MLEM_SEGS
-        int per = 1;
-        if ((e = sweep_grid(kb, n_vox, gs_u, std::max(1, n_cu / MLEM_SEGS), &per)) != hipSuccess) return e;
-        gu = MLEM_SEGS * per;
-    } else if ((e = sweep_grid(ku, vox_rows_max, gs_u, n_cu, &gu)) != hipSuccess) {
-        return e;
-    }
     k_mlem_load<<<gv, T256, 0, s>>>(n_bins, n_vox, nnz, image, sens, S, nullptr, nullptr, nullptr, nullptr, st);
     for (int it = 0; it < n_iter; ++it) {
-        kf<<<gb, T256, 0, s>>>(bin_rows, n_bins, st + ST_BINS, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
-        if (sliced) {
-            kb<<<gu, T256, 0, s>>>(n_vox, sb, Tt_col, Tt_val, ratio, part, st + ST_CALL_BAD);
-            k_mlem_combine<<<gv, T256, 0, s>>>(n_vox, part, sens, S, st + ST_CALL_BAD);
-        } else {
-            ku<<<gu, T256, 0, s>>>(vox_rows, n_vox, st + ST_VOXS, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
-        }
+        k_mlem_forward<<<grid_b, T256, 0, s>>>(n_bins, per_b, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
+        k_mlem_update<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
     return hipGetLastError();

@@ -567,45 +567,68 @@ __device__ inline double group_row_sum(int64_t k0, int64_t k1, int sub, Term ter
     return acc;
 }
 
-// ---- row order.  Sweeps of a dense matrix: a workgroup takes SWEEP_ROWS or
-// fewer consecutive rows, whose entries are consecutive too, and streams them
-// SWEEP_TILE at a time: coalesced loads of columns and values, eight gathers
-// in flight per thread, the products in LDS in FP64, then each row summed from
-// there by a power-of-two group of lanes.  The order of a sum depends only on
-// the matrix.  Bound by the stream of entries (8 bytes each) and the gathers.
-// What it replaces: a lane group per row with the row's loads in a chain (233
-// us per forward sweep and, in bin slices per XCD with a third kernel adding
-// them, 393 us per backprojection on a forced-detection matrix of 4.6e7
-// entries, 1.97 M bins and 2.6e5 voxels: 171 and 300 us now).  No slices are
-// needed: each XCD works on neighbouring rows (sweep_chunk), so a
-// backprojection's gathers from its slab of voxels fall in the bins of a few
-// detector rows, which its L2 holds (90 % hits).  Where columns are random,
-// which no camera gives, the slices were the better (2^20 bins x 2^17 voxels,
-// 3e7 entries: 442 against 465 us per iteration).
-constexpr int SWEEP_ROWS = 256;      // most rows of a workgroup (= T256: one row bound per thread)
-constexpr int SWEEP_TILE = 2048;     // entries in LDS
-constexpr int SWEEP_LOADS = SWEEP_TILE / T256;
+// ---- row order.  Sweeps of a dense matrix: a group of threads (a wavefront,
+// or a whole workgroup where rows are long) takes consecutive rows, whose
+// entries are consecutive too, and streams them a tile of eight entries per
+// thread at a time: coalesced loads of columns and values, eight gathers in
+// flight per thread, the products in LDS in FP64, then each row summed from
+// there by a power-of-two number of lanes.  The order of a sum depends only on
+// the matrix.  Bound by the stream of entries (8 bytes each) and the gathers'
+// traffic from L2 to L1, a line per entry.  What it replaces: a lane group per
+// row with the row's loads in a chain (233 us per forward sweep and, in bin
+// slices per XCD with a third kernel adding them, 393 us per backprojection on
+// a forced-detection matrix of 4.6e7 entries, 1.97 M bins and 2.6e5 voxels:
+// 169 and 299 us now).  No slices are needed: each XCD works on
+// neighbouring rows (sweep_chunk), so a backprojection's gathers from its slab
+// of voxels fall in the bins of a few detector rows, which its L2 holds (90 %
+// hits).  Where columns are random, which no camera gives, the slices were the
+// better (2^20 bins x 2^17 voxels, 3e7 entries: 442 against 460 us per
+// iteration).
+constexpr int SWEEP_LOADS = 8;
 
-// Rows per workgroup: three quarters of a tile on average, so that most
-// workgroups need one tile.
-inline int sweep_rows_for(int64_t nnz, int64_t n_rows) {
-    const int64_t mean = nnz / std::max<int64_t>(1, n_rows);
-    return (int)std::min<int64_t>(SWEEP_ROWS, std::max<int64_t>(1, (SWEEP_TILE * 3 / 4) / std::max<int64_t>(1, mean)));
+// How n rows are swept: threads per group (64 or T256) and rows per group, of
+// mean entries each; three quarters of a tile on average, so that most groups
+// need one.  Workgroups of four wavefronts are the better where they fill the
+// chip (one update of 2.6e5 rows of 5.5 entries: 11.8 against 17.1 us); a
+// wavefront on its own needs no barriers and takes smaller sweeps in more
+// pieces (1.7e5 rows of 3 entries in 9 subsets: 401 against 553 us per call),
+// but leaves rows of several of its tiles to a workgroup.
+struct SweepPlan {
+    int threads, per;
+};
+constexpr int64_t SWEEP_GROUPS = 768;
+constexpr int SWEEP_SHARE(int threads) { return SWEEP_LOADS * threads * 3 / 4; }
+inline SweepPlan sweep_plan(int64_t mean, int64_t n) {
+    mean = std::max<int64_t>(1, mean);
+    SweepPlan p;
+    p.threads = T256;
+    p.per = (int)std::min<int64_t>(T256, std::max<int64_t>(1, SWEEP_SHARE(T256) / mean));
+    if (n / p.per < SWEEP_GROUPS && mean <= 2 * SWEEP_LOADS * 64) {
+        p.threads = 64;
+        const int64_t per = std::min<int64_t>(SWEEP_SHARE(64) / mean, n / (4 * SWEEP_GROUPS));
+        p.per = (int)std::min<int64_t>(64, std::max<int64_t>(1, per));
+    }
+    return p;
 }
 
-// Workgroups for n chunks, and the chunk of workgroup b (workgroups are dealt
-// to the 8 XCDs in turn): each XCD takes runs of consecutive chunks, one run in
-// eight, 16 runs per XCD, so neighbouring rows meet in one L2 and dense and
-// empty regions are spread over the XCDs (with one contiguous eighth each, the
-// CUs were busy 70 % of a backprojection).
+// Workgroups for n chunks (a group's rows) in groups of G threads, and the
+// chunk of this group.  Workgroups are dealt to the 8 XCDs in turn: each XCD
+// takes runs of consecutive chunks, one run in eight, 16 runs per XCD, so
+// neighbouring rows meet in one L2 and dense and empty regions are spread over
+// the XCDs (with one contiguous eighth each, the CUs were busy 70 % of a
+// backprojection).
 constexpr int SWEEP_RUNS = 16;
-inline unsigned sweep_grid(int64_t n_chunks) {
-    const int64_t run = (n_chunks + 8 * SWEEP_RUNS - 1) / (8 * SWEEP_RUNS);
+inline unsigned sweep_grid(int64_t n_chunks, int threads) {
+    const int64_t blocks = (n_chunks + T256 / threads - 1) / (T256 / threads);
+    const int64_t run = (blocks + 8 * SWEEP_RUNS - 1) / (8 * SWEEP_RUNS);
     return (unsigned)(8 * SWEEP_RUNS * run);
 }
+template <int G>
 __device__ __forceinline__ int64_t sweep_chunk() {
     const uint32_t run = gridDim.x / (8 * SWEEP_RUNS), j = blockIdx.x / 8;
-    return (int64_t)((j / run * 8 + blockIdx.x % 8) * run + j % run);
+    const int64_t block = (int64_t)((j / run * 8 + blockIdx.x % 8) * run + j % run);
+    if constexpr (G >= T256) return block;
+    else return block * (T256 / G) + __builtin_amdgcn_readfirstlane(threadIdx.x / G);
 }
 
 __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
@@ -614,51 +637,72 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Sum over each row r in [r0, r0 + n) (n <= SWEEP_ROWS) of term(k) for its
-// entries k, done(r, sum) by one lane per non-empty row.  The term of entry
-// first + k is load(first, k) -> A, then value(A) -> double, so the loads of a
-// tile are issued before its gathers (first is in scalar registers).  All
-// threads of the workgroup call.
-template <class Load, class Value, class Done>
-__device__ inline void sweep(int64_t r0, int n, const int64_t* __restrict__ rp, Load load, Value value, Done done) {
-    __shared__ double prod[SWEEP_TILE];
-    __shared__ int64_t off[SWEEP_ROWS + 1];
-    const int tid = (int)threadIdx.x;
-    const int64_t e0 = rp[r0];
-    if (tid <= n) off[tid] = rp[r0 + tid] - e0;
-    if (tid == 0 && n == SWEEP_ROWS) off[n] = rp[r0 + n] - e0;
-    __syncthreads();
+// LDS written by some threads of a group before others read it.
+template <int G>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (G == 64) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+// Sum over each row r in [r0, r0 + n) (n <= G) of its entries' terms,
+// done(r, sum) by one lane per non-empty row.  The rows' entries start at e0 +
+// bound(0), bound(1), ..., bound(n); the term of entry first + k is load(first,
+// k) -> A, then value(A) -> double, so the loads of a tile are issued before
+// its gathers (first is in scalar registers).  All threads of a group call,
+// with the same r0 and n.  skip: nothing is done (loaded along with the
+// bounds, not before them).
+template <int G, class Bound, class Load, class Value, class Done>
+__device__ inline void sweep_bounds(int64_t r0, int n, bool skip, int64_t e0, Bound bound, Load load, Value value,
+                                    Done done) {
+    constexpr int TILE = SWEEP_LOADS * G;
+    __shared__ double prod_s[T256 / G][TILE];
+    __shared__ int64_t off_s[T256 / G][G + 1];
+    double* __restrict__ prod = prod_s[threadIdx.x / G];
+    int64_t* __restrict__ off = off_s[threadIdx.x / G];
+    const int tid = (int)(threadIdx.x % G);
+    if (tid <= n) off[tid] = bound(tid);
+    if (tid == 0 && n == G) off[n] = bound(n);
+    if (skip) return;
+    group_sync<G>();
     int s = 0;
     while (s < n) {
         // rows [s, e) fit in a tile
         int e = s, hi = n;
         while (e < hi) {
             const int mid = (e + hi + 1) >> 1;
-            if (off[mid] - off[s] <= SWEEP_TILE) e = mid; else hi = mid - 1;
+            if (off[mid] - off[s] <= TILE) e = mid; else hi = mid - 1;
         }
+        e = __builtin_amdgcn_readfirstlane(e);
         const int64_t first = uniform_i64(e0 + off[s]);
-        if (e == s) {
-            // one row longer than a tile: the whole workgroup, tile by tile
+        if (e <= s + 1) {
+            // one row: the whole group, tile by tile
             const int64_t len = uniform_i64(off[s + 1] - off[s]);
             double acc = 0.0;
-            for (int64_t k0 = 0; k0 < len; k0 += SWEEP_TILE) {
-                const int cnt = (int)(len - k0 < SWEEP_TILE ? len - k0 : SWEEP_TILE);
+            for (int64_t k0 = 0; k0 < len; k0 += TILE) {
+                const int cnt = (int)(len - k0 < TILE ? len - k0 : TILE);
                 decltype(load(0, 0)) a[SWEEP_LOADS];
 #pragma unroll
                 for (int u = 0; u < SWEEP_LOADS; ++u) {
-                    const int k = tid + u * T256;
+                    const int k = tid + u * G;
                     a[u] = load(first + k0, k < cnt ? k : cnt - 1);
                 }
 #pragma unroll
                 for (int u = 0; u < SWEEP_LOADS; ++u) {
                     const double x = value(a[u]);
-                    acc += tid + u * T256 < cnt ? x : 0.0;
+                    acc += tid + u * G < cnt ? x : 0.0;
                 }
             }
             acc = wave_sum_f64(acc);
-            if ((tid & 63) == 0) prod[tid >> 6] = acc;
-            __syncthreads();
-            if (tid == 0) done(r0 + s, (prod[0] + prod[1]) + (prod[2] + prod[3]));
+            if constexpr (G > 64) {
+                if ((tid & 63) == 0) prod[tid >> 6] = acc;
+                group_sync<G>();
+                acc = (prod[0] + prod[1]) + (prod[2] + prod[3]);
+            }
+            if (tid == 0) done(r0 + s, acc);
             ++s;
         } else {
             const int cnt = (int)uniform_i64(off[e] - off[s]);
@@ -666,18 +710,18 @@ __device__ inline void sweep(int64_t r0, int n, const int64_t* __restrict__ rp, 
                 decltype(load(0, 0)) a[SWEEP_LOADS];
 #pragma unroll
                 for (int u = 0; u < SWEEP_LOADS; ++u) {
-                    const int k = tid + u * T256;
+                    const int k = tid + u * G;
                     a[u] = load(first, k < cnt ? k : cnt - 1);
                 }
 #pragma unroll
-                for (int u = 0; u < SWEEP_LOADS; ++u) prod[tid + u * T256] = value(a[u]);
+                for (int u = 0; u < SWEEP_LOADS; ++u) prod[tid + u * G] = value(a[u]);
             }
-            __syncthreads();
+            group_sync<G>();
             // as many lanes per row as there are for all rows at once
             int gs = 1;
-            while (gs < 64 && 2 * gs * (e - s) <= T256) gs *= 2;
+            while (gs < 64 && 2 * gs * (e - s) <= G) gs *= 2;
             const int sub = tid & (gs - 1);
-            for (int r = s + tid / gs; r < e; r += T256 / gs) {
+            for (int r = s + tid / gs; r < e; r += G / gs) {
                 const int k0 = (int)(off[r] - off[s]), k1 = (int)(off[r + 1] - off[s]);
                 double acc = 0.0;
                 for (int k = k0 + sub; k < k1; k += gs) acc += prod[k];
@@ -686,8 +730,15 @@ __device__ inline void sweep(int64_t r0, int n, const int64_t* __restrict__ rp, 
             }
             s = e;
         }
-        __syncthreads();          // prod is written again
+        group_sync<G>();          // prod is written again
     }
+}
+
+template <int G, class Load, class Value, class Done>
+__device__ inline void sweep(int64_t r0, int n, bool skip, const int64_t* __restrict__ rp, Load load, Value value,
+                             Done done) {
+    const int64_t e0 = rp[r0];
+    sweep_bounds<G>(r0, n, skip, e0, [&](int i) { return rp[r0 + i] - e0; }, load, value, done);
 }
 
 // An entry and the matrix's product with a vector.
@@ -702,19 +753,22 @@ __device__ __forceinline__ Entry load_entry(const int32_t* __restrict__ col, con
 }
 
 // out[r] = sum of the row's values (sens), 0 for an empty row.
+template <int G>
 __global__ __launch_bounds__(T256) void k_sweep_sums(int64_t n_rows, int per, const int64_t* __restrict__ rp,
                                                      const float* __restrict__ v, double* __restrict__ out) {
-    const int64_t r0 = sweep_chunk() * per;
+    const int64_t r0 = sweep_chunk<G>() * per;
     if (r0 >= n_rows) return;
     const int n = (int)std::min<int64_t>(per, n_rows - r0);
-    if ((int)threadIdx.x < n && rp[r0 + threadIdx.x] == rp[r0 + threadIdx.x + 1]) out[r0 + threadIdx.x] = 0.0;
-    sweep(r0, n, rp, [&](int64_t first, int k) { return __builtin_nontemporal_load(v + first + (uint32_t)k); }, [](float x) { return (double)x; },
-          [&](int64_t r, double acc) { out[r] = acc; });
+    const int i = (int)(threadIdx.x % G);
+    if (i < n && rp[r0 + i] == rp[r0 + i + 1]) out[r0 + i] = 0.0;
+    sweep<G>(r0, n, false, rp, [&](int64_t first, int k) { return __builtin_nontemporal_load(v + first + (uint32_t)k); },
+             [](float x) { return (double)x; }, [&](int64_t r, double acc) { out[r] = acc; });
 }
 
 // y_j = sum_i T_ij S_i; ratio_j = P_j / y_j (0 when y_j = 0), over the
 // non-empty bin rows (an empty one is referred to by no entry of T^T, so its
 // ratio is never read).  A call that does not match the set-up sweeps nothing.
+template <int G>
 __global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, const int64_t* __restrict__ rp,
                                                        const uint32_t* __restrict__ call_bad,
                                                        const int32_t* __restrict__ col,
@@ -722,16 +776,17 @@ __global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, 
                                                        const double* __restrict__ S,
                                                        const float* __restrict__ P,
                                                        double* __restrict__ ratio) {
-    const int64_t r0 = sweep_chunk() * per;
-    if (r0 >= n_bins || *call_bad) return;
-    sweep(r0, (int)std::min<int64_t>(per, n_bins - r0), rp,
-          [&](int64_t first, int k) { return load_entry(col, val, first, k); },
-          [&](Entry e) { return (double)e.val * S[e.col]; },
-          [&](int64_t r, double y) { ratio[r] = y > 0.0 ? (double)P[r] / y : 0.0; });
+    const int64_t r0 = sweep_chunk<G>() * per;
+    if (r0 >= n_bins) return;
+    sweep<G>(r0, (int)std::min<int64_t>(per, n_bins - r0), *call_bad != 0, rp,
+             [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+             [&](Entry e) { return (double)e.val * S[e.col]; },
+             [&](int64_t r, double y) { ratio[r] = y > 0.0 ? (double)P[r] / y : 0.0; });
 }
 
 // S_i <- S_i * (sum_j T_ij ratio_j) / sens_i over the non-empty voxel rows
 // (an empty row has sens_i = 0, so its S_i is already 0).
+template <int G>
 __global__ __launch_bounds__(T256) void k_mlem_update(int64_t n_vox, int per, const int64_t* __restrict__ rp,
                                                       const uint32_t* __restrict__ call_bad,
                                                       const int32_t* __restrict__ col,
@@ -739,12 +794,12 @@ __global__ __launch_bounds__(T256) void k_mlem_update(int64_t n_vox, int per, co
                                                       const double* __restrict__ ratio,
                                                       const double* __restrict__ sens,
                                                       double* __restrict__ S) {
-    const int64_t r0 = sweep_chunk() * per;
-    if (r0 >= n_vox || *call_bad) return;
-    sweep(r0, (int)std::min<int64_t>(per, n_vox - r0), rp,
-          [&](int64_t first, int k) { return load_entry(col, val, first, k); },
-          [&](Entry e) { return (double)e.val * ratio[e.col]; },
-          [&](int64_t r, double b) { S[r] = sens[r] > 0.0 ? S[r] * b / sens[r] : 0.0; });
+    const int64_t r0 = sweep_chunk<G>() * per;
+    if (r0 >= n_vox) return;
+    sweep<G>(r0, (int)std::min<int64_t>(per, n_vox - r0), *call_bad != 0, rp,
+             [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+             [&](Entry e) { return (double)e.val * ratio[e.col]; },
+             [&](int64_t r, double b) { S[r] = sens[r] > 0.0 ? S[r] * b / sens[r] : 0.0; });
 }
 
 // ---- compact layout.  The non-empty rows of both matrices are listed in
@@ -1138,14 +1193,35 @@ __global__ __launch_bounds__(T256) void k_mlem_out(int64_t n_vox, const double* 
 // ---- ordered subsets (OSEM; dual matrix, Eq. DMOS; additive scatter, the
 // Sohlberg OS-EM equation).  Subset k holds the views v with v mod n_sub == k.
 
-// The backprojector split by subset, built once per call: for subset k and
-// voxel i, the entries of row i of B^T whose bin lies in subset k, in their
-// order in the row, at rows k * n_vox + i of one CSR (offsets off[], k-major),
-// so that a subset's backprojection reads that subset's entries only instead
-// of the whole of B^T once per subset.  One wavefront per row: 64 entries at
-// a time, the distinct subsets among them taken in turn (a ballot matches
-// the lanes of one subset); lane k of the wavefront keeps subset k's count
-// (hence at most 64 subsets).
+// The backprojector split by subset, built once per call, so that a subset's
+// backprojection reads that subset's entries only instead of the whole of B^T
+// once per subset.  A workgroup takes a chunk of consecutive rows and writes
+// their entries subset by subset, within a subset row by row in their order
+// in the row, into the chunk's own range of the copy: nothing has to be
+// counted over the whole matrix first.  offs[(chunk n_sub + k) (per + 1) + i]:
+// where row i of the chunk starts in subset k, relative to the chunk's first
+// entry (i = n: its end).  Each of 16 wavefronts (4 where a wavefront
+// sweeps a chunk) takes a share of the chunk's rows and goes over their entries
+// 64 at a time, SPLIT_LOADS groups loaded ahead (row by row, a wavefront waits
+// for each row's loads in turn); lanes of one row and subset are matched by a
+// ballot per bit of the subset's number.
+// Bound by reading B^T (twice, the second time from L2) and writing it once:
+// 8.6e6 entries of 2.6e5 rows in 6 subsets took 230 us as a count, a scan and
+// a scatter over single rows, 82 us now.
+constexpr int SPLIT_COUNTS = 4096;     // (subset, row) pairs of a chunk, counters in LDS
+constexpr int SPLIT_LOADS = 4;
+
+// Rows per chunk (and threads of the group that sweeps a subset's share of
+// one): half a tile on average, as dense regions hold several times the mean
+// (with twice as many rows the 12 updates and the split of 2.6e5 rows, 5.5
+// entries of each in a subset, took 573 against 437 us, with half 495).
+inline SweepPlan split_plan(int64_t nnz, int64_t n_bins, int64_t n_vox, int n_sub) {
+    SweepPlan p = sweep_plan(std::max<int64_t>(1, nnz / std::max<int64_t>(1, n_vox) * 2 / n_sub), n_vox);
+    p.per = (int)std::min<int64_t>(std::min(p.per, std::max(1, SPLIT_COUNTS / n_sub)), n_vox);
+    // a chunk's entries are counted in 32 bits
+    if (nnz > INT32_MAX) p.per = (int)std::max<int64_t>(1, std::min<int64_t>(p.per, INT32_MAX / n_bins));
+    return p;
+}
 
 // st[2] (as for MLEM: the image is NaN when set): the entry count the caller
 // gave is not B^T's own.
@@ -1154,81 +1230,165 @@ __global__ void k_os_check(int64_t n_vox, const int64_t* __restrict__ rp, int64_
     if (blockIdx.x == 0 && threadIdx.x < 4) st[threadIdx.x] = threadIdx.x == 2 ? (rp[n_vox] != nnz) : 0u;
 }
 
-__device__ __forceinline__ int os_subset_of(int32_t bin, int32_t bins_per_view, int32_t n_sub) {
-    return (bin / bins_per_view) % n_sub;
-}
+// Subset of a bin, (bin / bins_per_view) mod n_sub, with the quotients from
+// products with FP64 reciprocals: (x + 1/2) / d lies at least 1 / (2 d) from
+// every integer, and the product is off by less than that for x < 2^31.
+struct SubsetOf {
+    double inv_view, inv_sub;
+    int32_t n_sub;
+    __device__ SubsetOf(int32_t bins_per_view, int32_t n) : inv_view(1.0 / bins_per_view), inv_sub(1.0 / n), n_sub(n) {}
+    __device__ __forceinline__ int operator()(int32_t bin) const {
+        const int32_t view = (int32_t)(((double)bin + 0.5) * inv_view);
+        return view - n_sub * (int32_t)(((double)view + 0.5) * inv_sub);
+    }
+};
 
-// cnt[k * n_vox + i] = entries of row i in subset k (all 0 when st[2] is set).
-__global__ __launch_bounds__(T256) void k_os_split_count(int64_t n_vox, const int64_t* __restrict__ rp,
-                                                         const int32_t* __restrict__ col,
-                                                         int32_t bins_per_view, int32_t n_sub,
-                                                         uint32_t* __restrict__ cnt,
-                                                         const uint32_t* __restrict__ st) {
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_os_split(int64_t n_vox, int per, const int64_t* __restrict__ rp,
+                                                      const int32_t* __restrict__ col,
+                                                      const float* __restrict__ val, int32_t bins_per_view,
+                                                      int32_t n_sub, int32_t* __restrict__ offs,
+                                                      int32_t* __restrict__ col_s, float* __restrict__ val_s,
+                                                      const uint32_t* __restrict__ st) {
+    __shared__ uint32_t cnt[SPLIT_COUNTS];      // [subset][row]: counts, then next free slots
+    __shared__ uint32_t part[THREADS / 64];
+    __shared__ int32_t roff[T256 + 1];           // the rows' first entries in the chunk
+    const int64_t c = sweep_chunk<THREADS>(), r0 = c * per;
+    if (r0 >= n_vox) return;
+    const int n = (int)std::min<int64_t>(per, n_vox - r0), total = n * n_sub;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool bad = st[2] != 0;
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t waves = (int64_t)gridDim.x * (T256 / 64);
-    for (int64_t i = (int64_t)blockIdx.x * (T256 / 64) + (threadIdx.x >> 6); i < n_vox; i += waves) {
-        uint32_t c = 0;                    // lane k: entries of subset k so far
-        if (!bad) {
-            const int64_t lo = rp[i], hi = rp[i + 1];
-            for (int64_t e0 = lo; e0 < hi; e0 += 64) {
-                const int64_t e = e0 + lane;
-                const bool valid = e < hi;
-                const int k = valid ? os_subset_of(col[e], bins_per_view, n_sub) : -1;
-                uint64_t m = __ballot(valid);
-                while (m != 0) {
-                    const int kk = __builtin_amdgcn_readlane(k, __builtin_ctzll(m));
-                    const uint64_t grp = __ballot(k == kk) & m;
-                    if (lane == kk) c += (uint32_t)__popcll(grp);
-                    m &= ~grp;
-                }
-            }
+    const int64_t e0 = rp[r0];
+    const SubsetOf subset_of(bins_per_view, n_sub);
+    for (int i = tid; i < total; i += THREADS) cnt[i] = 0;
+    for (int i = tid; i <= n; i += THREADS) roff[i] = (int32_t)(rp[r0 + i] - e0);
+    __syncthreads();
+    // this wavefront's rows and entries
+    constexpr int WAVES = THREADS / 64;
+    const int ra = __builtin_amdgcn_readfirstlane(n * wave / WAVES);
+    const int rb = __builtin_amdgcn_readfirstlane(n * (wave + 1) / WAVES);
+    const int ea = bad ? 0 : __builtin_amdgcn_readfirstlane(roff[ra]);
+    const int eb = bad ? 0 : __builtin_amdgcn_readfirstlane(roff[rb]);
+    const int32_t* __restrict__ cols = col + e0;
+    // the row holding entry e: the last one starting at or before it
+    const auto row_of = [&](int e) {
+        int lo = ra, hi = rb - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (roff[mid] <= e) lo = mid; else hi = mid - 1;
         }
-        if (lane < n_sub) cnt[(int64_t)lane * n_vox + i] = c;
+        return lo;
+    };
+    for (int g = ea; g < eb; g += 64 * SPLIT_LOADS) {
+        int32_t cc[SPLIT_LOADS];
+#pragma unroll
+        for (int u = 0; u < SPLIT_LOADS; ++u) {
+            const int e = g + u * 64 + lane;
+            cc[u] = cols[(uint32_t)(e < eb ? e : eb - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < SPLIT_LOADS; ++u) {
+            const int e = g + u * 64 + lane;
+            if (e < eb) atomicAdd(&cnt[subset_of(cc[u]) * n + row_of(e)], 1u);
+        }
+    }
+    __syncthreads();
+    // exclusive scan, SPLIT_COUNTS / THREADS consecutive counters per thread
+    constexpr int PER = SPLIT_COUNTS / THREADS;
+    uint32_t mine[PER], sum = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = tid * PER + u;
+        mine[u] = i < total ? cnt[i] : 0u;
+        sum += mine[u];
+    }
+    uint32_t x = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    uint32_t run = x - sum;
+    for (int w = 0; w < wave; ++w) run += part[w];
+    int32_t* out = offs + c * n_sub * (int64_t)(per + 1);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = tid * PER + u;
+        if (i < total) {
+            const int k = i / n, r = i - k * n;
+            cnt[i] = run;
+            out[k * (per + 1) + r] = (int32_t)run;
+            run += mine[u];
+            if (r == n - 1) out[k * (per + 1) + n] = (int32_t)run;
+        }
+    }
+    __syncthreads();
+    const float* __restrict__ vals = val + e0;
+    int32_t* __restrict__ col_o = col_s + e0;
+    float* __restrict__ val_o = val_s + e0;
+    const uint64_t lane_lt = (1ull << lane) - 1ull;
+    for (int g = ea; g < eb; g += 64 * SPLIT_LOADS) {
+        int32_t cc[SPLIT_LOADS];
+        float v[SPLIT_LOADS];
+#pragma unroll
+        for (int u = 0; u < SPLIT_LOADS; ++u) {
+            const int e = g + u * 64 + lane;
+            cc[u] = cols[(uint32_t)(e < eb ? e : eb - 1)];
+            v[u] = vals[(uint32_t)(e < eb ? e : eb - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < SPLIT_LOADS; ++u) {
+            const int e = g + u * 64 + lane;
+            const bool ok = e < eb;
+            const int k = subset_of(cc[u]), r = row_of(ok ? e : eb - 1);
+            // the lanes of this row, then of this subset
+            const int first = roff[r] - (e - lane), end = roff[r + 1] - (e - lane);
+            uint64_t peers = __ballot(ok) & (first > 0 ? ~0ull << first : ~0ull) & (end < 64 ? (1ull << end) - 1ull : ~0ull);
+            for (int b = 0; (n_sub - 1) >> b; ++b) {
+                const bool bit = (k >> b) & 1;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t rank = (uint32_t)__popcll(peers & lane_lt);
+            if (ok) {
+                const uint32_t at = cnt[k * n + r];
+                col_o[at + rank] = cc[u];
+                val_o[at + rank] = v[u];
+                if (rank == 0) cnt[k * n + r] = at + (uint32_t)__popcll(peers);
+            }
+            // the next group reads the slots this one moved
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 
-// The entries moved to their subset rows: off[k * n_vox + i] is the first
-// slot of subset k's row i (an exclusive scan of cnt).
-__global__ __launch_bounds__(T256) void k_os_split_scatter(int64_t n_vox, const int64_t* __restrict__ rp,
-                                                           const int32_t* __restrict__ col,
-                                                           const float* __restrict__ val,
-                                                           int32_t bins_per_view, int32_t n_sub,
-                                                           const uint64_t* __restrict__ off,
-                                                           int32_t* __restrict__ col_s,
-                                                           float* __restrict__ val_s,
-                                                           const uint32_t* __restrict__ st) {
-    if (st[2] != 0) return;
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t waves = (int64_t)gridDim.x * (T256 / 64);
-    for (int64_t i = (int64_t)blockIdx.x * (T256 / 64) + (threadIdx.x >> 6); i < n_vox; i += waves) {
-        const int64_t lo = rp[i], hi = rp[i + 1];
-        if (lo == hi) continue;           // wave-uniform
-        // lane k: the next free slot of subset k's row i
-        uint64_t next = lane < n_sub ? off[(int64_t)lane * n_vox + i] : 0;
-        for (int64_t e0 = lo; e0 < hi; e0 += 64) {
-            const int64_t e = e0 + lane;
-            const bool valid = e < hi;
-            const int32_t c = valid ? col[e] : 0;
-            const float v = valid ? val[e] : 0.0f;
-            const int k = valid ? os_subset_of(c, bins_per_view, n_sub) : -1;
-            uint64_t m = __ballot(valid);
-            while (m != 0) {
-                const int kk = __builtin_amdgcn_readlane(k, __builtin_ctzll(m));
-                const uint64_t grp = __ballot(k == kk) & m;
-                const uint32_t lo32 = __builtin_amdgcn_readlane((uint32_t)next, kk);
-                const uint32_t hi32 = __builtin_amdgcn_readlane((uint32_t)(next >> 32), kk);
-                const uint64_t base = ((uint64_t)hi32 << 32) | lo32;
-                if (k == kk) {
-                    const uint64_t at = base + (uint64_t)__popcll(grp & ((1ull << lane) - 1ull));
-                    col_s[at] = c;
-                    val_s[at] = v;
-                }
-                if (lane == kk) next += (uint64_t)__popcll(grp);
-                m &= ~grp;
-            }
-        }
-    }
+// Subset k's part of chunk c of the split backprojector, swept.
+template <int G, class Load, class Value, class Done>
+__device__ inline void sweep_split(int64_t c, int k, int64_t n_vox, int per, int n_sub,
+                                   const int64_t* __restrict__ rp, const int32_t* __restrict__ offs, Load load,
+                                   Value value, Done done) {
+    const int64_t r0 = c * per;
+    const int32_t* __restrict__ o = offs + (c * n_sub + k) * (int64_t)(per + 1);
+    sweep_bounds<G>(r0, (int)std::min<int64_t>(per, n_vox - r0), false, rp[r0], [&](int i) { return (int64_t)o[i]; }, load,
+                 value, done);
+}
+
+// sens[k * n_vox + i] = sum of row i's values in subset k (blockIdx.y: k)
+template <int G>
+__global__ __launch_bounds__(T256) void k_os_sums(int64_t n_vox, int per, int n_sub, const int64_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ offs, const float* __restrict__ val,
+                                                  double* __restrict__ sens) {
+    const int64_t c = sweep_chunk<G>(), r0 = c * per;
+    if (r0 >= n_vox) return;
+    const int k = (int)blockIdx.y, i = (int)(threadIdx.x % G);
+    double* out = sens + k * n_vox;
+    const int32_t* o = offs + (c * n_sub + k) * (int64_t)(per + 1);
+    if (i < per && r0 + i < n_vox && o[i] == o[i + 1]) out[r0 + i] = 0.0;
+    sweep_split<G>(c, k, n_vox, per, n_sub, rp, offs,
+                [&](int64_t first, int e) { return __builtin_nontemporal_load(val + first + (uint32_t)e); },
+                [](float x) { return (double)x; }, [&](int64_t r, double acc) { out[r] = acc; });
 }
 
 __global__ __launch_bounds__(T256) void k_os_init(int64_t n_vox, int32_t n_sub,
@@ -1245,6 +1405,7 @@ __global__ __launch_bounds__(T256) void k_os_init(int64_t n_vox, int32_t n_sub,
 
 // subset k: y_j = sum_i c_ij S_i + s_j, ratio_j = P_j / y_j on the subset's
 // bins: views k, k + n_sub, ..., each in chunks of `per` rows.
+template <int G>
 __global__ __launch_bounds__(T256) void k_os_forward(int64_t n_chunks, int32_t per_view, int per,
                                                      int32_t bins_per_view, int32_t n_sub, int32_t k,
                                                      const int64_t* __restrict__ rp,
@@ -1254,7 +1415,7 @@ __global__ __launch_bounds__(T256) void k_os_forward(int64_t n_chunks, int32_t p
                                                      const float* __restrict__ P,
                                                      const float* __restrict__ scat,
                                                      double* __restrict__ ratio) {
-    const int64_t c = sweep_chunk();
+    const int64_t c = sweep_chunk<G>();
     if (c >= n_chunks) return;
     const int32_t in_view = (int32_t)(c % per_view) * per;
     const int64_t r0 = (k + n_sub * (c / per_view)) * bins_per_view + in_view;
@@ -1264,38 +1425,41 @@ __global__ __launch_bounds__(T256) void k_os_forward(int64_t n_chunks, int32_t p
         ratio[j] = y > 0.0 ? (double)P[j] / y : 0.0;
     };
     // a bin without entries still has its scatter term
-    if ((int)threadIdx.x < n && rp[r0 + threadIdx.x] == rp[r0 + threadIdx.x + 1]) done(r0 + threadIdx.x, 0.0);
-    sweep(r0, n, rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
-          [&](Entry e) { return (double)e.val * S[e.col]; }, done);
+    const int i = (int)(threadIdx.x % G);
+    if (i < n && rp[r0 + i] == rp[r0 + i + 1]) done(r0 + i, 0.0);
+    sweep<G>(r0, n, false, rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+             [&](Entry e) { return (double)e.val * S[e.col]; }, done);
 }
 
 // subset k: S_i <- S_i * (sum_{j in k} b_ij ratio_j) / sens_k,i (unchanged
-// where sens_k,i = 0), over subset k's rows of the split backprojector
-// (rp = off + k n_vox: row i spans [rp[i], rp[i + 1])).
-__global__ __launch_bounds__(T256) void k_os_update(int64_t n_vox, int per, const int64_t* __restrict__ rp,
+// where sens_k,i = 0), over subset k's part of the split backprojector.
+template <int G>
+__global__ __launch_bounds__(T256) void k_os_update(int64_t n_vox, int per, int n_sub, int k,
+                                                    const int64_t* __restrict__ rp,
+                                                    const int32_t* __restrict__ offs,
                                                     const int32_t* __restrict__ col,
                                                     const float* __restrict__ val,
                                                     const double* __restrict__ ratio,
                                                     const double* __restrict__ sens_k,
                                                     double* __restrict__ S) {
-    const int64_t r0 = sweep_chunk() * per;
-    if (r0 >= n_vox) return;
-    sweep(r0, (int)std::min<int64_t>(per, n_vox - r0), rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
-          [&](Entry e) { return (double)e.val * ratio[e.col]; },
-          [&](int64_t i, double b) {
-              const double si = sens_k[i];
-              if (si > 0.0) S[i] = S[i] * b / si;
-          });
+    const int64_t c = sweep_chunk<G>();
+    if (c * per >= n_vox) return;
+    sweep_split<G>(c, k, n_vox, per, n_sub, rp, offs,
+                [&](int64_t first, int e) { return load_entry(col, val, first, e); },
+                [&](Entry e) { return (double)e.val * ratio[e.col]; },
+                [&](int64_t i, double b) {
+                    const double si = sens_k[i];
+                    if (si > 0.0) S[i] = S[i] * b / si;
+                });
 }
 
 }  // namespace
 
 
 // OSEM workspace: per-subset sensitivities, S, the ratio, the check word,
-// and the subset-split backprojector (counts, their scan and its block sums,
-// columns and values).
+// and the subset-split backprojector (row bounds, columns and values).
 struct OsemLayout {
-    size_t sens, S, ratio, st, cnt, off, bsum, col_s, val_s, total;
+    size_t sens, S, ratio, st, offs, col_s, val_s, total;
 };
 
 OsemLayout osem_layout(uint64_t n_bins, uint64_t n_vox, uint32_t n_sub, uint64_t nnz) {
@@ -1311,9 +1475,7 @@ OsemLayout osem_layout(uint64_t n_bins, uint64_t n_vox, uint32_t n_sub, uint64_t
     L.S = take(8 * n_vox);
     L.ratio = take(8 * n_bins);
     L.st = take(16);
-    L.cnt = take(4 * rows);
-    L.off = take(8 * (rows + 1));
-    L.bsum = take(8 * ((rows + 1 + SCAN_BLOCK - 1) / SCAN_BLOCK));
+    L.offs = take(8 * rows);       // (per + 1) int32 per chunk and subset: at most two per row
     L.col_s = take(4 * nnz);
     L.val_s = take(4 * nnz);
     L.total = o;
@@ -1335,36 +1497,38 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
     double* S = (double*)(w + L.S);
     double* ratio = (double*)(w + L.ratio);
     uint32_t* st = (uint32_t*)(w + L.st);
-    uint32_t* cnt = (uint32_t*)(w + L.cnt);
-    uint64_t* off = (uint64_t*)(w + L.off);
+    int32_t* offs = (int32_t*)(w + L.offs);
     int32_t* col_s = (int32_t*)(w + L.col_s);
     float* val_s = (float*)(w + L.val_s);
     const int64_t n_views = n_bins / bins_per_view;
-    const uint64_t rows = (uint64_t)n_sub * (uint64_t)n_vox;
     const int gv = grid_for((uint64_t)n_vox, T256, 8192);
-    const int gw = grid_for((uint64_t)n_vox, T256 / 64, 8192);     // one wavefront per row
-    hipError_t e;
+    const SweepPlan ps = split_plan(bt_nnz, n_bins, n_vox, n_sub);
+    const int64_t n_chunks = (n_vox + ps.per - 1) / ps.per;
+    const unsigned grid_v = sweep_grid(n_chunks, ps.threads);
+    auto ks = ps.threads == 64 ? k_os_sums<64> : k_os_sums<T256>;
+    auto ku = ps.threads == 64 ? k_os_update<64> : k_os_update<T256>;
     k_os_check<<<1, 64, 0, s>>>(n_vox, Bt_rp, bt_nnz, st);
-    k_os_split_count<<<gw, T256, 0, s>>>(n_vox, Bt_rp, Bt_col, bins_per_view, n_sub, cnt, st);
-    if ((e = exclusive_scan(cnt, rows, off, (uint64_t*)(w + L.bsum), s)) != hipSuccess) return e;
-    k_os_split_scatter<<<gw, T256, 0, s>>>(n_vox, Bt_rp, Bt_col, Bt_val, bins_per_view, n_sub, off, col_s,
-                                           val_s, st);
-    const int per_u = sweep_rows_for(bt_nnz, (int64_t)rows);
-    k_sweep_sums<<<sweep_grid(((int64_t)rows + per_u - 1) / per_u), T256, 0, s>>>((int64_t)rows, per_u,
-                                                                                 (const int64_t*)off, val_s, sens);
+    const unsigned grid_s = sweep_grid(n_chunks, T256);
+    if (ps.threads == 64)
+        k_os_split<256><<<grid_s, 256, 0, s>>>(n_vox, ps.per, Bt_rp, Bt_col, Bt_val, bins_per_view, n_sub, offs,
+                                               col_s, val_s, st);
+    else
+        k_os_split<1024><<<grid_s, 1024, 0, s>>>(n_vox, ps.per, Bt_rp, Bt_col, Bt_val, bins_per_view, n_sub, offs,
+                                                 col_s, val_s, st);
+    ks<<<dim3(grid_v, (unsigned)n_sub), T256, 0, s>>>(n_vox, ps.per, n_sub, Bt_rp, offs, val_s, sens);
     k_os_init<<<gv, T256, 0, s>>>(n_vox, n_sub, image, sens, S);
     // the entry count of c is not known here: its rows as b's
-    const int per_f = sweep_rows_for(bt_nnz, n_bins);
-    const int32_t per_view = (bins_per_view + per_f - 1) / per_f;
+    const SweepPlan pf = sweep_plan(bt_nnz / std::max<int64_t>(1, n_bins), n_bins / n_sub);
+    const int32_t per_view = (bins_per_view + pf.per - 1) / pf.per;
+    auto kf = pf.threads == 64 ? k_os_forward<64> : k_os_forward<T256>;
     for (int it = 0; it < n_iter; ++it) {
         for (int k = 0; k < n_sub; ++k) {
             const int64_t chunks = (n_views - k + n_sub - 1) / n_sub * per_view;
             if (chunks <= 0) continue;
-            k_os_forward<<<sweep_grid(chunks), T256, 0, s>>>(chunks, per_view, per_f, bins_per_view, n_sub, k, C_rp,
-                                                             C_col, C_val, S, proj, scatter, ratio);
-            k_os_update<<<sweep_grid((n_vox + per_u - 1) / per_u), T256, 0, s>>>(
-                n_vox, per_u, (const int64_t*)(off + (uint64_t)k * (uint64_t)n_vox), col_s, val_s, ratio,
-                sens + (uint64_t)k * (uint64_t)n_vox, S);
+            kf<<<sweep_grid(chunks, pf.threads), T256, 0, s>>>(chunks, per_view, pf.per, bins_per_view, n_sub, k,
+                                                               C_rp, C_col, C_val, S, proj, scatter, ratio);
+            ku<<<grid_v, T256, 0, s>>>(n_vox, ps.per, n_sub, k, Bt_rp, offs, col_s, val_s, ratio,
+                                       sens + (uint64_t)k * (uint64_t)n_vox, S);
         }
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
@@ -1531,8 +1695,10 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     // Layout: compact when the matrix is sparse (its renumbered columns fit
     // the workspace), else row order.
     const bool compact = nnz <= n_bins + n_vox;
-    const int per_b = sweep_rows_for(nnz, n_bins), per_v = sweep_rows_for(nnz, n_vox);
-    const unsigned grid_b = sweep_grid((n_bins + per_b - 1) / per_b), grid_v = sweep_grid((n_vox + per_v - 1) / per_v);
+    const SweepPlan pb = sweep_plan(nnz / std::max<int64_t>(1, n_bins), n_bins);
+    const SweepPlan pv = sweep_plan(nnz / std::max<int64_t>(1, n_vox), n_vox);
+    const unsigned grid_b = sweep_grid((n_bins + pb.per - 1) / pb.per, pb.threads);
+    const unsigned grid_v = sweep_grid((n_vox + pv.per - 1) / pv.per, pv.threads);
     int dev = 0, n_cu = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -1540,7 +1706,8 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     const int gv = grid_for(nv, T256, 8192);
     const int gr = grid_for((nb + ROW_CHUNK - 1) / ROW_CHUNK + (nv + ROW_CHUNK - 1) / ROW_CHUNK, 1, 2048);
     if (setup) {
-        k_sweep_sums<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, Tt_val, sens);
+        auto ks = pv.threads == 64 ? k_sweep_sums<64> : k_sweep_sums<T256>;
+        ks<<<grid_v, T256, 0, s>>>(n_vox, pv.per, Tt_rp, Tt_val, sens);
         k_mlem_setup<<<1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
     }
     if (compact) {
@@ -1598,9 +1765,11 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     }
     if (!iterate) return hipGetLastError();
     k_mlem_load<<<gv, T256, 0, s>>>(n_bins, n_vox, nnz, image, sens, S, nullptr, nullptr, nullptr, nullptr, st);
+    auto kf = pb.threads == 64 ? k_mlem_forward<64> : k_mlem_forward<T256>;
+    auto ku = pv.threads == 64 ? k_mlem_update<64> : k_mlem_update<T256>;
     for (int it = 0; it < n_iter; ++it) {
-        k_mlem_forward<<<grid_b, T256, 0, s>>>(n_bins, per_b, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
-        k_mlem_update<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
+        kf<<<grid_b, T256, 0, s>>>(n_bins, pb.per, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
+        ku<<<grid_v, T256, 0, s>>>(n_vox, pv.per, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
     return hipGetLastError();

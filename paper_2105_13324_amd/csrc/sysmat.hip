@@ -13,16 +13,17 @@
 // run's counts, so P = T n exactly.
 //
 // Both orientations are built as CSR (bins x voxels and voxels x bins): the
-// events are radix-sorted by (row, column), runs of equal keys merged, and
-// the weights summed as Q31.32 integers, so the result does not depend on the
-// order of the event list.
+// events are radix-sorted by (bin, voxel) and runs of equal keys merged, the
+// weights summed as Q31.32 integers, so the result does not depend on the
+// order of the event list; the merged entries are then stably sorted by voxel,
+// which gives the other orientation with the same values.
 //
 // MLEM.  S_i <- S_i / sens_i * sum_j T_ij P_j / y_j, y = T S, sens_i =
 // sum_j T_ij; FP32 matrix values, FP64 accumulation; bins with y_j = 0 add
-// nothing; voxels with sens_i = 0 stay 0.  The non-empty rows are listed
-// once per call and only they are swept, by groups of 1 to 64 lanes sized to
-// their mean length; on large detectors the backprojection works on one bin
-// slice per XCD so its gathers hit L2.
+// nothing; voxels with sens_i = 0 stay 0.  Rows of a dense matrix are streamed
+// a tile of entries at a time; of a sparse one, only the non-empty rows are
+// swept, listed once per matrix, by groups of 1 to 64 lanes sized to their
+// length.
 #include <algorithm>
 
 #include "mc_internal.h"
@@ -48,18 +49,8 @@ __device__ inline uint64_t wave_sum64(uint64_t v) {
 
 // ---- generic exclusive scan: uint32 counts -> uint64 offsets [n + 1] ----
 
-// n_dev (nullable): a device-side count below n; items from it on are taken
-// as 0 without being read, and outputs past it are not written.
-__device__ inline uint64_t scan_limit(uint64_t n, const uint64_t* n_dev) {
-    if (!n_dev) return n;
-    const uint64_t m = *n_dev;
-    return m < n ? m : n;
-}
-
-__global__ __launch_bounds__(T256) void k_sum_blocks(const uint32_t* __restrict__ in, uint64_t n_host,
-                                                     const uint64_t* __restrict__ n_dev,
+__global__ __launch_bounds__(T256) void k_sum_blocks(const uint32_t* __restrict__ in, uint64_t n,
                                                      uint64_t* __restrict__ bsum) {
-    const uint64_t n = scan_limit(n_host, n_dev);
     const uint64_t base = (uint64_t)blockIdx.x * SCAN_BLOCK;
     uint64_t s = 0;
     for (int j = threadIdx.x; j < SCAN_BLOCK; j += T256) {
@@ -102,12 +93,9 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(uint64_t* bsum, int nb) {
 }
 
 // out[i] = sum_{k<i} in[k] for i in [0, n]; out[n] = total.
-__global__ __launch_bounds__(T256) void k_scan_write(const uint32_t* __restrict__ in, uint64_t n_host,
-                                                     const uint64_t* __restrict__ n_dev,
+__global__ __launch_bounds__(T256) void k_scan_write(const uint32_t* __restrict__ in, uint64_t n,
                                                      const uint64_t* __restrict__ bsum,
                                                      uint64_t* __restrict__ out) {
-    const uint64_t n = scan_limit(n_host, n_dev);
-    if ((uint64_t)blockIdx.x * SCAN_BLOCK > n) return;   // past the limit: no output here
     const uint64_t base = (uint64_t)blockIdx.x * SCAN_BLOCK + (uint64_t)threadIdx.x * SCAN_PER;
     uint32_t v[SCAN_PER];
     uint64_t s = 0;
@@ -135,14 +123,13 @@ __global__ __launch_bounds__(T256) void k_scan_write(const uint32_t* __restrict_
     }
 }
 
-// out[i] = sum_{k<i} in[k] for i in [0, min(n, *n_dev)] (n_dev nullable).
-hipError_t exclusive_scan(const uint32_t* in, uint64_t n, uint64_t* out, uint64_t* bsum,
-                          hipStream_t s, const uint64_t* n_dev = nullptr) {
+// out[i] = sum_{k<i} in[k] for i in [0, n].
+hipError_t exclusive_scan(const uint32_t* in, uint64_t n, uint64_t* out, uint64_t* bsum, hipStream_t s) {
     // one extra item so the block holding index n writes the total
     const int nb = (int)((n + 1 + SCAN_BLOCK - 1) / SCAN_BLOCK);
-    k_sum_blocks<<<nb, T256, 0, s>>>(in, n, n_dev, bsum);
+    k_sum_blocks<<<nb, T256, 0, s>>>(in, n, bsum);
     k_scan_blocks<<<1, 1024, 0, s>>>(bsum, nb);
-    k_scan_write<<<nb, T256, 0, s>>>(in, n, n_dev, bsum, out);
+    k_scan_write<<<nb, T256, 0, s>>>(in, n, bsum, out);
     return hipGetLastError();
 }
 
@@ -150,7 +137,7 @@ hipError_t exclusive_scan(const uint32_t* in, uint64_t n, uint64_t* out, uint64_
 
 struct SysArgs {
     const mc_event* events;
-    const unsigned long long* n_events;
+    const uint64_t* n_events;
     uint64_t capacity;
     uint32_t class_mask;     // bit 0: primary events, bit 1: scattered events
     uint32_t nv_nu;          // bins per view and class
@@ -158,9 +145,10 @@ struct SysArgs {
     uint64_t q_per_view, r_extra;
 };
 
-__device__ inline uint64_t n_events_of(const SysArgs& a) {
-    const uint64_t n = *a.n_events;
-    return n < a.capacity ? n : a.capacity;
+// Items of a list whose count is on the device (it may exceed the capacity).
+__device__ inline uint64_t items_of(const uint64_t* n_p, uint64_t capacity) {
+    const uint64_t n = *n_p;
+    return n < capacity ? n : capacity;
 }
 
 // projection bin (classes merged) and image voxel of event e; false if the
@@ -182,40 +170,69 @@ __global__ __launch_bounds__(T256) void k_fill_u64(uint64_t* p, uint64_t n, uint
          i += (uint64_t)gridDim.x * T256) p[i] = v;
 }
 
-// activity per image voxel, and the total
+// Activity per image voxel (a_img, zeroed before), and the total in
+// TOTAL_SLOTS partial sums.  A workgroup takes an image row (x) and a share of
+// the f x f phantom rows behind it: a thread adds up its columns, LDS adds the f columns of an image voxel.  Bound by the read of
+// the activity: 256^3, f = 4: 376 us with an atomic per voxel, 28 us now.
+constexpr uint32_t TOTAL_SLOTS = 64;
+
 __global__ __launch_bounds__(T256) void k_image_activity(const uint32_t* __restrict__ act,
-                                                         uint32_t nx, uint32_t ny, uint32_t nz,
-                                                         uint32_t f, uint32_t mx, uint32_t my,
+                                                         uint32_t nx, uint32_t ny, uint32_t f, uint32_t mx,
+                                                         uint32_t my, uint32_t shares,
                                                          unsigned long long* __restrict__ a_img,
                                                          unsigned long long* __restrict__ total) {
-    const uint64_t n = (uint64_t)nx * ny * nz;
+    __shared__ unsigned long long acc[T256];
+    __shared__ unsigned long long part[T256 / 64];
+    const uint32_t share = blockIdx.x % shares, row = blockIdx.x / shares, jy = row % my, jz = row / my;
+    const uint32_t r0 = (uint32_t)((uint64_t)f * f * share / shares);
+    const uint32_t r1 = (uint32_t)((uint64_t)f * f * (share + 1) / shares);
+    unsigned long long* out = a_img + (uint64_t)mx * (jy + (uint64_t)my * jz);
+    // columns c0 .. c0 + w - 1 at a time: whole image voxels, or part of one
+    const uint32_t w = f >= T256 ? T256 : T256 / f * f;
     uint64_t sum = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * T256 + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * T256) {
-        const uint32_t a = act[i];
-        if (!a) continue;
-        sum += a;
-        const uint32_t ix = (uint32_t)(i % nx), iy = (uint32_t)((i / nx) % ny), iz = (uint32_t)(i / ((uint64_t)nx * ny));
-        atomicAdd(a_img + (ix / f) + mx * ((iy / f) + my * (iz / f)), (unsigned long long)a);
+    for (uint32_t c0 = 0; c0 < nx; c0 += w) {
+        const uint32_t x = c0 + threadIdx.x, first = c0 / f;
+        acc[threadIdx.x] = 0;
+        __syncthreads();
+        uint64_t t = 0;
+        if (threadIdx.x < w && x < nx)
+            for (uint32_t r = r0; r < r1; ++r)
+                t += act[x + (uint64_t)nx * (jy * f + r % f + (uint64_t)ny * (jz * f + r / f))];
+        if (t) atomicAdd(&acc[x / f - first], (unsigned long long)t);
+        sum += t;
+        __syncthreads();
+        const unsigned long long v = acc[threadIdx.x];
+        if (v) atomicAdd(out + first + threadIdx.x, v);
+        __syncthreads();
     }
     sum = wave_sum64(sum);
-    if ((threadIdx.x & 63) == 0 && sum) atomicAdd(total, (unsigned long long)sum);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long t = (part[0] + part[1]) + (part[2] + part[3]);
+        if (t) atomicAdd(total + blockIdx.x % TOTAL_SLOTS, t);
+    }
 }
 
 // ---- response matrix rows by LSD radix sort ----
 //
-// Each orientation sorts the events by the key (row << col_bits) | col with
-// a least-significant-digit radix sort (8-bit digits, stable), so a row's
-// events end up together, ordered by column, with duplicates adjacent.  A
-// pass is three launches: per-tile digit histograms (LDS counters), one
-// exclusive scan of the histograms in digit-major order (the global output
-// offset of every (digit, tile)), and a stable scatter: within a tile, items
+// The events are sorted by the key (bin << col_bits) | voxel, and the merged
+// entries by voxel, with a least-significant-digit radix sort (digits of up to
+// 8 bits, stable), so a row's items end up together, ordered by column, with
+// duplicates adjacent.  A pass is three launches: per-tile digit histograms
+// (LDS counters; of the first pass, together with the keys), for each digit
+// an exclusive scan over the tiles, and a stable scatter: within a tile, items
 // are ranked round by round (256 consecutive items), inside a wavefront by
 // matching digits with eight ballots and across the four wavefronts through
 // LDS counts.  No global atomics: the per-event atomics of a counting sort
-// contend on the rows that collect many events.  The event count is read on
+// contend on the rows that collect many events.  The item count is read on
 // the device, so nothing waits on the host; tiles past it do no work.
 // Events of a filtered class take row n_rows and sort last.
+//
+// Sorting the merged entries by voxel alone, instead of the events a second
+// time by (voxel, bin), takes 3 passes over 12-byte items for 5 over 16-byte
+// ones (1.16e7 events, 2.0e6 bins x 2.6e5 voxels: the whole build 3.2 ms as two
+// sorts of the events with scans over all digit counts, 1.2 ms now).
 
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;              // digits per pass (= T256)
@@ -241,68 +258,126 @@ __device__ inline uint32_t tile_of(uint32_t b, uint64_t n) {
     return x * per + (x < rem ? x : rem) + q;
 }
 
-__global__ __launch_bounds__(T256) void k_make_keys(SysArgs a, int transpose, uint64_t n_rows,
-                                                    int col_bits, uint64_t* __restrict__ keys,
-                                                    int64_t* __restrict__ vals) {
-    const uint64_t n = n_events_of(a);
-    for (uint64_t e = (uint64_t)blockIdx.x * T256 + threadIdx.x; e < n;
-         e += (uint64_t)gridDim.x * T256) {
-        uint32_t bin, img;
-        const mc_event ev = a.events[e];
-        if (event_rc(a, ev, bin, img)) {
-            const uint64_t r = transpose ? img : bin, c = transpose ? bin : img;
-            keys[e] = (r << col_bits) | c;
-            vals[e] = ev.weight;
-        } else {
-            keys[e] = n_rows << col_bits;
-            vals[e] = 0;
-        }
-    }
-}
-
-// hist[d * n_tiles + t]: items of tile t (one workgroup per tile) with digit d
-__global__ __launch_bounds__(T256) void k_radix_hist(const uint64_t* __restrict__ keys, SysArgs a,
-                                                     int shift, uint32_t n_tiles,
-                                                     uint32_t* __restrict__ hist) {
+// Keys and weights of the events, with the first pass's histogram (as
+// k_radix_hist).
+__global__ __launch_bounds__(T256) void k_make_keys(SysArgs a, uint64_t n_rows, int col_bits, uint32_t mask,
+                                                    uint32_t n_tiles, uint64_t* __restrict__ keys,
+                                                    int64_t* __restrict__ vals, uint32_t* __restrict__ hist) {
     __shared__ uint32_t cnt[RADIX];
-    const uint64_t n = n_events_of(a);
-    cnt[threadIdx.x] = 0;
-    __syncthreads();
+    const uint64_t n = items_of(a.n_events, a.capacity);
     const uint32_t tile = tile_of(blockIdx.x, n);
     const uint64_t base = (uint64_t)tile * RADIX_TILE;
+    if (base >= n) return;       // an empty tile (the whole workgroup leaves)
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll 4
     for (int j = 0; j < RADIX_ITEMS; ++j) {
-        const uint64_t i = base + (uint64_t)j * T256 + threadIdx.x;
-        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (RADIX - 1)], 1u);
+        const uint64_t e = base + (uint64_t)j * T256 + threadIdx.x;
+        if (e >= n) break;
+        uint32_t bin, img;
+        const mc_event ev = a.events[e];
+        uint64_t k = n_rows << col_bits;
+        int64_t v = 0;
+        if (event_rc(a, ev, bin, img)) {
+            k = ((uint64_t)bin << col_bits) | img;
+            v = ev.weight;
+        }
+        keys[e] = k;
+        vals[e] = v;
+        atomicAdd(&cnt[(uint32_t)k & mask], 1u);
     }
     __syncthreads();
     hist[(uint64_t)threadIdx.x * n_tiles + tile] = cnt[threadIdx.x];
 }
 
-// Stable scatter of tile t's items to offs[d * n_tiles + t] + their rank
-// among the tile's items of digit d.  Each wavefront takes a quarter of the
-// tile (1024 consecutive items, 16 per lane, loaded at once) and ranks it on
-// its own, 64 items per round: lanes with equal digits found with eight
-// ballots, and a running count per digit kept in the wavefront's row of LDS.
-// After one barrier, the earlier wavefronts' counts place each item in a
-// digit-ordered copy of the tile in LDS (keys, then values through the same
-// 32 KB), which is written out so that each digit's run from this tile (16
-// items on average) goes to consecutive addresses.
+// hist[d * n_tiles + t]: items of tile t (one workgroup per tile) with digit d
+template <class Key>
+__global__ __launch_bounds__(T256) void k_radix_hist(const Key* __restrict__ keys, const uint64_t* __restrict__ n_p,
+                                                     uint64_t capacity, int shift, uint32_t mask,
+                                                     uint32_t n_tiles, uint32_t* __restrict__ hist) {
+    __shared__ uint32_t cnt[RADIX];
+    const uint64_t n = items_of(n_p, capacity);
+    const uint32_t tile = tile_of(blockIdx.x, n);
+    const uint64_t base = (uint64_t)tile * RADIX_TILE;
+    if (base >= n) return;
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    Key k[RADIX_ITEMS];
+#pragma unroll
+    for (int j = 0; j < RADIX_ITEMS; ++j) {
+        const uint64_t i = base + (uint64_t)j * T256 + threadIdx.x;
+        k[j] = keys[i < n ? i : n - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < RADIX_ITEMS; ++j) {
+        const uint64_t i = base + (uint64_t)j * T256 + threadIdx.x;
+        if (i < n) atomicAdd(&cnt[(uint32_t)(k[j] >> shift) & mask], 1u);
+    }
+    __syncthreads();
+    hist[(uint64_t)threadIdx.x * n_tiles + tile] = cnt[threadIdx.x];
+}
+
+// Exclusive scan of digit blockIdx.x's counts over the tiles that hold items,
+// in place, and the digit's total.  (A scan over all digits and tiles of the
+// list's capacity was three launches and 39 us for 3e7 slots; 5 us now.)
+__global__ __launch_bounds__(1024) void k_digit_scan(const uint64_t* __restrict__ n_p, uint64_t capacity,
+                                                     uint32_t n_tiles, uint32_t* __restrict__ hist,
+                                                     uint32_t* __restrict__ tot) {
+    __shared__ uint32_t part[16];
+    const uint64_t n = items_of(n_p, capacity);
+    const uint32_t used = (uint32_t)((n + RADIX_TILE - 1) / RADIX_TILE);
+    uint32_t* __restrict__ h = hist + (uint64_t)blockIdx.x * n_tiles;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t run = 0;
+    for (uint32_t t0 = 0; t0 < used; t0 += 1024) {
+        const uint32_t t = t0 + threadIdx.x, c = t < used ? h[t] : 0u;
+        uint32_t x = c;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) part[wave] = x;
+        __syncthreads();
+        uint32_t before = run, all = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) before += part[w];
+            all += part[w];
+        }
+        if (t < used) h[t] = before + x - c;
+        run += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) tot[blockIdx.x] = run;
+}
+
+// Stable scatter of tile t's items to the digit's first slot + the scan of its
+// counts at t + their rank among the tile's items of the digit.  Each wavefront
+// takes a quarter of the tile (1024 consecutive items, 16 per lane, loaded at
+// once) and ranks it on its own, 64 items per round: lanes with equal digits
+// found with eight ballots, and a running count per digit kept in the
+// wavefront's row of LDS.  After one barrier, the earlier wavefronts' counts
+// place each item in a digit-ordered copy of the tile in LDS (keys, then
+// values through the same 32 KB), which is written out so that each digit's
+// run from this tile (16 items on average) goes to consecutive addresses.
+// Bound by reading and writing the items.  col (nullable): the last pass of the
+// entries' sort writes the two halves of a value to col and val.
 constexpr uint32_t RADIX_WAVE_ITEMS = (uint32_t)(RADIX_TILE / (T256 / 64));
 
-__global__ __launch_bounds__(T256) void k_radix_scatter(const uint64_t* __restrict__ kin,
-                                                        const int64_t* __restrict__ vin,
-                                                        uint64_t* __restrict__ kout,
-                                                        int64_t* __restrict__ vout, SysArgs a,
-                                                        int shift, uint32_t n_tiles,
+template <class Key>
+__global__ __launch_bounds__(T256) void k_radix_scatter(const Key* __restrict__ kin,
+                                                        const uint64_t* __restrict__ vin,
+                                                        Key* __restrict__ kout, uint64_t* __restrict__ vout,
+                                                        int32_t* __restrict__ col, float* __restrict__ val,
+                                                        const uint64_t* __restrict__ n_p, uint64_t capacity,
+                                                        int shift, uint32_t mask, uint32_t n_tiles,
                                                         const uint32_t* __restrict__ hist,
-                                                        const uint64_t* __restrict__ offs) {
+                                                        const uint32_t* __restrict__ tot) {
     __shared__ uint64_t stage[RADIX_TILE];         // the tile's keys, then values, in digit order
-    __shared__ uint16_t sdig[RADIX_TILE];          // the digit of each staged slot
-    __shared__ uint64_t gbase[RADIX];              // global slot of each digit's first item
+    __shared__ uint32_t gbase[RADIX];              // global slot of each digit's first item, less its tile slot
     __shared__ uint32_t lstart[RADIX];             // tile slot of each digit's first item
     __shared__ uint32_t wcnt[T256 / 64][RADIX];    // items of each digit per wavefront
-    __shared__ uint32_t wsum[T256 / 64];
-    const uint64_t n = n_events_of(a);
+    __shared__ uint2 wsum[T256 / 64];
+    const uint64_t n = items_of(n_p, capacity);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t lane_lt = (1ull << lane) - 1ull;
     const uint32_t tile = tile_of(blockIdx.x, n);
@@ -310,30 +385,34 @@ __global__ __launch_bounds__(T256) void k_radix_scatter(const uint64_t* __restri
     if (base >= n) return;       // an empty tile (the whole workgroup leaves)
     const uint64_t wbase = base + (uint64_t)wave * RADIX_WAVE_ITEMS;
 
-    uint64_t k[RADIX_ITEMS];
-    int64_t v[RADIX_ITEMS];
+    Key k[RADIX_ITEMS];
+    uint64_t v[RADIX_ITEMS];
 #pragma unroll
     for (int j = 0; j < RADIX_ITEMS; ++j) {
         const uint64_t i = wbase + (uint64_t)j * 64 + lane;
         k[j] = i < n ? kin[i] : 0;
         v[j] = i < n ? vin[i] : 0;
     }
-    // tile slots: exclusive scan of this tile's digit counts
-    const uint32_t c = hist[(uint64_t)threadIdx.x * n_tiles + tile];
-    gbase[threadIdx.x] = offs[(uint64_t)threadIdx.x * n_tiles + tile];
+    // this thread's digit: its items in the tile, in earlier tiles, and in all;
+    // exclusive scans of the first (tile slots) and the last (global slots)
+    const uint32_t* h = hist + (uint64_t)threadIdx.x * n_tiles + tile;
+    const uint32_t all = tot[threadIdx.x], before_t = h[0];
+    const uint32_t c = (base + RADIX_TILE < n ? h[1] : all) - before_t;
 #pragma unroll
     for (int w = 0; w < T256 / 64; ++w) wcnt[w][threadIdx.x] = 0;
-    uint32_t x = c;
+    uint32_t x = c, g = all;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+        const uint32_t y = __shfl_up(x, o, 64), z = __shfl_up(g, o, 64);
+        if (lane >= o) { x += y; g += z; }
     }
-    if (lane == 63) wsum[wave] = x;
+    if (lane == 63) wsum[wave] = uint2{x, g};
     __syncthreads();
-    uint32_t pre = 0;
-    for (int w = 0; w < wave; ++w) pre += wsum[w];
-    lstart[threadIdx.x] = pre + x - c;
+    x -= c;
+    g -= all;
+    for (int w = 0; w < wave; ++w) { x += wsum[w].x; g += wsum[w].y; }
+    lstart[threadIdx.x] = x;
+    gbase[threadIdx.x] = g + before_t - x;
 
     // rank within this wavefront: items of the same digit in earlier rounds
     // (the running count) plus lower lanes of this round
@@ -341,7 +420,7 @@ __global__ __launch_bounds__(T256) void k_radix_scatter(const uint64_t* __restri
 #pragma unroll
     for (int j = 0; j < RADIX_ITEMS; ++j) {
         const bool ok = wbase + (uint64_t)j * 64 + lane < n;
-        const uint32_t d = ok ? (uint32_t)(k[j] >> shift) & (RADIX - 1) : 0;
+        const uint32_t d = ok ? (uint32_t)(k[j] >> shift) & mask : 0;
         uint64_t peers = __ballot(ok);
 #pragma unroll
         for (int b = 0; b < RADIX_BITS; ++b) {
@@ -356,126 +435,239 @@ __global__ __launch_bounds__(T256) void k_radix_scatter(const uint64_t* __restri
     }
     __syncthreads();
     // tile slots of this lane's items (kept for the second staging)
+    Key* const kstage = (Key*)stage;
     uint32_t slot[RADIX_ITEMS];
 #pragma unroll
     for (int j = 0; j < RADIX_ITEMS; ++j) {
         slot[j] = RADIX_TILE;
         if (wbase + (uint64_t)j * 64 + lane >= n) continue;
-        const uint32_t d = (uint32_t)(k[j] >> shift) & (RADIX - 1);
+        const uint32_t d = (uint32_t)(k[j] >> shift) & mask;
         uint32_t sl = lstart[d] + rk[j];
         for (int w = 0; w < wave; ++w) sl += wcnt[w][d];
         slot[j] = sl;
-        if (sl < RADIX_TILE) {
-            stage[sl] = k[j];
-            sdig[sl] = (uint16_t)d;
-        }
+        if (sl < RADIX_TILE) kstage[sl] = k[j];
     }
     __syncthreads();
-    const uint64_t in_tile = n - base < RADIX_TILE ? n - base : RADIX_TILE;
-    for (uint32_t t = threadIdx.x; t < in_tile; t += T256) {
-        const uint32_t d = sdig[t];
-        const uint64_t pos = gbase[d] + (t - lstart[d]);
-        if (pos < a.capacity) kout[pos] = stage[t];
+    // global slots of the tile slots this thread writes out
+    const uint32_t in_tile = (uint32_t)(n - base < RADIX_TILE ? n - base : RADIX_TILE);
+    uint32_t pos[RADIX_ITEMS];
+#pragma unroll
+    for (int j = 0; j < RADIX_ITEMS; ++j) {
+        const uint32_t t = (uint32_t)j * T256 + threadIdx.x;
+        pos[j] = UINT32_MAX;
+        if (t < in_tile) {
+            const Key key = kstage[t];
+            const uint32_t p = gbase[(uint32_t)(key >> shift) & mask] + t;
+            if (p < capacity) {
+                pos[j] = p;
+                kout[p] = key;
+            }
+        }
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < RADIX_ITEMS; ++j)
-        if (slot[j] < RADIX_TILE) stage[slot[j]] = (uint64_t)v[j];
+        if (slot[j] < RADIX_TILE) stage[slot[j]] = v[j];
     __syncthreads();
-    for (uint32_t t = threadIdx.x; t < in_tile; t += T256) {
-        const uint32_t d = sdig[t];
-        const uint64_t pos = gbase[d] + (t - lstart[d]);
-        if (pos < a.capacity) vout[pos] = (int64_t)stage[t];
-    }
-}
-
-// start[r] (r = 0..n_rows): first sorted position whose row is >= r (a
-// binary search, so start is non-decreasing and within [0, n] whatever the
-// keys hold); the filtered events (row n_rows) follow start[n_rows].
-__global__ __launch_bounds__(T256) void k_row_starts(const uint64_t* __restrict__ keys, SysArgs a,
-                                                     int col_bits, uint64_t n_rows,
-                                                     uint64_t* __restrict__ start) {
-    const uint64_t n = n_events_of(a);
-    for (uint64_t r = (uint64_t)blockIdx.x * T256 + threadIdx.x; r <= n_rows;
-         r += (uint64_t)gridDim.x * T256) {
-        const uint64_t key = r << col_bits;
-        uint64_t lo = 0, hi = n;
-        while (lo < hi) {
-            const uint64_t mid = (lo + hi) >> 1;
-            if (keys[mid] < key) lo = mid + 1; else hi = mid;
+#pragma unroll
+    for (int j = 0; j < RADIX_ITEMS; ++j) {
+        const uint32_t t = (uint32_t)j * T256 + threadIdx.x;
+        if (pos[j] == UINT32_MAX) continue;
+        const uint64_t x = stage[t];
+        if (col) {
+            col[pos[j]] = (int32_t)(uint32_t)x;
+            val[pos[j]] = __uint_as_float((uint32_t)(x >> 32));
+        } else {
+            vout[pos[j]] = x;
         }
-        start[r] = lo;
     }
 }
 
-// flag[i] = 1 where a run of equal keys starts, for the valid (unfiltered)
-// items i < start[n_rows] (the scan below reads no further)
-__global__ __launch_bounds__(T256) void k_run_heads(const uint64_t* __restrict__ keys,
-                                                    const uint64_t* __restrict__ start,
-                                                    uint64_t n_rows, uint64_t capacity,
-                                                    uint32_t* __restrict__ flag) {
-    const uint64_t n_valid = start[n_rows] < capacity ? start[n_rows] : capacity;
-    for (uint64_t i = (uint64_t)blockIdx.x * T256 + threadIdx.x; i < n_valid;
-         i += (uint64_t)gridDim.x * T256)
-        flag[i] = i == 0 || keys[i] != keys[i - 1];
+// Merging of the sorted events, a tile of RUN_TILE per workgroup.
+constexpr int RUN_ITEMS = 8;
+constexpr int RUN_TILE = T256 * RUN_ITEMS;
+
+// cnt[t]: runs of equal keys that start in tile t, of the unfiltered events
+// (0 for tiles past the count)
+__global__ __launch_bounds__(T256) void k_count_runs(const uint64_t* __restrict__ keys, SysArgs a,
+                                                     uint64_t n_rows, int col_bits, uint32_t* __restrict__ cnt) {
+    __shared__ uint32_t part[T256 / 64];
+    const uint64_t n = items_of(a.n_events, a.capacity), end = n_rows << col_bits;
+    const uint64_t base = (uint64_t)blockIdx.x * RUN_TILE;
+    uint32_t c = 0;
+    if (base < n) {
+#pragma unroll
+        for (int u = 0; u < RUN_ITEMS; ++u) {
+            const uint64_t i = base + (uint64_t)u * T256 + threadIdx.x, j = i < n ? i : n - 1;
+            const uint64_t k = keys[j], p = keys[j ? j - 1 : 0];
+            c += (uint32_t)__popcll(__ballot(i < n && k < end && (i == 0 || k != p)));
+        }
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
-// rowptr[r] = distinct entries before row r (head_pos: exclusive scan of the run heads)
-__global__ __launch_bounds__(T256) void k_rows_from_runs(const uint64_t* __restrict__ start,
-                                                         const uint64_t* __restrict__ head_pos,
-                                                         uint64_t n_rows, int64_t* __restrict__ rowptr) {
-    for (uint64_t r = (uint64_t)blockIdx.x * T256 + threadIdx.x; r <= n_rows;
-         r += (uint64_t)gridDim.x * T256)
-        rowptr[r] = (int64_t)head_pos[start[r]];
-}
-
-// Each run of equal keys (one distinct (row, column)) becomes CSR entry
-// head_pos[i] of its first item i: the column and T = c / n_i(j), with c the
-// run's summed weight.
-__global__ __launch_bounds__(T256) void k_emit_runs(SysArgs a, int transpose,
-                                                    const uint64_t* __restrict__ keys,
+// The runs that start in a tile (one distinct (bin, voxel) each) become the
+// entries first[tile], ...: the column and T = c / n_i(j), with c the run's
+// summed weight, and pair = bin | value << 32 for the other orientation.
+// acc[bin] (nullable, zeroed before) collects the weights of a bin.  A thread
+// takes eight consecutive events from LDS; scans over the tile number its runs
+// and add up the weights, so a run's or a bin's sum is a difference of two
+// prefix sums (modulo 2^64, exact), and runs and bins are then taken one per
+// thread, with coalesced writes.  A run that goes on past the tile is summed to
+// its end by the whole workgroup, and bins cut by the tile's ends are added
+// atomically.  Bound by the read of the events and the write of the entries.
+// (Flags, a scan over them, a thread per run and one per bin, each reading its
+// own events: 270 us for 1.16e7 events; 156 us now with k_count_runs.)
+__global__ __launch_bounds__(T256) void k_emit_runs(SysArgs a, const uint64_t* __restrict__ keys,
                                                     const int64_t* __restrict__ w,
-                                                    const uint64_t* __restrict__ start,
-                                                    const uint64_t* __restrict__ head_pos,
-                                                    uint64_t n_rows, int col_bits,
-                                                    int32_t* __restrict__ col, float* __restrict__ val,
+                                                    const uint64_t* __restrict__ first, uint64_t n_rows,
+                                                    int col_bits, int32_t* __restrict__ col,
+                                                    float* __restrict__ val, uint64_t* __restrict__ pair,
+                                                    unsigned long long* __restrict__ acc,
                                                     const unsigned long long* __restrict__ a_img,
                                                     const unsigned long long* __restrict__ total_p) {
-    const uint64_t n_valid = start[n_rows];
-    const double total = (double)*total_p;
-    const uint64_t mask = (1ull << col_bits) - 1ull;
+    // one slot of padding per thread's eight: its reads spread over the banks
+    constexpr int PAD = RUN_TILE + RUN_TILE / RUN_ITEMS + 1;
+    __shared__ uint64_t key_s[PAD];
+    __shared__ uint64_t sum_s[PAD];                // weights, then their exclusive prefix sums
+    __shared__ uint16_t run_at[RUN_TILE + 1];      // the tile's runs, and bins, by their first event
+    __shared__ uint16_t bin_at[RUN_TILE + 1];
+    __shared__ uint32_t part_n[T256 / 64];
+    __shared__ uint64_t part_w[T256 / 64];
+    const auto at = [](int i) { return i + i / RUN_ITEMS; };
+    const uint64_t n = items_of(a.n_events, a.capacity), end = n_rows << col_bits;
+    const uint64_t base = (uint64_t)blockIdx.x * RUN_TILE;
+    if (base >= n) return;
+    const int m = (int)(n - base < RUN_TILE ? n - base : RUN_TILE);
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // a list that lost events (count above the capacity) gives no matrix
     const bool lost = *a.n_events > a.capacity;
-    for (uint64_t i = (uint64_t)blockIdx.x * T256 + threadIdx.x; i < n_valid;
-         i += (uint64_t)gridDim.x * T256) {
-        const uint64_t k = keys[i];
-        if (i > 0 && keys[i - 1] == k) continue;
-        long long cw = 0;
-        for (uint64_t j = i; j < n_valid && keys[j] == k; ++j) cw += w[j];
-        const uint32_t r = (uint32_t)(k >> col_bits), c = (uint32_t)(k & mask);
-        const uint32_t bin = transpose ? c : r;
-        const uint32_t img = transpose ? r : c;
-        const uint64_t view = bin / a.nv_nu;
+    const double total = (double)wave_sum64(total_p[lane]);
+    static_assert(TOTAL_SLOTS == 64, "a lane per partial sum");
+    const uint64_t before = base ? keys[base - 1] : ~0ull;
+#pragma unroll
+    for (int u = 0; u < RUN_ITEMS; ++u) {
+        const int i = u * T256 + tid;
+        if (i < m) {
+            key_s[at(i)] = keys[base + i];
+            sum_s[at(i)] = (uint64_t)w[base + i];
+        }
+    }
+    __syncthreads();
+    // low half: runs, high half: bins
+    uint32_t flags[RUN_ITEMS], mine = 0;
+    uint64_t pre[RUN_ITEMS], sum = 0;
+    uint64_t prev = tid == 0 ? before : key_s[at(tid * RUN_ITEMS - 1)];
+#pragma unroll
+    for (int u = 0; u < RUN_ITEMS; ++u) {
+        const int i = tid * RUN_ITEMS + u;
+        const bool in = i < m;
+        const uint64_t k = in ? key_s[at(i)] : prev;
+        flags[u] = (k != prev ? 1u : 0u) | (in && (i == 0 || k >> col_bits != prev >> col_bits) ? 0x10000u : 0u);
+        pre[u] = sum;
+        sum += in ? sum_s[at(i)] : 0;
+        mine += flags[u];
+        prev = k;
+    }
+    uint32_t x = mine;
+    uint64_t y = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t p = __shfl_up(x, o, 64);
+        const uint64_t q = __shfl_up(y, o, 64);
+        if (lane >= o) { x += p; y += q; }
+    }
+    if (lane == 63) {
+        part_n[wave] = x;
+        part_w[wave] = y;
+    }
+    __syncthreads();
+    x -= mine;
+    y -= sum;
+    uint32_t tot_n = 0;
+    uint64_t tot_w = 0;
+    for (int v = 0; v < T256 / 64; ++v) {
+        if (v < wave) { x += part_n[v]; y += part_w[v]; }
+        tot_n += part_n[v];
+        tot_w += part_w[v];
+    }
+    const int n_run = (int)(tot_n & 0xFFFFu), n_bin = (int)(tot_n >> 16);
+#pragma unroll
+    for (int u = 0; u < RUN_ITEMS; ++u) {
+        const int i = tid * RUN_ITEMS + u;
+        if (flags[u] & 1u) run_at[x & 0xFFFFu] = (uint16_t)i;
+        if (flags[u] >> 16) bin_at[x >> 16] = (uint16_t)i;
+        x += flags[u];
+        if (i < m) sum_s[at(i)] = y + pre[u];
+    }
+    if (tid == 0) {
+        run_at[n_run] = (uint16_t)m;
+        bin_at[n_bin] = (uint16_t)m;
+        sum_s[at(m)] = tot_w;
+    }
+    __syncthreads();
+    // the rest of the last run, past the tile
+    uint64_t extra = 0;
+    const uint64_t last = key_s[at(m - 1)];
+    if (n_run > 0 && last < end && base + RUN_TILE < n && keys[base + RUN_TILE] == last) {
+        for (uint64_t p = base + RUN_TILE; p < n; p += T256) {
+            const bool same = p + tid < n && keys[p + tid] == last;
+            if (same) extra += (uint64_t)w[p + tid];
+            if (!__syncthreads_and(same)) break;
+        }
+        extra = wave_sum64(extra);
+        if (lane == 0) part_w[wave] = extra;
+        __syncthreads();
+        extra = (part_w[0] + part_w[1]) + (part_w[2] + part_w[3]);
+    }
+    const uint64_t o0 = first[blockIdx.x], mask = (1ull << col_bits) - 1ull;
+    for (int q = tid; q < n_run; q += T256) {
+        const int i = run_at[q], j = run_at[q + 1];
+        const uint64_t k = key_s[at(i)];
+        if (k >= end) break;
+        const long long cw = (long long)(sum_s[at(j)] - sum_s[at(i)] + (q == n_run - 1 ? extra : 0));
+        const uint32_t bin = (uint32_t)(k >> col_bits), img = (uint32_t)(k & mask);
+        const uint32_t view = bin / a.nv_nu;
         const double n_view = (double)(a.q_per_view + (view < a.r_extra ? 1u : 0u));
         const double n_i = n_view * (double)a_img[img] / total;
-        const uint64_t o = head_pos[i];
-        col[o] = (int32_t)c;
-        val[o] = lost ? __builtin_nanf("") : (float)((double)cw * 0x1p-32 / n_i);
+        const float t = lost ? __builtin_nanf("") : (float)((double)cw * 0x1p-32 / n_i);
+        col[o0 + q] = (int32_t)img;
+        val[o0 + q] = t;
+        pair[o0 + q] = bin | (uint64_t)__float_as_uint(t) << 32;
+    }
+    if (!acc) return;
+    for (int q = tid; q < n_bin; q += T256) {
+        const int i = bin_at[q], j = bin_at[q + 1];
+        const uint64_t bin = key_s[at(i)] >> col_bits;
+        if (bin >= n_rows) break;
+        const unsigned long long c = sum_s[at(j)] - sum_s[at(i)];
+        if (q > 0 && q < n_bin - 1) acc[bin] = c;
+        else if (c) atomicAdd(acc + bin, c);
     }
 }
 
-// P_j = the summed weight of bin row j's events (all its items); NaN when
-// the list lost events
-__global__ __launch_bounds__(T256) void k_proj_rows(const int64_t* __restrict__ w,
-                                                    const uint64_t* __restrict__ start,
-                                                    uint64_t n_rows, const unsigned long long* n_events,
-                                                    uint64_t capacity, float* __restrict__ proj) {
-    const bool lost = *n_events > capacity;
-    for (uint64_t r = (uint64_t)blockIdx.x * T256 + threadIdx.x; r < n_rows;
+// rowptr[r] (r = 0..n_rows): first of the nnz entries, sorted by row, whose row
+// is >= r (a binary search: non-decreasing and within [0, nnz] whatever the
+// rows hold).  With proj: P_r = the summed weight of bin r's events; NaN when
+// the list lost events.
+template <class Row>
+__global__ __launch_bounds__(T256) void k_row_ptr(const Row* __restrict__ rows, const uint64_t* __restrict__ nnz,
+                                                  uint64_t capacity, uint64_t n_rows,
+                                                  int64_t* __restrict__ rowptr, const int64_t* __restrict__ acc,
+                                                  const uint64_t* __restrict__ n_events,
+                                                  float* __restrict__ proj) {
+    const uint64_t n = items_of(nnz, capacity);
+    const bool lost = proj && *n_events > capacity;
+    for (uint64_t r = (uint64_t)blockIdx.x * T256 + threadIdx.x; r <= n_rows;
          r += (uint64_t)gridDim.x * T256) {
-        long long tot = 0;
-        for (uint64_t i = start[r]; i < start[r + 1]; ++i) tot += w[i];
-        proj[r] = lost ? __builtin_nanf("") : (float)((double)tot * 0x1p-32);
+        uint32_t lo = 0, hi = (uint32_t)n;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if ((uint32_t)rows[mid] < r) lo = mid + 1; else hi = mid;
+        }
+        rowptr[r] = (int64_t)lo;
+        if (proj && r < n_rows) proj[r] = lost ? __builtin_nanf("") : (float)((double)acc[r] * 0x1p-32);
     }
 }
 
@@ -1537,42 +1729,55 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
 
 // Workspace of the response-matrix build (layout in sysmat_layout).
 struct SysLayout {
-    uint64_t* start;       // [nr + 1] row starts in the sorted items
+    uint32_t* hist;        // [RADIX * n_tiles] digit histograms, then their scans
+    uint32_t* tot;         // [RADIX] digit totals
+    uint32_t* cnt;         // [n_runs] runs per tile of the sorted events
+    uint64_t* first;       // [n_runs + 1] their exclusive scan; the last: nnz
     uint64_t* bsum;        // scan block sums
-    uint32_t* hist;        // [RADIX * n_tiles] digit histograms
-    uint64_t* offs;        // [RADIX * n_tiles + 1] their exclusive scan
-    uint64_t* keys[2];     // [cap + 1] sort keys (double buffer; the spare one
-                           //  then holds the run-head positions)
-    int64_t* vals[2];      // [cap] weights, Q31.32
-    uint32_t* flag;        // [cap] run heads
-    unsigned long long* a_img;   // [n_img + 1] activity per image voxel, then the total
+    uint64_t* keys[2];     // [cap] sort keys (double buffer), then the entries' 32-bit keys
+    uint64_t* vals[2];     // [cap] weights, Q31.32, then the entries' (bin, value) pairs
+    unsigned long long* a_img;   // [n_img] activity per image voxel
+    unsigned long long* total;   // [TOTAL_SLOTS] partial sums of the activity
+    unsigned long long* acc;     // [n_bins] summed weight per bin
+    uint32_t n_tiles, n_runs;
     size_t bytes;
 };
 
 SysLayout sysmat_layout(char* w, uint64_t n_bins, uint64_t n_img, uint64_t capacity) {
     auto al = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
-    const uint64_t nr = n_bins > n_img ? n_bins : n_img;
     const uint64_t cap = capacity ? capacity : 1;
-    const uint64_t n_tiles = (cap + RADIX_TILE - 1) / RADIX_TILE;
-    uint64_t scan_n = nr;
-    if (cap > scan_n) scan_n = cap;
-    if (RADIX * n_tiles > scan_n) scan_n = RADIX * n_tiles;
-    const uint64_t nb = (scan_n + 1 + SCAN_BLOCK - 1) / SCAN_BLOCK;
     SysLayout L;
+    L.n_tiles = (uint32_t)((cap + RADIX_TILE - 1) / RADIX_TILE);
+    L.n_runs = (uint32_t)((cap + RUN_TILE - 1) / RUN_TILE);
     char* p = w;
     auto take = [&](uint64_t bytes) { char* q = p; p += al(bytes); return q; };
-    L.start = (uint64_t*)take(8 * (nr + 1));
-    L.bsum = (uint64_t*)take(8 * nb);
-    L.hist = (uint32_t*)take(4 * RADIX * n_tiles);
-    L.offs = (uint64_t*)take(8 * (RADIX * n_tiles + 1));
-    L.keys[0] = (uint64_t*)take(8 * (cap + 1));
-    L.keys[1] = (uint64_t*)take(8 * (cap + 1));
-    L.vals[0] = (int64_t*)take(8 * cap);
-    L.vals[1] = (int64_t*)take(8 * cap);
-    L.flag = (uint32_t*)take(4 * cap);
-    L.a_img = (unsigned long long*)take(8 * (n_img + 1));
+    L.hist = (uint32_t*)take(4ull * RADIX * L.n_tiles);
+    L.tot = (uint32_t*)take(4 * RADIX);
+    L.cnt = (uint32_t*)take(4ull * L.n_runs);
+    L.first = (uint64_t*)take(8 * (L.n_runs + 1ull));
+    L.bsum = (uint64_t*)take(8 * (L.n_runs / SCAN_BLOCK + 1ull));
+    L.keys[0] = (uint64_t*)take(8 * cap);
+    L.keys[1] = (uint64_t*)take(8 * cap);
+    L.vals[0] = (uint64_t*)take(8 * cap);
+    L.vals[1] = (uint64_t*)take(8 * cap);
+    // zeroed together: one array
+    L.a_img = (unsigned long long*)take(8 * (n_img + TOTAL_SLOTS + n_bins));
+    L.total = L.a_img + n_img;
+    L.acc = L.total + TOTAL_SLOTS;
     L.bytes = (size_t)(p - w);
     return L;
+}
+
+// Digits of a sort over `bits` bits: the fewest passes, of equal widths.
+struct Digits {
+    int passes, bits;
+    uint32_t mask() const { return (1u << bits) - 1u; }
+};
+Digits digits_of(int bits) {
+    Digits d;
+    d.passes = (bits + RADIX_BITS - 1) / RADIX_BITS;
+    d.bits = (bits + d.passes - 1) / d.passes;
+    return d;
 }
 
 size_t sysmat_workspace_bytes(uint64_t n_bins, uint64_t n_img, uint64_t capacity) {
@@ -1589,54 +1794,65 @@ hipError_t launch_sysmat(const mc_event* events, const unsigned long long* n_eve
     const uint32_t mx = nx / f, my = ny / f, mz = nz / f;
     const uint64_t n_img = (uint64_t)mx * my * mz;
     const SysLayout L = sysmat_layout((char*)workspace, n_bins, n_img, capacity);
-    const uint64_t cap = capacity ? capacity : 1;
-    const uint32_t n_tiles = (uint32_t)((cap + RADIX_TILE - 1) / RADIX_TILE);
-    unsigned long long* a_img = L.a_img;
-    unsigned long long* total = a_img + n_img;
+    const uint64_t* n_ev = (const uint64_t*)n_events;
 
     SysArgs a;
-    a.events = events; a.n_events = n_events; a.capacity = capacity;
+    a.events = events; a.n_events = n_ev; a.capacity = capacity;
     a.class_mask = class_mask;
     a.nv_nu = nu * nv;
     a.nx = nx; a.ny = ny; a.f = f; a.mx = mx; a.my = my;
     a.q_per_view = n_hist / n_views; a.r_extra = n_hist % n_views;
 
-    k_fill_u64<<<grid_for(n_img + 1, T256, 4096), T256, 0, s>>>((uint64_t*)a_img, n_img + 1, 0);
-    k_image_activity<<<grid_for((uint64_t)nx * ny * nz, T256, 8192), T256, 0, s>>>(
-        activity, nx, ny, nz, f, mx, my, a_img, total);
-    const int ge = grid_for(cap, T256, 8192);
-    for (int transpose = 0; transpose < 2; ++transpose) {
-        const uint64_t n_rows = transpose ? n_img : n_bins;
-        const uint64_t n_cols = transpose ? n_bins : n_img;
-        // rows 0..n_rows (n_rows: filtered events), columns 0..n_cols - 1
-        const int col_bits = std::max(1, bit_width(n_cols - 1));
-        const int key_bits = col_bits + bit_width(n_rows);
-        k_make_keys<<<ge, T256, 0, s>>>(a, transpose, n_rows, col_bits, L.keys[0], L.vals[0]);
-        int cur = 0;
-        for (int shift = 0; shift < key_bits; shift += RADIX_BITS) {
-            k_radix_hist<<<n_tiles, T256, 0, s>>>(L.keys[cur], a, shift, n_tiles, L.hist);
-            hipError_t e = exclusive_scan(L.hist, (uint64_t)RADIX * n_tiles, L.offs, L.bsum, s);
-            if (e != hipSuccess) return e;
-            k_radix_scatter<<<n_tiles, T256, 0, s>>>(L.keys[cur], L.vals[cur], L.keys[cur ^ 1],
-                                                     L.vals[cur ^ 1], a, shift, n_tiles, L.hist, L.offs);
-            cur ^= 1;
-        }
-        const uint64_t* keys = L.keys[cur];
-        const int64_t* w = L.vals[cur];
-        uint64_t* head_pos = L.keys[cur ^ 1];
-        k_row_starts<<<grid_for(n_rows + 1, T256, 8192), T256, 0, s>>>(keys, a, col_bits, n_rows, L.start);
-        k_run_heads<<<ge, T256, 0, s>>>(keys, L.start, n_rows, cap, L.flag);
-        hipError_t e = exclusive_scan(L.flag, cap, head_pos, L.bsum, s, L.start + n_rows);
-        if (e != hipSuccess) return e;
-        k_rows_from_runs<<<grid_for(n_rows + 1, T256, 8192), T256, 0, s>>>(
-            L.start, head_pos, n_rows, transpose ? Tt_rp : T_rp);
-        k_emit_runs<<<ge, T256, 0, s>>>(a, transpose, keys, w, L.start, head_pos, n_rows, col_bits,
-                                        transpose ? Tt_col : T_col, transpose ? Tt_val : T_val,
-                                        a_img, total);
-        if (!transpose && proj)
-            k_proj_rows<<<grid_for(n_rows, T256, 8192), T256, 0, s>>>(w, L.start, n_rows, n_events, capacity,
-                                                                      proj);
+    const uint64_t n_zero = n_img + TOTAL_SLOTS + (proj ? n_bins : 0);
+    k_fill_u64<<<grid_for(n_zero, T256, 4096), T256, 0, s>>>((uint64_t*)L.a_img, n_zero, 0);
+    // an image row's f x f phantom rows in as many shares as fill the chip
+    const uint64_t rows = (uint64_t)my * mz, shares = std::min<uint64_t>((uint64_t)f * f, (2047 + rows) / rows);
+    k_image_activity<<<(unsigned)(rows * shares), T256, 0, s>>>(activity, nx, ny, f, mx, my, (uint32_t)shares,
+                                                               L.a_img, L.total);
+
+    // the events by (bin, voxel): rows 0..n_bins (n_bins: filtered events)
+    const int col_bits = std::max(1, bit_width(n_img - 1));
+    const Digits d = digits_of(col_bits + bit_width(n_bins));
+    int cur = 0;
+    for (int p = 0; p < d.passes; ++p) {
+        if (p == 0)
+            k_make_keys<<<L.n_tiles, T256, 0, s>>>(a, n_bins, col_bits, d.mask(), L.n_tiles, L.keys[0],
+                                                   (int64_t*)L.vals[0], L.hist);
+        else
+            k_radix_hist<<<L.n_tiles, T256, 0, s>>>(L.keys[cur], n_ev, capacity, p * d.bits, d.mask(), L.n_tiles,
+                                                    L.hist);
+        k_digit_scan<<<RADIX, 1024, 0, s>>>(n_ev, capacity, L.n_tiles, L.hist, L.tot);
+        k_radix_scatter<uint64_t><<<L.n_tiles, T256, 0, s>>>(L.keys[cur], L.vals[cur], L.keys[cur ^ 1],
+                                                             L.vals[cur ^ 1], nullptr, nullptr, n_ev, capacity,
+                                                             p * d.bits, d.mask(), L.n_tiles, L.hist, L.tot);
+        cur ^= 1;
     }
+    // merged: T, and the entries' (bin, value) pairs
+    k_count_runs<<<L.n_runs, T256, 0, s>>>(L.keys[cur], a, n_bins, col_bits, L.cnt);
+    hipError_t e = exclusive_scan(L.cnt, L.n_runs, L.first, L.bsum, s);
+    if (e != hipSuccess) return e;
+    uint64_t* pair = L.vals[cur ^ 1];
+    k_emit_runs<<<L.n_runs, T256, 0, s>>>(a, L.keys[cur], (const int64_t*)L.vals[cur], L.first, n_bins, col_bits,
+                                          T_col, T_val, pair, proj ? L.acc : nullptr, L.a_img, L.total);
+    const uint64_t* nnz = L.first + L.n_runs;
+    k_row_ptr<<<grid_for(n_bins + 1, T256, 8192), T256, 0, s>>>(pair, nnz, capacity, n_bins, T_rp,
+                                                                (const int64_t*)L.acc, n_ev, proj);
+    // the entries by voxel, bins in order within one: T^T
+    const Digits t = digits_of(col_bits);
+    const uint32_t* kin = (const uint32_t*)T_col;
+    for (int p = 0; p < t.passes; ++p) {
+        uint32_t* kout = (uint32_t*)L.keys[cur];
+        const bool last = p == t.passes - 1;
+        k_radix_hist<<<L.n_tiles, T256, 0, s>>>(kin, nnz, capacity, p * t.bits, t.mask(), L.n_tiles, L.hist);
+        k_digit_scan<<<RADIX, 1024, 0, s>>>(nnz, capacity, L.n_tiles, L.hist, L.tot);
+        k_radix_scatter<uint32_t><<<L.n_tiles, T256, 0, s>>>(
+            kin, L.vals[cur ^ 1], kout, L.vals[cur], last ? Tt_col : nullptr, last ? Tt_val : nullptr, nnz, capacity,
+            p * t.bits, t.mask(), L.n_tiles, L.hist, L.tot);
+        kin = kout;
+        cur ^= 1;
+    }
+    k_row_ptr<<<grid_for(n_img + 1, T256, 8192), T256, 0, s>>>(kin, nnz, capacity, n_img, Tt_rp,
+                                                               (const int64_t*)nullptr, n_ev, (float*)nullptr);
     return hipGetLastError();
 }
 

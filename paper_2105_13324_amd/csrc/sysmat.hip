@@ -759,10 +759,10 @@ __device__ inline double group_row_sum(int64_t k0, int64_t k1, int sub, Term ter
     return acc;
 }
 
-// ---- row order.  Sweeps of a dense matrix: a group of threads (a wavefront,
-// or a whole workgroup where rows are long) takes consecutive rows, whose
-// entries are consecutive too, and streams them a tile of eight entries per
-// thread at a time: coalesced loads of columns and values, eight gathers in
+// ---- row order.  Sweeps of a dense matrix: a group of threads (a workgroup,
+// or a wavefront where there are few rows) takes consecutive rows, whose
+// entries are consecutive too, and streams them a tile of LOADS entries per
+// thread at a time: coalesced loads of columns and values, LOADS gathers in
 // flight per thread, the products in LDS in FP64, then each row summed from
 // there by a power-of-two number of lanes.  The order of a sum depends only on
 // the matrix.  Bound by the stream of entries (8 bytes each) and the gathers'
@@ -770,37 +770,18 @@ __device__ inline double group_row_sum(int64_t k0, int64_t k1, int sub, Term ter
 // row with the row's loads in a chain (233 us per forward sweep and, in bin
 // slices per XCD with a third kernel adding them, 393 us per backprojection on
 // a forced-detection matrix of 4.6e7 entries, 1.97 M bins and 2.6e5 voxels:
-// 169 and 299 us now).  No slices are needed: each XCD works on
+// 156 and 274 us now).  No slices are needed: each XCD works on
 // neighbouring rows (sweep_chunk), so a backprojection's gathers from its slab
 // of voxels fall in the bins of a few detector rows, which its L2 holds (90 %
 // hits).  Where columns are random, which no camera gives, the slices were the
 // better (2^20 bins x 2^17 voxels, 3e7 entries: 442 against 460 us per
 // iteration).
-constexpr int SWEEP_LOADS = 8;
 
-// How n rows are swept: threads per group (64 or T256) and rows per group, of
-// mean entries each; three quarters of a tile on average, so that most groups
-// need one.  Workgroups of four wavefronts are the better where they fill the
-// chip (one update of 2.6e5 rows of 5.5 entries: 11.8 against 17.1 us); a
-// wavefront on its own needs no barriers and takes smaller sweeps in more
-// pieces (1.7e5 rows of 3 entries in 9 subsets: 401 against 553 us per call),
-// but leaves rows of several of its tiles to a workgroup.
-struct SweepPlan {
-    int threads, per;
-};
-constexpr int64_t SWEEP_GROUPS = 768;
-constexpr int SWEEP_SHARE(int threads) { return SWEEP_LOADS * threads * 3 / 4; }
-inline SweepPlan sweep_plan(int64_t mean, int64_t n) {
-    mean = std::max<int64_t>(1, mean);
-    SweepPlan p;
-    p.threads = T256;
-    p.per = (int)std::min<int64_t>(T256, std::max<int64_t>(1, SWEEP_SHARE(T256) / mean));
-    if (n / p.per < SWEEP_GROUPS && mean <= 2 * SWEEP_LOADS * 64) {
-        p.threads = 64;
-        const int64_t per = std::min<int64_t>(SWEEP_SHARE(64) / mean, n / (4 * SWEEP_GROUPS));
-        p.per = (int)std::min<int64_t>(64, std::max<int64_t>(1, per));
-    }
-    return p;
+// Rows per group of `threads`, of mean entries each: three quarters of a tile
+// on average, so that most groups need one.
+inline int sweep_per(int loads, int threads, int64_t mean) {
+    const int64_t per = loads * threads * 3 / 4 / std::max<int64_t>(1, mean);
+    return (int)std::min<int64_t>(threads, std::max<int64_t>(1, per));
 }
 
 // Workgroups for n chunks (a group's rows) in groups of G threads, and the
@@ -847,10 +828,10 @@ __device__ __forceinline__ void group_sync() {
 // its gathers (first is in scalar registers).  All threads of a group call,
 // with the same r0 and n.  skip: nothing is done (loaded along with the
 // bounds, not before them).
-template <int G, class Bound, class Load, class Value, class Done>
+template <int G, int LOADS, class Bound, class Load, class Value, class Done>
 __device__ inline void sweep_bounds(int64_t r0, int n, bool skip, int64_t e0, Bound bound, Load load, Value value,
                                     Done done) {
-    constexpr int TILE = SWEEP_LOADS * G;
+    constexpr int TILE = LOADS * G;
     __shared__ double prod_s[T256 / G][TILE];
     __shared__ int64_t off_s[T256 / G][G + 1];
     double* __restrict__ prod = prod_s[threadIdx.x / G];
@@ -876,14 +857,14 @@ __device__ inline void sweep_bounds(int64_t r0, int n, bool skip, int64_t e0, Bo
             double acc = 0.0;
             for (int64_t k0 = 0; k0 < len; k0 += TILE) {
                 const int cnt = (int)(len - k0 < TILE ? len - k0 : TILE);
-                decltype(load(0, 0)) a[SWEEP_LOADS];
+                decltype(load(0, 0)) a[LOADS];
 #pragma unroll
-                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                for (int u = 0; u < LOADS; ++u) {
                     const int k = tid + u * G;
                     a[u] = load(first + k0, k < cnt ? k : cnt - 1);
                 }
 #pragma unroll
-                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                for (int u = 0; u < LOADS; ++u) {
                     const double x = value(a[u]);
                     acc += tid + u * G < cnt ? x : 0.0;
                 }
@@ -899,14 +880,14 @@ __device__ inline void sweep_bounds(int64_t r0, int n, bool skip, int64_t e0, Bo
         } else {
             const int cnt = (int)uniform_i64(off[e] - off[s]);
             if (cnt > 0) {
-                decltype(load(0, 0)) a[SWEEP_LOADS];
+                decltype(load(0, 0)) a[LOADS];
 #pragma unroll
-                for (int u = 0; u < SWEEP_LOADS; ++u) {
+                for (int u = 0; u < LOADS; ++u) {
                     const int k = tid + u * G;
                     a[u] = load(first, k < cnt ? k : cnt - 1);
                 }
 #pragma unroll
-                for (int u = 0; u < SWEEP_LOADS; ++u) prod[tid + u * G] = value(a[u]);
+                for (int u = 0; u < LOADS; ++u) prod[tid + u * G] = value(a[u]);
             }
             group_sync<G>();
             // as many lanes per row as there are for all rows at once
@@ -926,12 +907,16 @@ __device__ inline void sweep_bounds(int64_t r0, int n, bool skip, int64_t e0, Bo
     }
 }
 
-template <int G, class Load, class Value, class Done>
+template <int G, int LOADS, class Load, class Value, class Done>
 __device__ inline void sweep(int64_t r0, int n, bool skip, const int64_t* __restrict__ rp, Load load, Value value,
                              Done done) {
     const int64_t e0 = rp[r0];
-    sweep_bounds<G>(r0, n, skip, e0, [&](int i) { return rp[r0 + i] - e0; }, load, value, done);
+    sweep_bounds<G, LOADS>(r0, n, skip, e0, [&](int i) { return rp[r0 + i] - e0; }, load, value, done);
 }
+
+// Bins have short rows and voxels long ones: on the matrix above eight and
+// four took 156 and 274 us per sweep, four and eight 178 and 299 us.
+constexpr int FORWARD_LOADS = 8, UPDATE_LOADS = 4;
 
 // An entry and the matrix's product with a vector.
 struct Entry {
@@ -940,27 +925,90 @@ struct Entry {
 };
 __device__ __forceinline__ Entry load_entry(const int32_t* __restrict__ col, const float* __restrict__ val,
                                             int64_t first, int k) {
-    return Entry{__builtin_nontemporal_load(col + first + (uint32_t)k),
-                 __builtin_nontemporal_load(val + first + (uint32_t)k)};
+    return Entry{*(col + first + (uint32_t)k), *(val + first + (uint32_t)k)};
 }
 
 // out[r] = sum of the row's values (sens), 0 for an empty row.
-template <int G>
 __global__ __launch_bounds__(T256) void k_sweep_sums(int64_t n_rows, int per, const int64_t* __restrict__ rp,
                                                      const float* __restrict__ v, double* __restrict__ out) {
-    const int64_t r0 = sweep_chunk<G>() * per;
+    const int64_t r0 = sweep_chunk<T256>() * per;
     if (r0 >= n_rows) return;
     const int n = (int)std::min<int64_t>(per, n_rows - r0);
-    const int i = (int)(threadIdx.x % G);
+    const int i = (int)(threadIdx.x);
     if (i < n && rp[r0 + i] == rp[r0 + i + 1]) out[r0 + i] = 0.0;
-    sweep<G>(r0, n, false, rp, [&](int64_t first, int k) { return __builtin_nontemporal_load(v + first + (uint32_t)k); },
+    sweep<T256, UPDATE_LOADS>(r0, n, false, rp, [&](int64_t first, int k) { return *(v + first + (uint32_t)k); },
              [](float x) { return (double)x; }, [&](int64_t r, double acc) { out[r] = acc; });
+}
+
+// Sums over the rows by groups of GS lanes, one row per group and pass, four
+// entries per lane in flight.  For matrices whose both orientations stay in the
+// caches between sweeps: with the latencies that small, the sweeps above lose
+// more to their barriers and part-filled tiles than a row's chain of loads
+// costs (36 iterations on 2.4e6 entries, 4.3e5 bins, 1.2e4 voxels: 1002 us
+// against 1169 us swept; 5.1e6 entries, 15 iterations: 870 against 938 us;
+// 1.1e7: even; 4.3e7, 10 iterations: 7633 against 4541 us).  Long rows are
+// swept all the same: with a wavefront per row too few are in flight (1331
+// voxels of 486 entries: 14.6 against 9.8 us per backprojection).
+constexpr int64_t SWEEP_MIN_NNZ = 1 << 23;
+constexpr int64_t SWEEP_MIN_MEAN = 256;
+
+// Lanes that share a row: the smallest group of 1, 4, 16 or 64 for which four
+// entries per lane cover the mean row; 0: the rows are swept.
+inline int lanes_per_row(int64_t nnz, int64_t n_rows) {
+    if (nnz >= SWEEP_MIN_NNZ || nnz >= SWEEP_MIN_MEAN * n_rows) return 0;
+    return nnz <= 4 * n_rows ? 1 : nnz <= 16 * n_rows ? 4 : nnz <= 64 * n_rows ? 16 : 64;
+}
+
+template <int GS, class Own, class Term, class Done>
+__device__ inline void sweep_groups(int64_t n_rows, const int64_t* __restrict__ rp,
+                                    const uint32_t* __restrict__ call_bad, Own own, Term term, Done done) {
+    const RowGroups<GS> G(blockIdx.x, gridDim.x);
+    const bool skip = *call_bad != 0;
+    for (int64_t r = G.first; r < n_rows; r += G.step) {
+        const int64_t lo = rp[r], hi = rp[r + 1];
+        if (skip) return;
+        if (hi == lo) continue;
+        const auto o = own(r);
+        const double sum = group_row_sum<GS>(lo, hi, G.sub, term);
+        if (G.sub == 0) done(r, o, sum);
+    }
+}
+
+template <int GS>
+__global__ __launch_bounds__(T256) void k_mlem_forward_rows(int64_t n_bins, int, const int64_t* __restrict__ rp,
+                                                            const uint32_t* __restrict__ call_bad,
+                                                            const int32_t* __restrict__ col,
+                                                            const float* __restrict__ val,
+                                                            const double* __restrict__ S,
+                                                            const float* __restrict__ P,
+                                                            double* __restrict__ ratio) {
+    sweep_groups<GS>(n_bins, rp, call_bad, [&](int64_t r) { return P[r]; },
+                     [&](int64_t k, bool ok) {
+                         const double x = (double)val[k] * S[col[k]];
+                         return ok ? x : 0.0;
+                     },
+                     [&](int64_t r, float p, double y) { ratio[r] = y > 0.0 ? (double)p / y : 0.0; });
+}
+
+template <int GS>
+__global__ __launch_bounds__(T256) void k_mlem_update_rows(int64_t n_vox, int, const int64_t* __restrict__ rp,
+                                                           const uint32_t* __restrict__ call_bad,
+                                                           const int32_t* __restrict__ col,
+                                                           const float* __restrict__ val,
+                                                           const double* __restrict__ ratio,
+                                                           const double* __restrict__ sens,
+                                                           double* __restrict__ S) {
+    sweep_groups<GS>(n_vox, rp, call_bad, [&](int64_t r) { return double2{S[r], sens[r]}; },
+                     [&](int64_t k, bool ok) {
+                         const double x = (double)val[k] * ratio[col[k]];
+                         return ok ? x : 0.0;
+                     },
+                     [&](int64_t r, double2 o, double b) { S[r] = o.y > 0.0 ? o.x * b / o.y : 0.0; });
 }
 
 // y_j = sum_i T_ij S_i; ratio_j = P_j / y_j (0 when y_j = 0), over the
 // non-empty bin rows (an empty one is referred to by no entry of T^T, so its
 // ratio is never read).  A call that does not match the set-up sweeps nothing.
-template <int G>
 __global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, const int64_t* __restrict__ rp,
                                                        const uint32_t* __restrict__ call_bad,
                                                        const int32_t* __restrict__ col,
@@ -968,9 +1016,9 @@ __global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, 
                                                        const double* __restrict__ S,
                                                        const float* __restrict__ P,
                                                        double* __restrict__ ratio) {
-    const int64_t r0 = sweep_chunk<G>() * per;
+    const int64_t r0 = sweep_chunk<T256>() * per;
     if (r0 >= n_bins) return;
-    sweep<G>(r0, (int)std::min<int64_t>(per, n_bins - r0), *call_bad != 0, rp,
+    sweep<T256, FORWARD_LOADS>(r0, (int)std::min<int64_t>(per, n_bins - r0), *call_bad != 0, rp,
              [&](int64_t first, int k) { return load_entry(col, val, first, k); },
              [&](Entry e) { return (double)e.val * S[e.col]; },
              [&](int64_t r, double y) { ratio[r] = y > 0.0 ? (double)P[r] / y : 0.0; });
@@ -978,7 +1026,6 @@ __global__ __launch_bounds__(T256) void k_mlem_forward(int64_t n_bins, int per, 
 
 // S_i <- S_i * (sum_j T_ij ratio_j) / sens_i over the non-empty voxel rows
 // (an empty row has sens_i = 0, so its S_i is already 0).
-template <int G>
 __global__ __launch_bounds__(T256) void k_mlem_update(int64_t n_vox, int per, const int64_t* __restrict__ rp,
                                                       const uint32_t* __restrict__ call_bad,
                                                       const int32_t* __restrict__ col,
@@ -986,9 +1033,9 @@ __global__ __launch_bounds__(T256) void k_mlem_update(int64_t n_vox, int per, co
                                                       const double* __restrict__ ratio,
                                                       const double* __restrict__ sens,
                                                       double* __restrict__ S) {
-    const int64_t r0 = sweep_chunk<G>() * per;
+    const int64_t r0 = sweep_chunk<T256>() * per;
     if (r0 >= n_vox) return;
-    sweep<G>(r0, (int)std::min<int64_t>(per, n_vox - r0), *call_bad != 0, rp,
+    sweep<T256, UPDATE_LOADS>(r0, (int)std::min<int64_t>(per, n_vox - r0), *call_bad != 0, rp,
              [&](int64_t first, int k) { return load_entry(col, val, first, k); },
              [&](Entry e) { return (double)e.val * ratio[e.col]; },
              [&](int64_t r, double b) { S[r] = sens[r] > 0.0 ? S[r] * b / sens[r] : 0.0; });
@@ -1400,6 +1447,27 @@ __global__ __launch_bounds__(T256) void k_mlem_out(int64_t n_vox, const double* 
 // Bound by reading B^T (twice, the second time from L2) and writing it once:
 // 8.6e6 entries of 2.6e5 rows in 6 subsets took 230 us as a count, a scan and
 // a scatter over single rows, 82 us now.
+// How n rows are swept: threads per group (64 or T256) and rows per group.
+// Workgroups of four wavefronts are the better where they fill the chip (one
+// update of 2.6e5 rows of 5.5 entries: 11.8 against 17.1 us); a wavefront on
+// its own needs no barriers and takes smaller sweeps in more pieces (1.7e5 rows
+// of 3 entries in 9 subsets: 401 against 553 us per call), but leaves rows of
+// several of its tiles to a workgroup.
+struct SweepPlan {
+    int threads, per;
+};
+constexpr int OS_LOADS = 8;
+constexpr int64_t SWEEP_GROUPS = 768;
+inline SweepPlan sweep_plan(int64_t mean, int64_t n) {
+    mean = std::max<int64_t>(1, mean);
+    SweepPlan p{T256, sweep_per(OS_LOADS, T256, mean)};
+    if (n / p.per < SWEEP_GROUPS && mean <= 2 * OS_LOADS * 64) {
+        p.threads = 64;
+        p.per = (int)std::max<int64_t>(1, std::min<int64_t>(sweep_per(OS_LOADS, 64, mean), n / (4 * SWEEP_GROUPS)));
+    }
+    return p;
+}
+
 constexpr int SPLIT_COUNTS = 4096;     // (subset, row) pairs of a chunk, counters in LDS
 constexpr int SPLIT_LOADS = 4;
 
@@ -1563,7 +1631,7 @@ __device__ inline void sweep_split(int64_t c, int k, int64_t n_vox, int per, int
                                    Value value, Done done) {
     const int64_t r0 = c * per;
     const int32_t* __restrict__ o = offs + (c * n_sub + k) * (int64_t)(per + 1);
-    sweep_bounds<G>(r0, (int)std::min<int64_t>(per, n_vox - r0), false, rp[r0], [&](int i) { return (int64_t)o[i]; }, load,
+    sweep_bounds<G, OS_LOADS>(r0, (int)std::min<int64_t>(per, n_vox - r0), false, rp[r0], [&](int i) { return (int64_t)o[i]; }, load,
                  value, done);
 }
 
@@ -1579,7 +1647,7 @@ __global__ __launch_bounds__(T256) void k_os_sums(int64_t n_vox, int per, int n_
     const int32_t* o = offs + (c * n_sub + k) * (int64_t)(per + 1);
     if (i < per && r0 + i < n_vox && o[i] == o[i + 1]) out[r0 + i] = 0.0;
     sweep_split<G>(c, k, n_vox, per, n_sub, rp, offs,
-                [&](int64_t first, int e) { return __builtin_nontemporal_load(val + first + (uint32_t)e); },
+                [&](int64_t first, int e) { return *(val + first + (uint32_t)e); },
                 [](float x) { return (double)x; }, [&](int64_t r, double acc) { out[r] = acc; });
 }
 
@@ -1619,7 +1687,7 @@ __global__ __launch_bounds__(T256) void k_os_forward(int64_t n_chunks, int32_t p
     // a bin without entries still has its scatter term
     const int i = (int)(threadIdx.x % G);
     if (i < n && rp[r0 + i] == rp[r0 + i + 1]) done(r0 + i, 0.0);
-    sweep<G>(r0, n, false, rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
+    sweep<G, OS_LOADS>(r0, n, false, rp, [&](int64_t first, int k) { return load_entry(col, val, first, k); },
              [&](Entry e) { return (double)e.val * S[e.col]; }, done);
 }
 
@@ -1911,10 +1979,10 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     // Layout: compact when the matrix is sparse (its renumbered columns fit
     // the workspace), else row order.
     const bool compact = nnz <= n_bins + n_vox;
-    const SweepPlan pb = sweep_plan(nnz / std::max<int64_t>(1, n_bins), n_bins);
-    const SweepPlan pv = sweep_plan(nnz / std::max<int64_t>(1, n_vox), n_vox);
-    const unsigned grid_b = sweep_grid((n_bins + pb.per - 1) / pb.per, pb.threads);
-    const unsigned grid_v = sweep_grid((n_vox + pv.per - 1) / pv.per, pv.threads);
+    const int per_b = sweep_per(FORWARD_LOADS, T256, nnz / n_bins);
+    const int per_v = sweep_per(UPDATE_LOADS, T256, nnz / n_vox);
+    const unsigned grid_b = sweep_grid((n_bins + per_b - 1) / per_b, T256);
+    const unsigned grid_v = sweep_grid((n_vox + per_v - 1) / per_v, T256);
     int dev = 0, n_cu = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -1922,8 +1990,7 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     const int gv = grid_for(nv, T256, 8192);
     const int gr = grid_for((nb + ROW_CHUNK - 1) / ROW_CHUNK + (nv + ROW_CHUNK - 1) / ROW_CHUNK, 1, 2048);
     if (setup) {
-        auto ks = pv.threads == 64 ? k_sweep_sums<64> : k_sweep_sums<T256>;
-        ks<<<grid_v, T256, 0, s>>>(n_vox, pv.per, Tt_rp, Tt_val, sens);
+        k_sweep_sums<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, Tt_val, sens);
         k_mlem_setup<<<1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
     }
     if (compact) {
@@ -1981,11 +2048,16 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     }
     if (!iterate) return hipGetLastError();
     k_mlem_load<<<gv, T256, 0, s>>>(n_bins, n_vox, nnz, image, sens, S, nullptr, nullptr, nullptr, nullptr, st);
-    auto kf = pb.threads == 64 ? k_mlem_forward<64> : k_mlem_forward<T256>;
-    auto ku = pv.threads == 64 ? k_mlem_update<64> : k_mlem_update<T256>;
+    const int g_b = lanes_per_row(nnz, n_bins), g_v = lanes_per_row(nnz, n_vox);
+    auto kf = g_b == 0 ? k_mlem_forward : g_b == 1 ? k_mlem_forward_rows<1> : g_b == 4 ? k_mlem_forward_rows<4>
+            : g_b == 16 ? k_mlem_forward_rows<16> : k_mlem_forward_rows<64>;
+    auto ku = g_v == 0 ? k_mlem_update : g_v == 1 ? k_mlem_update_rows<1> : g_v == 4 ? k_mlem_update_rows<4>
+            : g_v == 16 ? k_mlem_update_rows<16> : k_mlem_update_rows<64>;
+    const unsigned gf = g_b ? (unsigned)grid_for(nb * g_b, T256, 1 << 16) : grid_b;
+    const unsigned gu = g_v ? (unsigned)grid_for(nv * g_v, T256, 1 << 16) : grid_v;
     for (int it = 0; it < n_iter; ++it) {
-        kf<<<grid_b, T256, 0, s>>>(n_bins, pb.per, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
-        ku<<<grid_v, T256, 0, s>>>(n_vox, pv.per, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
+        kf<<<gf, T256, 0, s>>>(n_bins, per_b, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
+        ku<<<gu, T256, 0, s>>>(n_vox, per_v, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
     return hipGetLastError();

@@ -78,3 +78,46 @@ def test_sweeps(kind, transpose):
                 b = Tk.T @ np.divide(P[sub == k], y, out=np.zeros_like(y), where=y > 0)
                 S = np.where(sk > 0, S * b / np.maximum(sk, 1e-300), S)
         np.testing.assert_allclose(img.cpu().numpy(), S, rtol=RTOL, atol=0)
+
+
+@pytest.mark.parametrize("transpose", [False, True])
+def test_sweeps_large(transpose):
+    """Above the entry count from which MLEM sweeps tiles whatever the row
+    lengths: several rows per tile, uneven, some empty, in thousands of groups."""
+    import scipy.sparse as sp
+    import torch
+    mc = _mc()
+    rng = np.random.Generator(np.random.PCG64(17))
+    n_rows, n_cols = 300_000, 9973
+    lengths = (rng.pareto(1.2, size=n_rows) * 10).astype(int).clip(0, 3000)
+    lengths[rng.integers(0, n_rows, size=5000)] = 0
+    ptr = np.concatenate([[0], np.cumsum(lengths)])
+    k = np.arange(ptr[-1]) - np.repeat(ptr[:-1], lengths)
+    cols = (np.repeat(rng.integers(0, n_cols, size=n_rows), lengths) + 7 * k) % n_cols
+    T = sp.csr_matrix((rng.uniform(0.1, 1.0, size=ptr[-1]).astype(np.float32), cols, ptr), shape=(n_rows, n_cols))
+    T = (T.T if transpose else T).tocsr()
+    T.sort_indices()
+    assert T.nnz >= 1 << 23
+    P = rng.uniform(0.0, 5.0, size=T.shape[0]).astype(np.float32)
+    m = mc.csr_from_scipy(T)
+    m.proj = torch.as_tensor(P, device="cuda")
+    T = T.astype(np.float64)
+    Tt = T.T.tocsr()
+    img = torch.ones(m.n_img, dtype=torch.float32, device="cuda")
+    mc.Mlem(m).run(img, 2)
+    sens = np.asarray(T.sum(axis=0)).ravel()
+    S = np.where(sens > 0, 1.0, 0.0)
+    for _ in range(2):
+        y = T @ S
+        S = np.where(sens > 0, S * (Tt @ np.divide(P, y, out=np.zeros_like(y), where=y > 0)) / np.maximum(sens, 1e-300), 0)
+    np.testing.assert_allclose(img.cpu().numpy(), S, rtol=RTOL, atol=0)
+    img = torch.ones(m.n_img, dtype=torch.float32, device="cuda")
+    mc.osem(m, img, 1, 2, 1)
+    S = np.where(sens > 0, 1.0, 0.0)
+    for s in range(2):
+        Tk = T[s::2]
+        y = Tk @ S
+        sk = np.asarray(Tk.sum(axis=0)).ravel()
+        b = Tk.T @ np.divide(P[s::2], y, out=np.zeros_like(y), where=y > 0)
+        S = np.where(sk > 0, S * b / np.maximum(sk, 1e-300), S)
+    np.testing.assert_allclose(img.cpu().numpy(), S, rtol=RTOL, atol=0)

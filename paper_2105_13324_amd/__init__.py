@@ -324,14 +324,17 @@ class Simulator:
         total = sum(self.sizes)
         self.tally = torch.zeros(total, dtype=torch.int64, device=dev)
         self.tally_sq = torch.zeros(total, dtype=torch.int64, device=dev) if want_sq else None
-        self.fates = torch.zeros((n, 8), dtype=torch.int64, device=dev)
-        self.energy = torch.zeros((n, 4), dtype=torch.int64, device=dev)
-        self.counters = torch.zeros((n, 8), dtype=torch.int64, device=dev)
-        self.status = torch.zeros(4, dtype=torch.int64, device=dev)
+        # the small outputs in one allocation (each on a 64-byte line): one fill
+        # instead of five before a run that is not repeated, and the status and
+        # the event count come back in one copy
+        small = torch.zeros(8 * (n + (n + 1) // 2 + n + 1), dtype=torch.int64, device=dev)
+        self.fates, rest = small[:8 * n].view(n, 8), small[8 * n:]
+        self.counters, rest = rest[:8 * n].view(n, 8), rest[8 * n:]
+        self.status, self.n_events, self._ends = rest[:4], rest[4:5], rest[:5]
+        self.energy = rest[8:8 + 4 * n].view(n, 4)
         self.event_capacity = int(event_capacity)
         self.events = (torch.zeros((max(self.event_capacity, 1), 3), dtype=torch.int64, device=dev)
                        if self.event_capacity else None)
-        self.n_events = torch.zeros(1, dtype=torch.int64, device=dev)
         nb = _lib.mc_workspace_bytes(self._arr, n, C.byref(self.options) if self.options else None)
         if nb == 0:
             raise McError("mc_workspace_bytes: invalid problem description")
@@ -369,15 +372,24 @@ class Simulator:
             self.n_events.data_ptr(), self.status.data_ptr(), _stream_ptr())
         _check(rc, "mc_simulate_projections_static")
 
+    def _check_ends(self):
+        """Waits for the run; the status words and the event count (int64
+        [5]).  Raises as check_status."""
+        st = self._ends.cpu().numpy()
+        bits = int(st[0])
+        if bits & (STATUS_BAD_MU | STATUS_NO_ACTIVITY | STATUS_BAD_ANGLE | STATUS_BAD_EVENT):
+            rc = MC_EINVAL
+        elif bits & (STATUS_GRAD_OVERFLOW | STATUS_TALLY_OVERFLOW | STATUS_ACTIVITY_OVERFLOW):
+            rc = MC_EOVERFLOW
+        else:
+            return st
+        raise McError(f"{_lib.mc_error_string(rc).decode()} (status bits {bits})")
+
     def check_status(self):
-        """mc_check_status on the call's status: raises McError for bad
-        device input or a tally that left its fixed-point range; returns the
+        """What mc_check_status makes of the call's status: raises McError for
+        bad device input or a tally that left its fixed-point range; returns the
         status array (list overflow and capped histories are reported there)."""
-        rc = _lib.mc_check_status(self.status.data_ptr(), _stream_ptr())
-        st = self.status.cpu().numpy()
-        if rc in (MC_EINVAL, MC_EOVERFLOW, MC_EDEVICE):
-            raise McError(f"{_lib.mc_error_string(rc).decode()} (status bits {int(st[0])})")
-        return st
+        return self._check_ends()[:4]
 
     def tallies(self):
         """Per-problem tally tensors (int64 Q31.32) shaped [V, 2, nv, nu]."""
@@ -695,8 +707,8 @@ def _mc_project_fn():
         @staticmethod
         def forward(ctx, mu, problem, event_capacity, frac_bits):
             dp = problem.with_(mu=mu.detach().to(torch.float32).contiguous())
-            sim = simulate(dp, event_capacity=event_capacity, want_sq=False)
-            if int(sim.n_events.item()) > event_capacity:
+            sim = simulate(dp, event_capacity=event_capacity, want_sq=False, sync=False)
+            if int(sim._check_ends()[4]) > event_capacity:
                 raise McError("event list overflow in forward; raise event_capacity")
             ctx.dp, ctx.sim, ctx.frac_bits = dp, sim, frac_bits
             return sim.tally.view(dp.tally_shape).to(torch.float64) * (2.0 ** -32)

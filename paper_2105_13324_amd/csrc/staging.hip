@@ -402,8 +402,23 @@ __device__ inline void palette_merge(uint32_t* pal, uint32_t* overflow, const ui
         __syncthreads();
         if (n_missing == 0 || n_there > (uint32_t)PALETTE_N) return;
         if (n_there + n_missing > (uint32_t)PALETTE_N) {
-            if (threadIdx.x == 0) atomicOr(overflow, 1u);
-            return;
+            // The look is not of one moment: a value can be in it behind a slot
+            // of its probe order that was read before another workgroup filled
+            // it.  Counted again wherever they lie, what is there and what is
+            // missing are different values of the map.
+            __syncthreads();
+            if (threadIdx.x == 0) n_missing = 0;
+            __syncthreads();
+            for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) {
+                bool there = false;
+                for (int i = 0; i < PALETTE_N; ++i) there |= snap[i] == vals[k];
+                if (!there) atomicAdd(&n_missing, 1u);
+            }
+            __syncthreads();
+            if (n_there + n_missing > (uint32_t)PALETTE_N) {
+                if (threadIdx.x == 0) atomicOr(overflow, 1u);
+                return;
+            }
         }
         for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) {
             const uint32_t slot = free_slot(vals[k]);

@@ -59,7 +59,7 @@ __device__ inline uint32_t wave_or_u32(uint32_t v) {
 // One launch for up to STAGE_MAX problems, so small problems overlap instead
 // of queueing.  On small problems staging is bound by its launches, 2 to 5 us
 // each whatever they do: 12 of them (with the call's preparation) took 55 us
-// at 32^3 and 95 us at 128^3, the four 24 and 45 us.
+// at 32^3 and 95 us at 128^3, the three or four 19 and 45 us.
 constexpr int STAGE_MAX = 8;
 constexpr int KN_BLOCKS = (KN_TABLE_N + 255) / 256;
 
@@ -86,6 +86,18 @@ static_assert(sizeof(StageArgs) <= 4096, "kernel arguments");
 struct StagePart {
     uint32_t mx, flags, lo, hi;
 };
+
+// Where they are kept until combined: a problem of few stretches (TOP_SMALL) has
+// no launch for that, so its results must outlast the threshold table's writing;
+// otherwise the table's place.
+constexpr int TOP_SMALL = SCAN_THREADS;
+constexpr int PARTS_AT = 512;
+static_assert(TOP_SMALL <= PARTS_AT && PARTS_AT + TOP_SMALL * sizeof(StagePart) / 8 <= BLOCK_SCRATCH_MIN,
+              "after the stretches' sums, in the block-sum scratch");
+__device__ __forceinline__ StagePart* parts_of(const ProbDesc& d) {
+    const uint64_t n_blocks = (d.nvox + SCAN_ITEMS - 1) / SCAN_ITEMS;
+    return n_blocks <= TOP_SMALL ? (StagePart*)(d.block_sums + PARTS_AT) : (StagePart*)d.q32;
+}
 constexpr uint32_t PART_ANY = 1u << 31;
 
 // Klein-Nishina total cross-section per electron over 2 pi r_e^2 (closed form).
@@ -185,7 +197,7 @@ __device__ inline void stage_scan(const ProbDesc& d) {
             runs += part_runs[v];
         }
         // in the threshold table's place: it is written from launch 3 on
-        ((StagePart*)d.q32)[blockIdx.x] = p;
+        parts_of(d)[blockIdx.x] = p;
         d.block_sums[blockIdx.x] = sum;
         d.block_cnt[blockIdx.x] = runs;
     }
@@ -255,22 +267,22 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_stage_scan(StageArgs A) {
     }
 }
 
-// Launch 2, one workgroup of 1024 threads per problem: the stretches' results
-// combined into the descriptor (max mu, flags, box), their sums and run counts
-// scanned (each thread a contiguous stretch of blocks), the activity total and
-// the number of runs.
-__global__ __launch_bounds__(1024) void k_stage_top(ProbDesc* descs) {
-    ProbDesc* pd = descs + blockIdx.y;
+// One workgroup per problem: the stretches' results combined into the
+// descriptor (max mu, flags, box), their sums and run counts scanned (each thread
+// a contiguous stretch of blocks; the prefixes put in their place with PREFIXES),
+// the activity total and the number of runs.
+template <int THREADS, bool PREFIXES>
+__device__ inline void stage_top(ProbDesc* pd) {
     const int n_blocks = (int)((pd->nvox + SCAN_ITEMS - 1) / SCAN_ITEMS);
     __shared__ uint64_t tot[16];
     __shared__ uint32_t totc[16];
     __shared__ uint32_t s_mx, s_fl, s_lo[3], s_hi[3];
     uint64_t* __restrict__ bs = pd->block_sums;
     uint32_t* __restrict__ bc = pd->block_cnt;
-    const StagePart* __restrict__ parts = (const StagePart*)pd->q32;
+    const StagePart* __restrict__ parts = parts_of(*pd);
     if (threadIdx.x < 3) { s_lo[threadIdx.x] = 1023u; s_hi[threadIdx.x] = 0u; }
     if (threadIdx.x == 3) s_mx = s_fl = 0;
-    const int per = (n_blocks + 1023) / 1024;
+    const int per = (n_blocks + THREADS - 1) / THREADS;
     const int b0 = threadIdx.x * per;
     uint64_t s = 0;
     uint32_t c = 0, mx = 0, fl = 0, lo[3] = {1023u, 1023u, 1023u}, hi[3] = {0u, 0u, 0u};
@@ -317,14 +329,16 @@ __global__ __launch_bounds__(1024) void k_stage_top(ProbDesc* descs) {
         if (b0 + j < n_blocks) {
             const uint64_t v = bs[b0 + j];
             const uint32_t vc = bc[b0 + j];
-            bs[b0 + j] = run;
-            bc[b0 + j] = runc;
+            if (PREFIXES) {
+                bs[b0 + j] = run;
+                bc[b0 + j] = runc;
+            }
             run += v;
             runc += vc;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 1023) {
+    if (threadIdx.x == THREADS - 1) {
         pd->total = run;
         pd->n_runs = runc;
         pd->mu_hat_bits = s_mx;
@@ -337,6 +351,9 @@ __global__ __launch_bounds__(1024) void k_stage_top(ProbDesc* descs) {
         }
     }
 }
+
+// Launch 2, where a problem has more than TOP_SMALL stretches.
+__global__ __launch_bounds__(1024) void k_stage_top(ProbDesc* descs) { stage_top<1024, true>(descs + blockIdx.y); }
 
 // A workgroup's set of the distinct thresholds it has met: open addressing in
 // LDS with room for four times the palette, so a probe is short up to the
@@ -442,9 +459,20 @@ __device__ inline uint32_t table_index(uint32_t i, uint32_t nx, uint32_t ny, int
 // scanned map) marks the palette as overflowed instead and leaves the table
 // alone: probing a full global table value by value took 2.8 ms on a 128^3
 // map of distinct values, against 26 us now (segmented map: 20 against 17 us).
+template <bool OWN_TOP>
 __device__ inline void stage_thresholds(ProbDesc* pd, uint32_t block, uint32_t n_blocks) {
     const uint64_t nvox = pd->nvox;
-    const float mu_hat = __uint_as_float(pd->mu_hat_bits);
+    float mu_hat;
+    if constexpr (OWN_TOP) {
+        __shared__ uint32_t part[SCAN_THREADS / 64];
+        const uint32_t n_parts = (uint32_t)((nvox + SCAN_ITEMS - 1) / SCAN_ITEMS);
+        const uint32_t mx = wave_max_u32(threadIdx.x < n_parts ? parts_of(*pd)[threadIdx.x].mx : 0u);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
+        __syncthreads();
+        mu_hat = __uint_as_float(max(max(part[0], part[1]), max(part[2], part[3])));
+    } else {
+        mu_hat = __uint_as_float(pd->mu_hat_bits);
+    }
     const float* __restrict__ mu = pd->mu;
     uint32_t* __restrict__ q = pd->q32;
     const uint32_t nx = (uint32_t)pd->nx, ny = (uint32_t)pd->ny;
@@ -591,6 +619,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_mu_codes(ProbDesc* descs) {
 // exclusive scans of the thread totals, plus the block offsets; each voxel
 // that starts a run writes the run (cumulative weight before it, its packed
 // coordinates, its weight) at its compacted slot.
+template <bool OWN_TOP>
 __device__ inline void stage_runs(const ProbDesc* pd) {
     constexpr int PER = SCAN_ITEMS / SCAN_THREADS;
     const uint64_t nvox = pd->nvox;
@@ -632,8 +661,31 @@ __device__ inline void stage_runs(const ProbDesc* pd) {
     }
     if (lane == 63) { tot[wave] = x; totc[wave] = xc; }
     __syncthreads();
-    uint64_t before = pd->block_sums[blockIdx.x] + x - s;   // weight before voxel base
-    uint32_t k = pd->block_cnt[blockIdx.x] + xc - c;
+    // weight and runs before the block
+    uint64_t before;
+    uint32_t k;
+    if constexpr (OWN_TOP) {
+        __shared__ uint64_t part[SCAN_THREADS / 64];
+        __shared__ uint32_t partc[SCAN_THREADS / 64];
+        uint64_t w = threadIdx.x < blockIdx.x ? pd->block_sums[threadIdx.x] : 0;
+        uint32_t n = threadIdx.x < blockIdx.x ? pd->block_cnt[threadIdx.x] : 0;
+        for (int o = 32; o > 0; o >>= 1) {
+            w += (uint64_t)__shfl_xor((long long)w, o, 64);
+            n += (uint32_t)__shfl_xor((int)n, o, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            part[threadIdx.x >> 6] = w;
+            partc[threadIdx.x >> 6] = n;
+        }
+        __syncthreads();
+        before = (part[0] + part[1]) + (part[2] + part[3]);
+        k = (partc[0] + partc[1]) + (partc[2] + partc[3]);
+    } else {
+        before = pd->block_sums[blockIdx.x];
+        k = pd->block_cnt[blockIdx.x];
+    }
+    before += x - s;                                        // weight before voxel base
+    k += xc - c;
     for (int v = 0; v < wave; ++v) { before += tot[v]; k += totc[v]; }
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -718,11 +770,18 @@ __device__ inline void stage_guide(ProbDesc* pd, uint32_t block, uint32_t n_bloc
 
 // Launch 3, after the problem's maximum, total and block prefixes: the
 // emission runs (workgroups [0, scan_blocks)) and the accept thresholds with
-// their palette (the rest), which do not need each other.
+// their palette (the rest), which do not need each other.  OWN_TOP (all problems
+// have at most TOP_SMALL stretches): instead of launch 2, each workgroup adds up
+// what it needs of the stretches' results, one load per thread, and the last one
+// fills in the descriptor (32^3: 66 us per call of 2e5 histories with launch 2,
+// 60 without).
+template <bool OWN_TOP>
 __global__ __launch_bounds__(SCAN_THREADS) void k_stage_tables(ProbDesc* descs, uint32_t scan_blocks) {
     ProbDesc* pd = descs + blockIdx.y;
-    if (blockIdx.x < scan_blocks) stage_runs(pd);
-    else stage_thresholds(pd, blockIdx.x - scan_blocks, gridDim.x - scan_blocks);
+    const uint32_t end = gridDim.x - (OWN_TOP ? 1 : 0);
+    if (blockIdx.x < scan_blocks) stage_runs<OWN_TOP>(pd);
+    else if (blockIdx.x < end) stage_thresholds<OWN_TOP>(pd, blockIdx.x - scan_blocks, end - scan_blocks);
+    else stage_top<SCAN_THREADS, false>(pd);
 }
 
 // Launch 4: the guide table over the runs ([0, guide_blocks)), the palette
@@ -789,11 +848,13 @@ hipError_t launch_staging_batch(ProbDesc* d, const ProbDesc* h, int n, const Cal
         a.zero_blocks = zero_blocks;
         k_stage_scan<<<dim3(scan_blocks + 1 + KN_BLOCKS + zero_blocks, (unsigned)cnt), SCAN_THREADS, 0, st>>>(a);
     }
-    k_stage_top<<<dim3(1, ny), 1024, 0, st>>>(d);
+    const bool own_top = scan_blocks <= TOP_SMALL;
+    if (!own_top) k_stage_top<<<dim3(1, ny), 1024, 0, st>>>(d);
     // each workgroup puts each threshold value it meets into the palette once
     // (a few round trips to memory): not more of them than keep the chip busy
     const uint32_t stream_blocks = (uint32_t)std::min<uint64_t>((max_vox + RED_THREADS * ROWS - 1) / (RED_THREADS * ROWS), 1024);
-    k_stage_tables<<<dim3(scan_blocks + stream_blocks, ny), SCAN_THREADS, 0, st>>>(d, scan_blocks);
+    if (own_top) k_stage_tables<true><<<dim3(scan_blocks + stream_blocks + 1, ny), SCAN_THREADS, 0, st>>>(d, scan_blocks);
+    else k_stage_tables<false><<<dim3(scan_blocks + stream_blocks, ny), SCAN_THREADS, 0, st>>>(d, scan_blocks);
     const uint32_t guide_blocks = (uint32_t)grid_for(max_cap, RED_THREADS, 1024);
     k_stage_finish<<<dim3(guide_blocks + stream_blocks + 1, ny), RED_THREADS, 0, st>>>(d, guide_blocks);
     return hipGetLastError();

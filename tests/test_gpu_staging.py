@@ -39,3 +39,19 @@ def test_palette_around_its_capacity(n_distinct, brick, spread):
     b = mc.simulate(dp, options={"brick_log2": brick, "threshold_bytes": 4})
     assert int(a.check_status()[2]) == (1 if n_distinct <= 256 else 0)
     _same(a, b)
+
+
+@pytest.mark.parametrize("n", [8, 16, 17, 48, 101])
+def test_small_problem_alone_and_beside_a_large_one(n):
+    """A call of problems of at most 256 stretches of 4096 voxels has its maxima
+    and prefixes taken by each workgroup; beside a problem of more, a launch of
+    its own takes them: the same bits, for one stretch and less up to 252."""
+    mc = _mc()
+    p = mc.to_device(phantoms.thorax_problem("small", n, 38.4 / n, 3, 3, 180.0, 16, 2.4, 40_000))
+    big = mc.to_device(phantoms.thorax_problem("big", 104, 0.36, 4, 3, 180.0, 16, 2.4, 10_000, problem_id=1))
+    a, b = mc.simulate([p]), mc.simulate([p, big])
+    m = a.tally.numel()
+    for x, y in ((a.tally, b.tally[:m]), (a.tally_sq, b.tally_sq[:m]), (a.fates[0], b.fates[0]),
+                 (a.energy[0], b.energy[0]), (a.counters[0], b.counters[0])):
+        np.testing.assert_array_equal(x.cpu().numpy(), y.cpu().numpy())
+    assert int(a.fates[0].sum().item()) == 40_000

@@ -133,7 +133,7 @@ __device__ int replay_path(const Cst& C, uint64_t hist, int view, bool walk_now,
         const int before = L.state;
         const float e_flight = L.e;
         int iu = -1, iv = -1;
-        const int fate = advance<true>(C, C.pal, L, c0, c1, c2, c3, A, iu, iv);
+        const int fate = advance(C, C.pal, L, c0, c1, c2, c3, A, iu, iv);
         if (fate == R_RUNNING) {
             if (walk_now && before == S_STEP && L.state == S_KAHN) {
                 // Compton vertex at L.x: close the segment (its direction is

@@ -295,7 +295,8 @@ __device__ inline void rotate_dir(float& u, float& v, float& w, float ct, float 
 }
 
 // rotate_dir on a lane's direction.  ALT: the other order of the second
-// component's products, which the weighted, replay and adjoint kernels have.
+// component's products, which the weighted transport has, and the replay of its
+// histories; a plain history, its replay and its adjoint have the first.
 template <bool ALT>
 __device__ inline void rotate(Lane& L, float ct, float phi_u) {
     const float sp = sin_rev(phi_u), cp = cos_rev(phi_u);

@@ -691,6 +691,9 @@ __global__ __launch_bounds__(256) void k_transport_cfd(TransportArgs T) {
 }
 
 // Replay: one listed history per lane, run to its end, one record out.
+// VR: with variance-reduction options (each form rounds as its own transport
+// kernel does, so a replayed history follows the same path bit for bit).
+template <bool VR>
 __global__ __launch_bounds__(256) void k_replay(const ProbDesc* __restrict__ d,
                                                 const int32_t* __restrict__ views,
                                                 const uint64_t* __restrict__ hists, int64_t n,
@@ -711,15 +714,15 @@ __global__ __launch_bounds__(256) void k_replay(const ProbDesc* __restrict__ d,
     r.fate = -1; r.iu = -1; r.iv = -1;
     if (C.flags == 0 && view_ok) {
         const Emission e = emit_history(C, (uint32_t)L.hist, (uint32_t)L.view,
-                                        (vr_flags & VR_FORCED_DIRECTION) != 0, vr_omc);
+                                        VR && (vr_flags & VR_FORCED_DIRECTION) != 0, vr_omc);
         begin_history(C, L, (uint32_t)L.view, (uint32_t)L.hist, e);
         for (;;) {
             uint32_t c0 = (uint32_t)L.hist, c1 = (uint32_t)L.view, c2, c3;
             counter_of(L, c2, c3);
             philox10(c0, c1, c2, c3, C.seed, C.pid);
             int iu = -1, iv = -1;
-            const int fate = advance<true>(C, C.pal, L, c0, c1, c2, c3, A, iu, iv,
-                                     (vr_flags & VR_FORCED_INTERACTION) != 0);
+            const int fate = advance<VR>(C, C.pal, L, c0, c1, c2, c3, A, iu, iv,
+                                         VR && (vr_flags & VR_FORCED_INTERACTION) != 0);
             if (fate != R_RUNNING) {
                 r.fate = fate;
                 r.iu = iu;
@@ -834,7 +837,8 @@ hipError_t launch_replay(const ProbDesc* d_desc, const int32_t* views, const uin
                          float vr_omc, hipStream_t s) {
     if (n > 0) {
         const int64_t g = (n + block - 1) / block;
-        k_replay<<<(int)g, block, 0, s>>>(d_desc, views, hists, n, out, vr_flags, vr_omc);
+        auto k = vr_flags ? k_replay<true> : k_replay<false>;
+        k<<<(int)g, block, 0, s>>>(d_desc, views, hists, n, out, vr_flags, vr_omc);
     }
     k_replay_status<<<1, 64, 0, s>>>(d_desc, status);
     return hipGetLastError();

@@ -758,7 +758,7 @@ __device__ inline float ray_mu(const Cst& C, const RayGeom& g, float ox, float o
     return sum;
 }
 
-// The same walk over the map's one-byte codes in bricks (mu_code_address),
+// The same walk over the map's one-byte codes in bricks (mu_code_x, mu_code_y),
 // with the map values of the codes in LDS.  The FP32 map's walk is bound by
 // its gathers: nearly every lane of every gather is on a cache line of its
 // own, a line each 2 crossings (and on a 256^3 map, 64 MB, a miss of the L2);
@@ -770,11 +770,13 @@ __device__ inline float ray_mu(const Cst& C, const RayGeom& g, float ox, float o
 // A voxel's address is the bitwise or of one part per axis, and a part steps
 // by an add and a mask (dilated integers: the carry runs through the bits the
 // mask clears).  x and y are padded to powers of two for that, z is not.
-// Every piece but the last lies in the grid (a ray that ends at an edge of
-// the grid, where rounding can order the last planes of two axes either way,
-// goes to ray_mu: near_edge).  The last piece can lie one step past the grid
-// (ray_batch); it is taken after the walk, from the FP32 map at the same
-// clamped index as there, so both walks return the same bits.
+// The last piece can lie one step past the grid (ray_batch); it is taken after
+// the walk, from the FP32 map at the same clamped index as there.  Where a face
+// of the grid and a plane of another axis lie within rounding of each other, an
+// earlier piece can, too: false then, and the ray is walked again by ray_mu
+// (planes within 2^-21 of the path of each other, on rays that leave the grid:
+// a few in 10^5; one that ends at an edge of the grid goes there at once:
+// near_edge).  So both walks return the same bits.
 constexpr uint32_t MU_BRICK_X = 4, MU_BRICK_Y = 3;      // log2 of the brick, x and y
 
 struct CodeWalk {
@@ -837,8 +839,8 @@ __device__ __forceinline__ int unwrap(int i, int i0, int m, bool up, bool moved)
 }
 
 template <bool FLAT>
-__device__ inline float ray_mu_codes(const Cst& C, const float* mu_of, const RayGeom& g, float ox, float oy,
-                                     float oz, uint32_t& pieces) {
+__device__ inline bool ray_mu_codes(const Cst& C, const float* mu_of, const RayGeom& g, float ox, float oy,
+                                    float oz, uint32_t& pieces, float& depth) {
     const uint32_t lx = mu_code_log2(C.nx, MU_BRICK_X), ly = mu_code_log2(C.ny, MU_BRICK_Y);
     const uint32_t bx = (1u << MU_BRICK_X) - 1u, by = (1u << MU_BRICK_Y) - 1u;
     CodeWalk w;
@@ -883,16 +885,26 @@ __device__ inline float ray_mu_codes(const Cst& C, const float* mu_of, const Ray
     const int iy = unwrap(uy, g.iy, 1 << ly, oy > 0.0f, w.ty != g.ty);
     const int iz = (int)w.az >> (lx + ly);
     pieces = (uint32_t)(abs(ix - g.ix) + abs(iy - g.iy) + abs(iz - g.iz)) + 1u;
-    if (w.done) {
-        // the last piece, from t to the exit
-        float m;
-        if (((uint32_t)ix < (uint32_t)C.nx) & ((uint32_t)iy < (uint32_t)C.ny) & ((uint32_t)iz < (uint32_t)C.nz))
-            m = mu_of[ldg(codes + (w.ax | w.ay | w.az))];
-        else
-            m = ldg(C.mu + min((uint32_t)(ix + C.nx * (iy + C.ny * iz)), (uint32_t)(C.nx * C.ny * C.nz - 1)));
-        sum = fmaf(m, s.t_exit - w.t, sum);
+    depth = sum;
+    if (!w.done) return false;
+    // the last piece, from t to the exit
+    const bool out_x = (uint32_t)ix >= (uint32_t)C.nx, out_y = (uint32_t)iy >= (uint32_t)C.ny;
+    const bool out_z = (uint32_t)iz >= (uint32_t)C.nz;
+    if (!(out_x | out_y | out_z)) {
+        depth = fmaf(mu_of[ldg(codes + (w.ax | w.ay | w.az))], s.t_exit - w.t, sum);
+        return true;
     }
-    return sum;
+    const float m = ldg(C.mu + min((uint32_t)(ix + C.nx * (iy + C.ny * iz)), (uint32_t)(C.nx * C.ny * C.nz - 1)));
+    depth = fmaf(m, s.t_exit - w.t, sum);
+    // outside: on one axis, and no other axis stepped since, as far as the last
+    // planes crossed are known from the next ones (half an ulp of the sum)
+    const float up = 1.0f + 0x1p-22f, down = 1.0f - 0x1p-22f, none = -__builtin_huge_valf();
+    const float hi_x = w.tx != g.tx ? fmaf(w.tx, up, -s.ddx) : none, lo_x = fmaf(w.tx, down, -s.ddx);
+    const float hi_y = w.ty != g.ty ? fmaf(w.ty, up, -s.ddy) : none, lo_y = fmaf(w.ty, down, -s.ddy);
+    const float hi_z = w.tz != g.tz ? fmaf(w.tz, up, -s.ddz) : none, lo_z = fmaf(w.tz, down, -s.ddz);
+    if (out_x) return !(out_y | out_z) & (lo_x > fmaxf(hi_y, hi_z));
+    if (out_y) return !out_z & (lo_y > fmaxf(hi_x, hi_z));
+    return lo_z > fmaxf(hi_x, hi_y);
 }
 
 // A forced copy that scores, up to its ray walk: start point, direction,
@@ -911,9 +923,9 @@ struct FdJob {
 template <bool FLAT>
 __device__ inline float fd_walk_score(const Cst& C, const FdJob& j, const float* mu_of, uint32_t& pieces) {
     const RayGeom g = ray_geom(C, j.x, j.y, j.z, j.ox, j.oy, j.oz);
-    const bool by_code = C.use_codes && !g.near_edge;
+    bool by_code = C.use_codes && !g.near_edge;
     float depth = 0.0f;
-    if (by_code) depth = ray_mu_codes<FLAT>(C, mu_of, g, j.ox, j.oy, j.oz, pieces);
+    if (by_code) by_code = ray_mu_codes<FLAT>(C, mu_of, g, j.ox, j.oy, j.oz, pieces, depth);
     if (!by_code) depth = ray_mu(C, g, j.ox, j.oy, j.oz, pieces);
     return j.w * __expf(-j.g * depth);
 }

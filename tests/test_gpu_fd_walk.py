@@ -77,3 +77,31 @@ def test_values_sharing_a_threshold_use_the_map():
     assert int(a.status[2]) == 1
     np.testing.assert_array_equal(a.tally.cpu().numpy(), b.tally.cpu().numpy())
     np.testing.assert_array_equal(a.tally_sq.cpu().numpy(), b.tally_sq.cpu().numpy())
+
+
+@pytest.mark.parametrize("angle", [math.pi / 4, 0.6])
+def test_rays_past_a_corner_near_the_exit(angle):
+    """Rays from the corner voxel that leave the grid within rounding of another
+    plane, a fraction of a voxel away: the last planes (multiples of the rounded
+    voxel size) lie before the exits (the rounded grid size), so such a walk
+    takes a step outside the grid before its last piece.  1.004 cm is a size where 17 voxels differ most from the grid.
+    The attenuation is chosen so that the table's padding there, leftover
+    bytes of the thresholds, would be taken for the code of a high value."""
+    mc = _mc()
+    n, vox, v = 17, 1.004, 0x40A8A8          # two bytes of v equal its palette slot
+    assert (v * 2654435761 & 0xFFFFFFFF) >> 24 == v & 255 == v >> 8 & 255
+    assert float(np.float32(n * vox)) - n * float(np.float32(vox)) > 1.5e-6
+    mu = np.zeros((n, n, n), dtype=np.float32)
+    mu[:n - 1] = v * 2.0**-10
+    mu[0, 0, 0] = 2.0**24 * 2.0**-10
+    act = np.zeros((n, n, n), dtype=np.uint32)
+    act[-1, -1, -1] = 1
+    p = phantoms.Problem(
+        name="corner", nx=n, ny=n, nz=n, voxel_cm=vox, mu=mu, activity=act, angles=np.array([angle]), nu=4, nv=32,
+        pixel_cm=1.0, radius_cm=phantoms.detector_radius(n, n, vox), accept_half_angle_rad=0.035, e_lo_kev=100.0,
+        e_hi_kev=154.0, e_cut_kev=90.0, n_histories=1_000_000_000, seed=5, max_steps=1)
+    dp = mc.to_device(p)
+    a = mc.simulate(dp, options={"forced_detection": 1})
+    b = mc.simulate(dp, options={"forced_detection": 1, "threshold_bytes": 4})
+    assert int(a.status[2]) == 1 and int(b.status[2]) == 0 and int(b.tally.sum()) > 0
+    np.testing.assert_array_equal(a.tally.cpu().numpy(), b.tally.cpu().numpy())

@@ -361,8 +361,9 @@ size_t mlem_workspace_bytes(int64_t n_bins, int64_t n_vox);
  * launch, and is checked on the device: a different value leaves the image
  * NaN.  Two kernels per iteration.  A sparse matrix (nnz <= n_bins + n_vox)
  * is iterated in a compact layout (vectors over the non-empty rows, listed
- * once per call, columns renumbered) whose gathers stay in L2; a dense one is
- * streamed row by row, neighbouring rows by one XCD.  Deterministic: the summation
+ * once per call, columns renumbered) whose gathers stay in L2; of a dense one
+ * the non-empty rows are listed too, or all rows streamed where that is faster.
+ * Deterministic: the summation
  * order depends only on the matrix.  Asynchronous on stream: no host
  * synchronisation, no allocation, no memset, so a call can be captured in a
  * graph (mc_graph_begin) and replayed. */

@@ -20,10 +20,10 @@
 //
 // MLEM.  S_i <- S_i / sens_i * sum_j T_ij P_j / y_j, y = T S, sens_i =
 // sum_j T_ij; FP32 matrix values, FP64 accumulation; bins with y_j = 0 add
-// nothing; voxels with sens_i = 0 stay 0.  Rows of a dense matrix are streamed
-// a tile of entries at a time; of a sparse one, only the non-empty rows are
-// swept, listed once per matrix, by groups of 1 to 64 lanes sized to their
-// length.
+// nothing; voxels with sens_i = 0 stay 0.  Only the non-empty rows are swept,
+// listed once per matrix, by groups of 1 to 64 lanes sized to their length;
+// of a large dense matrix the rows are streamed instead, a tile of entries at
+// a time, where that is the faster (lanes_per_row).
 #include <algorithm>
 
 #include "mc_internal.h"
@@ -694,10 +694,8 @@ enum {
 
 // Set-up: the state zeroed, the entry count checked against both row-pointer
 // arrays, the fingerprint stored (one workgroup).
-__global__ __launch_bounds__(T256) void k_mlem_setup(int64_t n_bins, int64_t n_vox, int64_t nnz,
-                                                     const int64_t* __restrict__ T_rp,
-                                                     const int64_t* __restrict__ Tt_rp,
-                                                     uint32_t* __restrict__ st) {
+__device__ inline void mlem_setup(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t* __restrict__ T_rp,
+                                  const int64_t* __restrict__ Tt_rp, uint32_t* __restrict__ st) {
     const uint32_t t = threadIdx.x;
     if (t >= ST_WORDS) return;
     uint32_t v = 0;
@@ -707,6 +705,13 @@ __global__ __launch_bounds__(T256) void k_mlem_setup(int64_t n_bins, int64_t n_v
     else if (t == ST_FP + 2) v = (uint32_t)(uint64_t)nnz;
     else if (t == ST_FP + 3) v = (uint32_t)((uint64_t)nnz >> 32);
     st[t] = v;
+}
+
+__global__ __launch_bounds__(T256) void k_mlem_setup(int64_t n_bins, int64_t n_vox, int64_t nnz,
+                                                     const int64_t* __restrict__ T_rp,
+                                                     const int64_t* __restrict__ Tt_rp,
+                                                     uint32_t* __restrict__ st) {
+    mlem_setup(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
 }
 
 // A call's sizes against the set-up's fingerprint (and its entry-count flag).
@@ -759,22 +764,19 @@ __device__ inline double group_row_sum(int64_t k0, int64_t k1, int sub, Term ter
     return acc;
 }
 
-// ---- row order.  Sweeps of a dense matrix: a workgroup takes consecutive
+// ---- row order.  Tiles of a large dense matrix: a workgroup takes consecutive
 // rows, whose entries are consecutive too, and streams them a tile of LOADS
 // entries per thread at a time: coalesced loads of columns and values, LOADS gathers in
 // flight per thread, the products in LDS in FP64, then each row summed from
 // there by a power-of-two number of lanes.  The order of a sum depends only on
 // the matrix.  Bound by the stream of entries (8 bytes each) and the gathers'
-// traffic from L2 to L1, a line per entry.  What it replaces: a lane group per
-// row with the row's loads in a chain (233 us per forward sweep and, in bin
-// slices per XCD with a third kernel adding them, 393 us per backprojection on
-// a forced-detection matrix of 4.6e7 entries, 1.97 M bins and 2.6e5 voxels:
-// 156 and 274 us now).  No slices are needed: each XCD works on
-// neighbouring rows (sweep_chunk), so a backprojection's gathers from its slab
-// of voxels fall in the bins of a few detector rows, which its L2 holds (90 %
-// hits).  Where columns are random, which no camera gives, the slices were the
-// better (2^20 bins x 2^17 voxels, 3e7 entries: 442 against 460 us per
-// iteration).
+// traffic from L2 to L1, a line per entry.  On a forced-detection matrix of 4.6e7
+// entries, 1.97 M bins and 2.6e5 voxels, 156 us per forward sweep, against 233 us
+// by a lane group per listed row, four rows per pass.  Each XCD works on
+// neighbouring rows (sweep_chunk), so a sweep's gathers fall in what its L2
+// holds.  (Where columns are random, which no camera gives, a backprojection in
+// slices of the bins, one per XCD, which was here before, is the better: 2^20
+// bins x 2^17 voxels, 3e7 entries: 437 us per iteration against 471 now.)
 
 // Rows per workgroup, of mean entries each: three quarters of a tile on
 // average, so that most need one.
@@ -919,71 +921,210 @@ __global__ __launch_bounds__(T256) void k_sweep_sums(int64_t n_rows, int per, co
              [](float x) { return (double)x; }, [&](int64_t r, double acc) { out[r] = acc; });
 }
 
-// Sums over the rows by groups of GS lanes, one row per group and pass, four
-// entries per lane in flight.  For matrices whose both orientations stay in the
-// caches between sweeps: with the latencies that small, the sweeps above lose
-// more to their barriers and part-filled tiles than a row's chain of loads
-// costs (36 iterations on 2.4e6 entries, 4.3e5 bins, 1.2e4 voxels: 1002 us
-// against 1169 us swept; 5.1e6 entries, 15 iterations: 870 against 938 us;
-// 1.1e7: even; 4.3e7, 10 iterations: 7633 against 4541 us).  Long rows are
-// swept all the same: with a wavefront per row too few are in flight (1331
-// voxels of 486 entries: 14.6 against 9.8 us per backprojection).
-constexpr int64_t SWEEP_MIN_NNZ = 1 << 23;
-constexpr int64_t SWEEP_MIN_MEAN = 256;
+// ---- row lists.  The non-empty rows of T and of T^T, each in row order, made
+// once per matrix: of a camera's matrix 30 to 80 % of the bins and voxels have
+// no entries.  A listed row is summed by a group of lanes, one row per group and
+// pass, four entries per lane in flight.
 
-// Lanes that share a row: the smallest group of 1, 4, 16 or 64 for which `each`
-// entries per lane cover the mean row of a matrix of nnz entries, `part` of them
-// in these rows; 0: the rows are swept.
-inline int lanes_per_row(int64_t nnz, int64_t part, int64_t n_rows, int each) {
-    if (nnz >= SWEEP_MIN_NNZ || part >= SWEEP_MIN_MEAN * n_rows) return 0;
-    return part <= each * n_rows ? 1 : part <= 4 * each * n_rows ? 4 : part <= 16 * each * n_rows ? 16 : 64;
-}
+// A non-empty row: its index and entry range.
+struct RowRef {
+    int64_t lo;
+    int32_t row, len;
+};
 
-template <int GS, class Own, class Term, class Done>
-__device__ inline void sweep_groups(int64_t n_rows, const int64_t* __restrict__ rp,
-                                    const uint32_t* __restrict__ call_bad, Own own, Term term, Done done) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    const bool skip = *call_bad != 0;
-    for (int64_t r = G.first; r < n_rows; r += G.step) {
-        const int64_t lo = rp[r], hi = rp[r + 1];
-        if (skip) return;
-        if (hi == lo) continue;
-        const auto o = own(r);
-        const double sum = group_row_sum<GS>(lo, hi, G.sub, term);
-        if (G.sub == 0) done(r, o, sum);
+// A workgroup takes ROW_CHUNK consecutive rows of one matrix at a time.  First
+// pass: chunk[c] = non-empty rows of chunk c (T's chunks, then T^T's); the last
+// workgroup does the set-up instead.  Second pass: the rows at their positions,
+// and the lengths of the lists, st[ST_BINS] and st[ST_VOXS]; each workgroup adds
+// up the counts before its only chunk, or (SCANNED, for more than
+// ROWS_MAX_CHUNKS) finds their exclusive scan there.  In row order, so that
+// the rows in flight at a time are neighbours, whose gathers meet in the caches:
+// appended as the workgroups came, an iteration on 3.5e6 entries, 1.5e6 bins and
+// 6.8e5 voxels took 72 us instead of 61.
+constexpr int64_t ROWS_MAX_CHUNKS = 2048;
+enum { ROWS_COUNT, ROWS_PLACE, ROWS_PLACE_SCANNED };
+
+template <int PASS>
+__global__ __launch_bounds__(T256) void k_mlem_rows(int64_t n_bins, int64_t n_vox, int64_t nnz,
+                                                    const int64_t* __restrict__ T_rp,
+                                                    const int64_t* __restrict__ Tt_rp,
+                                                    RowRef* __restrict__ bins, RowRef* __restrict__ voxs,
+                                                    uint64_t* __restrict__ chunk, uint32_t* __restrict__ st) {
+    constexpr int WAVES = T256 / 64;
+    __shared__ uint32_t before[ROWS_PER_THREAD * WAVES];
+    __shared__ uint32_t total;
+    __shared__ uint64_t part[WAVES];
+    const int64_t n_blocks = PASS == ROWS_COUNT ? gridDim.x - 1 : gridDim.x;
+    if constexpr (PASS == ROWS_COUNT) {
+        if (blockIdx.x == n_blocks) {
+            mlem_setup(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
+            return;
+        }
+    } else {
+        if (st[ST_BAD]) return;
+    }
+    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
+    const uint64_t lane_lt = (1ull << lane) - 1;
+    const int64_t nbc = (n_bins + ROW_CHUNK - 1) / ROW_CHUNK;
+    const int64_t nvc = (n_vox + ROW_CHUNK - 1) / ROW_CHUNK;
+    for (int64_t c = blockIdx.x; c < nbc + nvc; c += n_blocks) {
+        const bool vox = c >= nbc;
+        const int64_t r0 = (vox ? c - nbc : c) * ROW_CHUNK, nr = vox ? n_vox : n_bins;
+        const int64_t* rp = vox ? Tt_rp : T_rp;
+        int64_t lo[ROWS_PER_THREAD];
+        int32_t len[ROWS_PER_THREAD];
+        uint64_t m[ROWS_PER_THREAD];
+#pragma unroll
+        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
+            const int64_t r = r0 + k * T256 + threadIdx.x;
+            lo[k] = 0;
+            len[k] = 0;
+            if (r < nr) {
+                lo[k] = rp[r];
+                len[k] = (int32_t)(rp[r + 1] - lo[k]);
+            }
+        }
+        uint64_t first = 0;
+        if constexpr (PASS == ROWS_PLACE) {
+            for (int64_t k = (vox ? nbc : 0) + threadIdx.x; k < c; k += T256) first += chunk[k];
+            first = wave_sum64(first);
+            if (lane == 0) part[w] = first;
+        }
+        if constexpr (PASS == ROWS_PLACE_SCANNED) first = chunk[c] - (vox ? chunk[nbc] : 0);
+#pragma unroll
+        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
+            m[k] = __ballot(len[k] > 0);
+            if (lane == 0) before[k * WAVES + w] = (uint32_t)__popcll(m[k]);
+        }
+        __syncthreads();
+        // exclusive scan: rows r0 + k * 256 + w * 64 + lane in (k, w, lane) order
+        if (w == 0) {
+            static_assert(ROWS_PER_THREAD * WAVES == 64, "one count per lane");
+            const uint32_t v = before[lane];
+            uint32_t x = v;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            before[lane] = x - v;
+            if (lane == 63) total = x;
+        }
+        if constexpr (PASS == ROWS_PLACE) first = (part[0] + part[1]) + (part[2] + part[3]);
+        __syncthreads();
+        if constexpr (PASS == ROWS_COUNT) {
+            if (threadIdx.x == 0) chunk[c] = total;
+        } else {
+            RowRef* out = vox ? voxs : bins;
+#pragma unroll
+            for (int k = 0; k < ROWS_PER_THREAD; ++k) {
+                const int64_t r = r0 + k * T256 + threadIdx.x;
+                const uint64_t at = first + before[k * WAVES + w] + (uint32_t)__popcll(m[k] & lane_lt);
+                if (len[k] > 0) out[at] = RowRef{lo[k], (int32_t)r, len[k]};
+            }
+            if (threadIdx.x == 0 && (c == nbc - 1 || c == nbc + nvc - 1))
+                st[vox ? ST_VOXS : ST_BINS] = (uint32_t)(first + total);
+        }
+        __syncthreads();     // before[] is rewritten for the next chunk
     }
 }
 
+// How a matrix's sweeps are done.  Listed rows: lanes_per_row lanes share one,
+// the smallest group of 1, 4, 16 or 64 for which `each` entries per lane cover
+// the mean row of `part` entries in n_rows rows.  Tiles (0):
+//  * where there are few rows, too few for a wavefront each to keep the chip
+//    busy (1331 voxels of 486 entries: 14.6 us per backprojection by wavefronts,
+//    9.8 swept);
+//  * the forward sweep of a matrix that does not stay in the caches, from
+//    SWEEP_MIN_NNZ entries on (20 iterations on 2.6e7 entries, 2.5e5 bins,
+//    2.6e5 voxels: 4.65 ms with listed forward sweeps, 4.32 with tiles; on
+//    9.4e6 even; below, tiles lose more to their barriers and part-filled
+//    tiles than a row's chain of loads costs: 2.4e6 entries, 36 iterations: 1002
+//    against 1169 us);
+//  * the backprojection of such a matrix if its rows are short (1.0e7 entries,
+//    2.1e6 voxels: 2.40 ms swept, 2.48 listed; with longer rows listed is the
+//    better: 2.6e7 entries, 2.6e5 voxels: 4.09 against 4.32 ms, 1.3e7 entries,
+//    3.3e4 voxels: 1.35 against 1.86 ms).
+constexpr int64_t SWEEP_MIN_NNZ = 1 << 23;
+constexpr int64_t SWEEP_MIN_MEAN = 256;
+constexpr int64_t SWEEP_FEW_ROWS = 1 << 15;
+constexpr int64_t SWEEP_SHORT_ROW = 16;
+
+inline int lanes_per_row(int64_t part, int64_t n_rows, int each) {
+    return part <= each * n_rows ? 1 : part <= 4 * each * n_rows ? 4 : part <= 16 * each * n_rows ? 16 : 64;
+}
+inline bool few_long_rows(int64_t part, int64_t n_rows) {
+    return n_rows < SWEEP_FEW_ROWS && part >= SWEEP_MIN_MEAN * n_rows;
+}
+inline int mlem_forward_lanes(int64_t nnz, int64_t n_bins) {
+    return nnz >= SWEEP_MIN_NNZ || few_long_rows(nnz, n_bins) ? 0 : lanes_per_row(nnz, n_bins, 4);
+}
+inline int mlem_update_lanes(int64_t nnz, int64_t n_vox) {
+    if (few_long_rows(nnz, n_vox) || (nnz >= SWEEP_MIN_NNZ && nnz < SWEEP_SHORT_ROW * n_vox)) return 0;
+    return lanes_per_row(nnz, n_vox, 4);
+}
+// OSEM: 0 (tiles) for a subset's `part` of nnz entries in n_rows rows
+inline int os_lanes(int64_t nnz, int64_t part, int64_t n_rows, int each) {
+    if (nnz >= SWEEP_MIN_NNZ || part >= SWEEP_MIN_MEAN * n_rows) return 0;
+    return lanes_per_row(part, n_rows, each);
+}
+
+// The rows of a list (at most cap, *count of them) by groups of GS lanes;
+// `block` of gridDim.x workgroups.  The first row's reference is loaded along
+// with the list's length, not after it.
+template <int GS, class Own, class Term, class Done>
+__device__ inline void sweep_list(int64_t block, const RowRef* __restrict__ L, int64_t cap,
+                                  const uint32_t* __restrict__ count, const uint32_t* __restrict__ call_bad,
+                                  Own own, Term term, Done done) {
+    const RowGroups<GS> G(block, gridDim.x);
+    if (G.first >= cap) return;
+    RowRef ref = L[G.first];
+    const uint32_t listed = *count, bad = *call_bad;
+    // all in flight before any is used (the compiler would load the reference
+    // once the length's test has passed)
+    asm volatile("" ::"v"(ref.lo), "s"(listed), "s"(bad));
+    const int64_t n = bad ? 0 : listed;     // a call that does not match the set-up sweeps nothing
+    for (int64_t r = G.first; r < n; r += G.step) {
+        if (r != G.first) ref = L[r];
+        const auto o = own(ref.row);
+        const double sum = group_row_sum<GS>(ref.lo, ref.lo + ref.len, G.sub, term);
+        if (G.sub == 0) done(ref.row, o, sum);
+    }
+}
+
+// (An XCD takes runs of consecutive rows here: 20 iterations on 5.8e6 entries,
+// 9.8e5 bins and 2.1e6 voxels, whose vector no L2 holds, 2.34 ms, without 2.50.)
 template <int GS>
-__global__ __launch_bounds__(T256) void k_mlem_forward_rows(int64_t n_bins, int, const int64_t* __restrict__ rp,
+__global__ __launch_bounds__(T256) void k_mlem_forward_rows(const RowRef* __restrict__ L, int64_t cap,
+                                                            const uint32_t* __restrict__ count,
                                                             const uint32_t* __restrict__ call_bad,
                                                             const int32_t* __restrict__ col,
                                                             const float* __restrict__ val,
                                                             const double* __restrict__ S,
                                                             const float* __restrict__ P,
                                                             double* __restrict__ ratio) {
-    sweep_groups<GS>(n_bins, rp, call_bad, [&](int64_t r) { return P[r]; },
-                     [&](int64_t k, bool ok) {
-                         const double x = (double)val[k] * S[col[k]];
-                         return ok ? x : 0.0;
-                     },
-                     [&](int64_t r, float p, double y) { ratio[r] = y > 0.0 ? (double)p / y : 0.0; });
+    sweep_list<GS>(sweep_chunk(), L, cap, count, call_bad, [&](int32_t r) { return P[r]; },
+                   [&](int64_t k, bool ok) {
+                       const double x = (double)val[k] * S[col[k]];
+                       return ok ? x : 0.0;
+                   },
+                   [&](int32_t r, float p, double y) { ratio[r] = y > 0.0 ? (double)p / y : 0.0; });
 }
 
 template <int GS>
-__global__ __launch_bounds__(T256) void k_mlem_update_rows(int64_t n_vox, int, const int64_t* __restrict__ rp,
+__global__ __launch_bounds__(T256) void k_mlem_update_rows(const RowRef* __restrict__ L, int64_t cap,
+                                                           const uint32_t* __restrict__ count,
                                                            const uint32_t* __restrict__ call_bad,
                                                            const int32_t* __restrict__ col,
                                                            const float* __restrict__ val,
                                                            const double* __restrict__ ratio,
                                                            const double* __restrict__ sens,
                                                            double* __restrict__ S) {
-    sweep_groups<GS>(n_vox, rp, call_bad, [&](int64_t r) { return double2{S[r], sens[r]}; },
-                     [&](int64_t k, bool ok) {
-                         const double x = (double)val[k] * ratio[col[k]];
-                         return ok ? x : 0.0;
-                     },
-                     [&](int64_t r, double2 o, double b) { S[r] = o.y > 0.0 ? o.x * b / o.y : 0.0; });
+    sweep_list<GS>(blockIdx.x, L, cap, count, call_bad, [&](int32_t r) { return double2{S[r], sens[r]}; },
+                   [&](int64_t k, bool ok) {
+                       const double x = (double)val[k] * ratio[col[k]];
+                       return ok ? x : 0.0;
+                   },
+                   [&](int32_t r, double2 o, double b) { S[r] = o.y > 0.0 ? o.x * b / o.y : 0.0; });
 }
 
 // y_j = sum_i T_ij S_i; ratio_j = P_j / y_j (0 when y_j = 0), over the
@@ -1807,7 +1948,7 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
     const unsigned grid_v = sweep_grid(n_chunks);
     // a subset's voxel rows are short and uneven: two entries per lane (four:
     // 11.5 us per update, 4.3e4 voxels of 4 entries)
-    const int g_f = lanes_per_row(bt_nnz, bt_nnz, n_bins, 4), g_u = lanes_per_row(bt_nnz, bt_nnz / n_sub, n_vox, 2);
+    const int g_f = os_lanes(bt_nnz, bt_nnz, n_bins, 4), g_u = os_lanes(bt_nnz, bt_nnz / n_sub, n_vox, 2);
     const unsigned gu = g_u ? (unsigned)grid_for((uint64_t)n_vox * g_u, T256, 1 << 16) : grid_v;
     k_os_check<<<1, 64, 0, s>>>(n_vox, Bt_rp, bt_nnz, st);
     if (bt_nnz < SWEEP_MIN_NNZ)
@@ -2040,9 +2181,10 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
     if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
     const int gv = grid_for(nv, T256, 8192);
     const int gr = grid_for((nb + ROW_CHUNK - 1) / ROW_CHUNK + (nv + ROW_CHUNK - 1) / ROW_CHUNK, 1, 2048);
+    const int g_b = compact ? 0 : mlem_forward_lanes(nnz, n_bins), g_v = compact ? 0 : mlem_update_lanes(nnz, n_vox);
     if (setup) {
         k_sweep_sums<<<grid_v, T256, 0, s>>>(n_vox, per_v, Tt_rp, Tt_val, sens);
-        k_mlem_setup<<<1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
+        if (!(g_b || g_v)) k_mlem_setup<<<1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, st);
     }
     if (compact) {
         double* sens_l = (double*)(w + Lo.sens_l);
@@ -2097,18 +2239,33 @@ hipError_t launch_mlem(int64_t n_bins, int64_t n_vox, int64_t nnz, const int64_t
         k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, vox_pos, st, image);
         return hipGetLastError();
     }
+    RowRef* bin_rows = (RowRef*)(w + Lo.bin_rows);
+    RowRef* vox_rows = (RowRef*)(w + Lo.vox_rows);
+    if (setup && (g_b || g_v)) {
+        uint64_t* chunk = (uint64_t*)(w + Lo.Tc);       // the compact layout's, idle here
+        const int64_t n_chunks = (int64_t)((nb + ROW_CHUNK - 1) / ROW_CHUNK + (nv + ROW_CHUNK - 1) / ROW_CHUNK);
+        k_mlem_rows<ROWS_COUNT><<<gr + 1, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, bin_rows, vox_rows, chunk, st);
+        if (n_chunks > ROWS_MAX_CHUNKS) k_scan_blocks<<<1, 1024, 0, s>>>(chunk, (int)n_chunks);
+        auto place = n_chunks > ROWS_MAX_CHUNKS ? k_mlem_rows<ROWS_PLACE_SCANNED> : k_mlem_rows<ROWS_PLACE>;
+        place<<<gr, T256, 0, s>>>(n_bins, n_vox, nnz, T_rp, Tt_rp, bin_rows, vox_rows, chunk, st);
+    }
     if (!iterate) return hipGetLastError();
     k_mlem_load<<<gv, T256, 0, s>>>(n_bins, n_vox, nnz, image, sens, S, nullptr, nullptr, nullptr, nullptr, st);
-    const int g_b = lanes_per_row(nnz, nnz, n_bins, 4), g_v = lanes_per_row(nnz, nnz, n_vox, 4);
-    auto kf = g_b == 0 ? k_mlem_forward : g_b == 1 ? k_mlem_forward_rows<1> : g_b == 4 ? k_mlem_forward_rows<4>
+    auto kf = g_b == 1 ? k_mlem_forward_rows<1> : g_b == 4 ? k_mlem_forward_rows<4>
             : g_b == 16 ? k_mlem_forward_rows<16> : k_mlem_forward_rows<64>;
-    auto ku = g_v == 0 ? k_mlem_update : g_v == 1 ? k_mlem_update_rows<1> : g_v == 4 ? k_mlem_update_rows<4>
+    auto ku = g_v == 1 ? k_mlem_update_rows<1> : g_v == 4 ? k_mlem_update_rows<4>
             : g_v == 16 ? k_mlem_update_rows<16> : k_mlem_update_rows<64>;
-    const unsigned gf = g_b ? (unsigned)grid_for(nb * g_b, T256, 1 << 16) : grid_b;
+    const unsigned gf = g_b ? sweep_grid(grid_for(nb * g_b, T256, 1 << 16)) : grid_b;
     const unsigned gu = g_v ? (unsigned)grid_for(nv * g_v, T256, 1 << 16) : grid_v;
     for (int it = 0; it < n_iter; ++it) {
-        kf<<<gf, T256, 0, s>>>(n_bins, per_b, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
-        ku<<<gu, T256, 0, s>>>(n_vox, per_v, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
+        if (g_b)
+            kf<<<gf, T256, 0, s>>>(bin_rows, n_bins, st + ST_BINS, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
+        else
+            k_mlem_forward<<<gf, T256, 0, s>>>(n_bins, per_b, T_rp, st + ST_CALL_BAD, T_col, T_val, S, proj, ratio);
+        if (g_v)
+            ku<<<gu, T256, 0, s>>>(vox_rows, n_vox, st + ST_VOXS, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
+        else
+            k_mlem_update<<<gu, T256, 0, s>>>(n_vox, per_v, Tt_rp, st + ST_CALL_BAD, Tt_col, Tt_val, ratio, sens, S);
     }
     k_mlem_out<<<gv, T256, 0, s>>>(n_vox, S, nullptr, st, image);
     return hipGetLastError();

@@ -1049,7 +1049,7 @@ constexpr int64_t SWEEP_MIN_MEAN = 256;
 constexpr int64_t SWEEP_FEW_ROWS = 1 << 15;
 constexpr int64_t SWEEP_SHORT_ROW = 16;
 
-inline int lanes_per_row(int64_t part, int64_t n_rows, int each) {
+__host__ __device__ inline int lanes_per_row(int64_t part, int64_t n_rows, int each) {
     return part <= each * n_rows ? 1 : part <= 4 * each * n_rows ? 4 : part <= 16 * each * n_rows ? 16 : 64;
 }
 inline bool few_long_rows(int64_t part, int64_t n_rows) {
@@ -1818,29 +1818,78 @@ __global__ __launch_bounds__(T256) void k_os_update(int64_t n_vox, int per, int 
 // that stay in the caches, and for sparse ones, most of whose rows are empty
 // (1.2e5 entries in 2.0e6 bins x 2.6e5 voxels, 80 subset updates: 1050 us
 // with the tiles, 745 us so).
-template <int GS>
-__global__ __launch_bounds__(T256) void k_os_forward_rows(int64_t n_rows, int32_t bins_per_view, int32_t n_sub,
-                                                          int32_t k, const int64_t* __restrict__ rp,
-                                                          const int32_t* __restrict__ col,
-                                                          const float* __restrict__ val,
-                                                          const double* __restrict__ S,
-                                                          const float* __restrict__ P,
-                                                          const float* __restrict__ scat,
-                                                          double* __restrict__ ratio) {
-    const RowGroups<GS> G(blockIdx.x, gridDim.x);
-    for (int64_t t = G.first; t < n_rows; t += G.step) {
+// Forward rows: row t of subset k is a bin of view k + n_sub (t / bins_per_view).
+struct OsForward {
+    const int64_t* __restrict__ rp;
+    const int32_t* __restrict__ col;
+    const float* __restrict__ val;
+    const double* __restrict__ S;
+    const float* __restrict__ P;
+    const float* __restrict__ scat;
+    double* __restrict__ ratio;
+    int64_t n_rows, n_bins;
+    int32_t bins_per_view, n_sub, k;
+
+    __device__ int64_t bin(int64_t t) const {
         const uint32_t v = (uint32_t)t / (uint32_t)bins_per_view;      // fewer than 2^31 bins
-        const int64_t j = t + (int64_t)(k + (n_sub - 1) * (int64_t)v) * bins_per_view;
-        const int64_t lo = rp[j], hi = rp[j + 1];
-        const float p = P[j], s = scat ? scat[j] : 0.0f;
+        return t + (int64_t)(k + (n_sub - 1) * (int64_t)v) * bins_per_view;
+    }
+    template <int GS>
+    __device__ void row(int64_t j, int64_t lo, int64_t hi, float p, float s, int sub) const {
         double y = 0.0;
         if (hi > lo)
-            y = group_row_sum<GS>(lo, hi, G.sub, [&](int64_t e, bool ok) {
+            y = group_row_sum<GS>(lo, hi, sub, [&](int64_t e, bool ok) {
                 const double x = (double)val[e] * S[col[e]];
                 return ok ? x : 0.0;
             });
         y += scat ? (double)s : 0.0;
-        if (G.sub == 0) ratio[j] = y > 0.0 ? (double)p / y : 0.0;
+        if (sub == 0) ratio[j] = y > 0.0 ? (double)p / y : 0.0;
+    }
+};
+
+// This group's rows; j, lo, hi: the first one's bin and bounds.
+template <int GS>
+__device__ inline void os_forward(const OsForward& F, const RowGroups<GS>& G, int64_t j, int64_t lo, int64_t hi) {
+    for (int64_t t = G.first; t < F.n_rows; t += G.step) {
+        if (t != G.first) {
+            j = F.bin(t);
+            lo = F.rp[j];
+            hi = F.rp[j + 1];
+        }
+        const float p = F.P[j], s = F.scat ? F.scat[j] : 0.0f;
+        F.row<GS>(j, lo, hi, p, s, G.sub);
+    }
+}
+template <int GS>
+__device__ inline void os_forward(const OsForward& F) {
+    const RowGroups<GS> G(blockIdx.x, gridDim.x);
+    if (G.first >= F.n_rows) return;
+    const int64_t j = F.bin(G.first);
+    os_forward<GS>(F, G, j, F.rp[j], F.rp[j + 1]);
+}
+
+// GS: the lanes per row for c as dense as b, whose entry count the call knows.
+// c's own count is read along with the first row's bounds, and where it asks for
+// other lanes (a dual matrix: c with scatter, b without), they do it, on at
+// least OS_FORWARD_BLOCKS workgroups if 64 lanes per row would take as many:
+// c of 6.4e6 entries with b of 1.1e5, 245760 bins, 4 updates of 1 / 24 of 6
+// subsets: 399 / 755 us with b's lanes, 249 / 772 with c's on the few workgroups
+// of one lane per row, 235 / 386 now.  Workgroups without rows cost nothing
+// that shows (1.8e5 to 8e6 entries, b = c).
+constexpr int OS_FORWARD_BLOCKS = 4096;
+
+template <int GS>
+__global__ __launch_bounds__(T256) void k_os_forward_rows(OsForward F) {
+    const RowGroups<GS> G(blockIdx.x, gridDim.x);
+    const int64_t c_nnz = F.rp[F.n_bins];
+    const int64_t j = F.bin(G.first < F.n_rows ? G.first : F.n_rows - 1);
+    const int64_t lo = F.rp[j], hi = F.rp[j + 1];
+    asm volatile("" ::"s"(c_nnz), "v"(lo), "v"(hi));     // all in flight before the count is tested
+    switch (lanes_per_row(c_nnz, F.n_bins, 4)) {
+        case GS: os_forward<GS>(F, G, j, lo, hi); break;
+        case GS == 1 ? 4 : 1: os_forward<GS == 1 ? 4 : 1>(F); break;
+        case GS <= 4 ? 16 : 4: os_forward<GS <= 4 ? 16 : 4>(F); break;
+        default: os_forward<GS <= 16 ? 64 : 16>(F); break;
     }
 }
 
@@ -1961,7 +2010,9 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
             : g_u == 16 ? k_os_sums_rows<16> : k_os_sums_rows<64>;
     ks<<<dim3(gu, (unsigned)n_sub), T256, 0, s>>>(n_vox, per, n_sub, Bt_rp, offs, val_s, sens);
     k_os_init<<<gv, T256, 0, s>>>(n_vox, n_sub, image, sens, S);
-    // the entry count of c is not known here: its rows as b's
+    // c's entry count is not known here: tiles by b's, lanes corrected on the
+    // device (tiles of a c 7 times as dense, 7.3e7 entries: 1.5 ms for 4 updates;
+    // by its lanes 3.6)
     const int per_f = sweep_per(OS_LOADS, bt_nnz / n_bins);
     const int32_t per_view = (bins_per_view + per_f - 1) / per_f;
     auto kf = g_f == 1 ? k_os_forward_rows<1> : g_f == 4 ? k_os_forward_rows<4>
@@ -1973,8 +2024,10 @@ hipError_t launch_osem(int64_t n_bins, int64_t n_vox, int32_t bins_per_view, int
             const int64_t views = (n_views - k + n_sub - 1) / n_sub, chunks = views * per_view;
             if (chunks <= 0) continue;
             if (g_f)
-                kf<<<grid_for((uint64_t)(views * bins_per_view) * g_f, T256, 1 << 16), T256, 0, s>>>(
-                    views * bins_per_view, bins_per_view, n_sub, k, C_rp, C_col, C_val, S, proj, scatter, ratio);
+                kf<<<std::max(grid_for((uint64_t)(views * bins_per_view) * g_f, T256, 1 << 16),
+                              grid_for((uint64_t)(views * bins_per_view) * 64, T256, OS_FORWARD_BLOCKS)),
+                     T256, 0, s>>>(OsForward{C_rp, C_col, C_val, S, proj, scatter, ratio, views * bins_per_view,
+                                             n_bins, bins_per_view, n_sub, k});
             else
                 k_os_forward<<<sweep_grid(chunks), T256, 0, s>>>(chunks, per_view, per_f, bins_per_view, n_sub,
                                                                        k, C_rp, C_col, C_val, S, proj, scatter,

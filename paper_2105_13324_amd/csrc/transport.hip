@@ -74,13 +74,25 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 // counter for the whole device took 13 ns whatever the waves did, so 3072
 // resident waves waited up to 40 us for their first chunk and again for the
 // refusal at the end (10^4 histories: 67 us); and with contiguous ranges a
-// wave works on one or two of a batch's problems instead of all of them, and
-// an XCD (workgroups b mod 8) on an eighth, so it drains less often and its L2
-// holds fewer problems' tables.
+// wave works on one or two of a batch's problems instead of all of them, so it
+// drains less often.
+//
+// Which range a queue has.  Workgroups go to the 8 XCDs in turn, so XCD x serves
+// queues x, x + 8, x + 16 and x + 24: they get four neighbouring ranges, an
+// eighth of the work for each XCD, whose L2 then holds the tables of an eighth
+// of a call's problems and, of one problem, an eighth of the views.  With the
+// q-th range for queue q an XCD worked at four places a quarter of the work
+// apart: 8 thoraxes 3.40 ms, 3.07 now, 16: 6.55, 6.04; both lines of Tl-201 in
+// two windows 8.91, 8.70; 1e7 forced-detection histories at 128^3 2.15, 2.12.
 enum : int { CLAIM_FIRST = 0, CLAIM_HOME, CLAIM_OTHERS };
 
+static_assert(N_QUEUES % 8 == 0, "as many queues for each XCD");
+__device__ __forceinline__ uint32_t range_of(uint32_t q) { return q % 8 * (N_QUEUES / 8) + q / 8; }
 __device__ __forceinline__ uint64_t queue_begin(uint64_t n_chunks, uint32_t q) {
-    return (n_chunks * q) / N_QUEUES;
+    return (n_chunks * range_of(q)) / N_QUEUES;
+}
+__device__ __forceinline__ uint64_t queue_end(uint64_t n_chunks, uint32_t q) {
+    return (n_chunks * (range_of(q) + 1)) / N_QUEUES;
 }
 // Waves that start on queue q: they take its first chunks without a claim.
 __device__ __forceinline__ uint32_t queue_waves(uint32_t q) {
@@ -88,10 +100,17 @@ __device__ __forceinline__ uint32_t queue_waves(uint32_t q) {
 }
 
 // This wave's queue, its rank among the queue's waves, and its copy of the
-// totals (recomputed where needed: scalar registers are short in the loop).
-__device__ __forceinline__ uint32_t wave_queue() { return blockIdx.x % N_QUEUES; }
+// totals, computed where they are needed: kept through the transport loop, they
+// take scalar registers that are short there (1e8 histories of the 128^3 thorax:
+// 3.60 ms, 3.63 when the compiler moves them out of it).
+__device__ __forceinline__ uint32_t block_here() {
+    uint32_t b = blockIdx.x;
+    asm volatile("" : "+s"(b));
+    return b;
+}
+__device__ __forceinline__ uint32_t wave_queue() { return block_here() % N_QUEUES; }
 __device__ __forceinline__ uint32_t wave_rank() {
-    return blockIdx.x / N_QUEUES * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return block_here() / N_QUEUES * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 __device__ __forceinline__ uint64_t* wave_totals(const TransportArgs& T, int p) {
     return T.descs[p].block_sums + (wave_rank() * N_QUEUES + wave_queue()) % ACC_COPIES * ACC_WORDS;
@@ -104,11 +123,12 @@ __device__ inline uint64_t claim_chunk(int& phase, uint64_t n_chunks, uint64_t* 
         unsigned long long k = 0;
         if (lane == 0) k = atomicAdd((unsigned long long*)queues + q * ACC_WORDS, 1ull);
         const uint64_t at = queue_begin(n_chunks, q) + queue_waves(q) + uniform64(k);
-        return at < queue_begin(n_chunks, q + 1) ? at : n_chunks;
+        return at < queue_end(n_chunks, q) ? at : n_chunks;
     };
     const uint32_t home = wave_queue();
+    asm volatile("" : "+s"(n_chunks));       // (as block_here)
     if (phase == CLAIM_FIRST) {
-        const uint64_t size = queue_begin(n_chunks, home + 1) - queue_begin(n_chunks, home);
+        const uint64_t size = queue_end(n_chunks, home) - queue_begin(n_chunks, home);
         phase = size > queue_waves(home) ? CLAIM_HOME : CLAIM_OTHERS;
         if (wave_rank() < size) return queue_begin(n_chunks, home) + wave_rank();
     }
@@ -122,7 +142,7 @@ __device__ inline uint64_t claim_chunk(int& phase, uint64_t n_chunks, uint64_t* 
         const uint32_t q = (uint32_t)lane;
         uint64_t dealt = 0;                        // chunks the queue's counter hands out
         if (q < N_QUEUES) {
-            const uint64_t size = queue_begin(n_chunks, q + 1) - queue_begin(n_chunks, q);
+            const uint64_t size = queue_end(n_chunks, q) - queue_begin(n_chunks, q);
             dealt = size > queue_waves(q) ? size - queue_waves(q) : 0;
         }
         bool some = dealt > 0;

@@ -375,7 +375,10 @@ class Simulator:
     def _check_ends(self):
         """Waits for the run; the status words and the event count (int64
         [5]).  Raises as check_status."""
-        st = self._ends.cpu().numpy()
+        try:
+            st = self._ends.cpu().numpy()
+        except RuntimeError as e:       # a HIP error that the run left
+            raise McError(f"{_lib.mc_error_string(MC_EDEVICE).decode()}: {e}") from e
         bits = int(st[0])
         if bits & (STATUS_BAD_MU | STATUS_NO_ACTIVITY | STATUS_BAD_ANGLE | STATUS_BAD_EVENT):
             rc = MC_EINVAL
@@ -387,8 +390,9 @@ class Simulator:
 
     def check_status(self):
         """What mc_check_status makes of the call's status: raises McError for
-        bad device input or a tally that left its fixed-point range; returns the
-        status array (list overflow and capped histories are reported there)."""
+        bad device input, a tally that left its fixed-point range or a HIP error
+        of the run; returns the status array (list overflow and capped histories
+        are reported there)."""
         return self._check_ends()[:4]
 
     def tallies(self):

@@ -95,7 +95,6 @@ bool plan(const mc_problem* probs, int n, Layout& L, bool cfd = false) {
     size_t off = 0;
     L.desc = off;   off += align256(sizeof(ProbDesc) * (size_t)n);
     L.prefix = off; off += align256(sizeof(uint64_t) * 2 * ((size_t)n + 1));
-    off += 256;                                  // spare (a workspace's size stays what it was)
     L.q.resize(n); L.q8.resize(n); L.pal.resize(n); L.runs.resize(n); L.bsum.resize(n); L.bcnt.resize(n);
     L.guide.resize(n); L.views.resize(n); L.kn.resize(n);
     L.lay.assign(n, 0); L.kern.assign(n, 0); L.hw.assign(n, 0);
@@ -292,9 +291,11 @@ int simulate_impl(const mc_problem* problems, int32_t n_problems, const mc_optio
         // most 1024, so a small call is one claim per wave (1e6 histories at
         // 128^3: 78 us of transport with claims of 384, 83 with 512, 99 with
         // 64; from 1e7 on 256 to 1024 measure within 2 %).  Forced detection
-        // costs more, and less evenly, per history: four claims or more per
-        // wave, of at most 256 (1e6: 361 us with 128, 381 with 512; 1e7:
-        // 2.78 ms with 256, 2.91 with 1024).
+        // costs more, and less evenly, per history: claims of at most 256, a
+        // quarter of the wave's share rounded up to whole multiples of 64 (two
+        // claims per wave or more; a call of 1e6 at 128^3 takes 329 us with
+        // claims of 128 or 256, of 3e6 677 us with 256 and 726 with 64; rounded
+        // down instead, 246 for 260 us at 6e5 and 528 for 514 at 2e6: no better).
         uint64_t work = 0;
         for (int i = 0; i < n_problems; ++i) work += hd[i].work_count;
         const uint64_t waves = (uint64_t)n_cu * (uint64_t)bpc * (uint64_t)(block / 64);

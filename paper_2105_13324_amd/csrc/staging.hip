@@ -21,8 +21,8 @@
 //    steps, evaluated in double precision.
 //
 // Four launches: one over everything that only needs the inputs, one workgroup
-// per problem that combines it, the runs and thresholds, the guide table and
-// codes.
+// per problem that combines it (small problems do without), the runs and
+// thresholds, the guide table and codes.
 #include <algorithm>
 
 #include "mc_internal.h"
@@ -196,7 +196,6 @@ __device__ inline void stage_scan(const ProbDesc& d) {
             sum += part_sum[v];
             runs += part_runs[v];
         }
-        // in the threshold table's place: it is written from launch 3 on
         parts_of(d)[blockIdx.x] = p;
         d.block_sums[blockIdx.x] = sum;
         d.block_cnt[blockIdx.x] = runs;

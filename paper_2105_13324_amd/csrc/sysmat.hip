@@ -807,7 +807,8 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
 }
 
 // Sum over each row r in [r0, r0 + n) (n <= T256) of its entries' terms,
-// done(r, sum) by one lane per non-empty row.  The rows' entries start at e0 +
+// done(r, sum) by one lane per non-empty row (and of an empty row that is taken
+// alone, with the sum 0).  The rows' entries start at e0 +
 // bound(0), bound(1), ..., bound(n); the term of entry first + k is load(first,
 // k) -> A, then value(A) -> double, so the loads of a tile are issued before
 // its gathers (first is in scalar registers).  All threads of a workgroup call,
@@ -1570,6 +1571,7 @@ __global__ __launch_bounds__(T256) void k_mlem_out(int64_t n_vox, const double* 
 // a scatter over single rows, 82 us now.
 constexpr int OS_LOADS = 8;
 constexpr int SPLIT_COUNTS = 4096;     // (subset, row) pairs of a chunk, counters in LDS
+static_assert(OSEM_MAX_SUBSETS <= SPLIT_COUNTS, "a row's counters at least");
 constexpr int SPLIT_LOADS = 4;
 
 // Rows per chunk: a subset's share of them fills three eighths of a tile on

@@ -67,11 +67,11 @@ def table_ops(n_hist, n_tent, n_kahn, n_real, cost=None):
 # counters read for a plain 1 GiB device copy (FETCH x2.0, WRITE x1.0); keyed
 # by a hash of the kernel sources so a changed kernel reports null.
 COPY_SCALE = {"fetch": 2.0, "write": 1.0}
-TRAFFIC_KIB = {"0448069114d180f5": {"fetch": 6849.69, "write": 4217.13}}
+TRAFFIC_KIB = {"adaba902283ae76e": {"fetch": 6728.69, "write": 4217.13}}
 # rocprofv3 --pmc SQ_INSTS_VALU of the same launch (and the dispatch time of
 # that run), keyed like the traffic
-VALU_COUNTERS = {"0448069114d180f5": {"workload": "thorax_128", "SQ_INSTS_VALU": 1.90312e9,
-                                      "kernel_ms": 3.7681}}
+VALU_COUNTERS = {"adaba902283ae76e": {"workload": "thorax_128", "SQ_INSTS_VALU": 1.90221e9,
+                                      "kernel_ms": 3.7613}}
 
 
 def kernel_source_hash() -> str:

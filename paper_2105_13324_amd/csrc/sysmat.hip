@@ -23,7 +23,7 @@
 // nothing; voxels with sens_i = 0 stay 0.  Only the non-empty rows are swept,
 // listed once per matrix, by groups of 1 to 64 lanes sized to their length;
 // of a large dense matrix the rows are streamed instead, a tile of entries at
-// a time, where that is the faster (lanes_per_row).
+// a time, where that is the faster (mlem_forward_lanes, mlem_update_lanes).
 #include <algorithm>
 
 #include "mc_internal.h"

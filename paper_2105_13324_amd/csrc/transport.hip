@@ -82,8 +82,9 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 // eighth of the work for each XCD, whose L2 then holds the tables of an eighth
 // of a call's problems and, of one problem, an eighth of the views.  With the
 // q-th range for queue q an XCD worked at four places a quarter of the work
-// apart: 8 thoraxes 3.40 ms, 3.07 now, 16: 6.55, 6.04; both lines of Tl-201 in
-// two windows 8.91, 8.70; 1e7 forced-detection histories at 128^3 2.15, 2.12.
+// apart: 12 thoraxes 2.74 ms and 5.0e7 L2 misses, 2.51 ms and 5.0e6 now; both
+// lines of Tl-201 in two windows 9.00 ms, 4.4e7, now 8.62 ms, 1.1e7; 1e7
+// forced-detection histories at 128^3 2.15, 2.12 ms.
 enum : int { CLAIM_FIRST = 0, CLAIM_HOME, CLAIM_OTHERS };
 
 static_assert(N_QUEUES % 8 == 0, "as many queues for each XCD");
